@@ -63,7 +63,8 @@ typedef enum { NCO_F32 = 0, NCO_F16_DEV = 1, NCO_BF16_DEV = 2, NCO_F64 = 3 } nco
 
 typedef enum { NCO_OP_BGK = 0, NCO_OP_MRT = 1, NCO_OP_NCO = 2, NCO_OP_STREAM = 3 } nco_op;
 
-/* Arithmetic of the network: float32 (VALU), float32 matrix cores, bf16
+/* Arithmetic of the network: float32 (VALU; in float64, on the matrix cores,
+ * for NCO_F64 storage), float32 matrix cores, bf16
  * matrix-core products with float32 accumulation, or float32 split over the
  * 16-bit matrix cores (NCO_MLP_F32_SPLIT: the first layer on the float32
  * matrix cores; each hidden-to-hidden layer's weights and activations split

@@ -174,6 +174,7 @@ struct nco_lattice {
     double omega_high[4] = {1.0, 1.0, 1.0, 1.0};
     float* net = nullptr;
     void* mfma_tab = nullptr;     // per-lane operand table + group gather table
+    void* f64_tab = nullptr;      // network table of float64 storage
     int width = 0, act = 0, mlp_prec = 0;
     int depth = 2;                // hidden layers
     int user_width = 0;           // width as given (a depth-3 network runs padded to 32)
@@ -334,6 +335,7 @@ hipEvent_t batch_event(int device, int k) { return g_side[device].ev[k]; }
 bool use_mfma(const nco_lattice* lat) {
     return lat->op == NCO_OP_NCO && lat->mlp_prec != NCO_MLP_F32 && lat->mfma_tab;
 }
+bool use_f64_net(const nco_lattice* lat) { return lat->op == NCO_OP_NCO && lat->storage == NCO_F64; }
 const float* mfma_lane_tab(const nco_lattice* lat) { return static_cast<const float*>(lat->mfma_tab); }
 const int* mfma_group_tab(const nco_lattice* lat) {
     return reinterpret_cast<const int*>(static_cast<const char*>(lat->mfma_tab) +
@@ -445,6 +447,8 @@ int launch_one(nco_lattice* lat, const void* fin, void* fout, long t, int slot =
     if (use_mfma(lat))
         HIP_TRY(launch_nco_mfma(lat->storage, lat->mlp_prec, fin, fout, a, mfma_lane_tab(lat), mfma_group_tab(lat),
                                 nullptr, lat->stream));
+    else if (use_f64_net(lat))
+        HIP_TRY(launch_nco_f64(fin, fout, a, lat->f64_tab, nullptr, lat->stream));
     else
         HIP_TRY(launch_step(lat->storage, fin, fout, a, lat->stream));
     return NCO_OK;
@@ -526,6 +530,7 @@ int nco_lattice_destroy(nco_lattice* lat) {
         if (lat->f[b]) hipFree(lat->f[b]);
     if (lat->net) hipFree(lat->net);
     if (lat->mfma_tab) hipFree(lat->mfma_tab);
+    if (lat->f64_tab) hipFree(lat->f64_tab);
     if (lat->staging) hipFree(lat->staging);
     if (lat->partial) hipFree(lat->partial);
     if (lat->small) hipFree(lat->small);
@@ -649,6 +654,15 @@ int nco_set_net_weights_depth(nco_lattice* lat, int depth, int width, int act, i
         HIP_TRY(hipStreamSynchronize(lat->stream));
         HIP_TRY(hipFree(lat->net));
         lat->net = nullptr;
+        if (lat->f64_tab) HIP_TRY(hipFree(lat->f64_tab));
+        lat->f64_tab = nullptr;
+    }
+    if (lat->storage == NCO_F64) {
+        std::vector<char> tab(nco_f64_table_bytes(W, depth));
+        nco_f64_prepare_table(params, W, act, depth, G.src, tab.data());
+        if (!lat->f64_tab) HIP_TRY(hipMalloc(&lat->f64_tab, tab.size()));
+        HIP_TRY(hipMemcpyAsync(lat->f64_tab, tab.data(), tab.size(), hipMemcpyHostToDevice, lat->stream));
+        HIP_TRY(hipStreamSynchronize(lat->stream));
     }
     if (!lat->net) HIP_TRY(hipMalloc(&lat->net, sizeof(float) * buf.size()));
     HIP_TRY(hipMemcpyAsync(lat->net, buf.data(), sizeof(float) * buf.size(), hipMemcpyHostToDevice,
@@ -1392,6 +1406,8 @@ int nco_read_rates(nco_lattice* lat, double* omega) {
     if (use_mfma(lat))
         HIP_TRY(launch_nco_mfma(lat->storage, lat->mlp_prec, lat->f[lat->cur], nullptr, a, mfma_lane_tab(lat),
                                 mfma_group_tab(lat), lat->staging, lat->stream));
+    else if (lat->storage == NCO_F64)
+        HIP_TRY(launch_nco_f64(lat->f[lat->cur], nullptr, a, lat->f64_tab, lat->staging, lat->stream));
     else
         HIP_TRY(launch_rates(lat->storage, lat->f[lat->cur], lat->staging, a, lat->stream));
     HIP_TRY(hipMemcpyAsync(omega, lat->staging, sizeof(double) * 4 * (size_t)lat->n, hipMemcpyDeviceToHost,

@@ -174,6 +174,13 @@ hipError_t launch_nco_mfma(int storage, int prec, const void* fin, void* fout, c
                            const float* lane_tab, const int* gtab, double* omega_out, hipStream_t st);
 hipError_t launch_nco_mfma_grouped(int storage, int prec, int act, const LaunchGroup& g, hipStream_t st);
 
+// NCO step of float64 lattices on the float64 matrix cores (nco_f64.hip);
+// omega_out != nullptr: the rates of the state in fin instead of a step.
+size_t nco_f64_table_bytes(int width, int depth);
+void nco_f64_prepare_table(const float* params, int width, int act, int depth, const int (*gsrc)[27], void* table);
+hipError_t launch_nco_f64(const void* fin, void* fout, const StepArgs& a, const void* table, double* omega_out,
+                          hipStream_t st);
+
 // Adjoint of a step (adjoint.hip), network width 32, float arithmetic.
 int adjoint_param_count();
 // Partial gradient rows of one launch_adjoint (several per 64-node block).

@@ -690,7 +690,12 @@ hipError_t launch_step(int storage, const void* fin, void* fout, const StepArgs&
     switch (a.op) {
         case OP_BGK: DISPATCH_STORAGE(storage, return (launch_step_op<SS, OP_BGK>(fin, fout, a, st)))
         case OP_MRT: DISPATCH_STORAGE(storage, return (launch_step_op<SS, OP_MRT>(fin, fout, a, st)))
-        case OP_NCO: DISPATCH_STORAGE(storage, return (launch_step_op<SS, OP_NCO>(fin, fout, a, st)))
+        case OP_NCO:
+            // Vector-unit network; float64 lattices run launch_nco_f64.
+            if (storage == ST_F32) return launch_step_op<ST_F32, OP_NCO>(fin, fout, a, st);
+            if (storage == ST_F16) return launch_step_op<ST_F16, OP_NCO>(fin, fout, a, st);
+            if (storage == ST_BF16) return launch_step_op<ST_BF16, OP_NCO>(fin, fout, a, st);
+            return hipErrorInvalidValue;
         case OP_NONE: DISPATCH_STORAGE(storage, return (launch_step_op<SS, OP_NONE>(fin, fout, a, st)))
         default: return hipErrorInvalidValue;
     }
@@ -734,7 +739,10 @@ hipError_t launch_step_grouped(int storage, int op, const LaunchGroup& g, hipStr
 }
 
 hipError_t launch_rates(int storage, const void* fin, double* omega, const StepArgs& a, hipStream_t st) {
-    DISPATCH_STORAGE(storage, return launch_rates_s<SS>(fin, omega, a, st))
+    if (storage == ST_F32) return launch_rates_s<ST_F32>(fin, omega, a, st);
+    if (storage == ST_F16) return launch_rates_s<ST_F16>(fin, omega, a, st);
+    if (storage == ST_BF16) return launch_rates_s<ST_BF16>(fin, omega, a, st);
+    return hipErrorInvalidValue;
 }
 
 hipError_t launch_init_equilibrium(int storage, void* f, const double* rho, const double* u, int n,

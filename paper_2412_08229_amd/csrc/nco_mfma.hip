@@ -44,6 +44,7 @@
 #include <cstring>
 
 #include "adjoint.h"
+#include "fold.h"
 #include "kernels.h"
 #include "stream.h"
 
@@ -53,9 +54,6 @@ namespace {
 
 constexpr int MW = 32;              // network width on this path
 constexpr int NODE_STRIDE = 29;     // LDS floats per node: 27 moments, 1.0, 0.0
-constexpr int KSTEPS = 10;          // K-steps of the eight parity-class products
-constexpr int GT_STRIDE = 12;       // ints per (pi, q) in the gather table
-constexpr int GT_ENTRIES = 6 * 4 * GT_STRIDE;
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
@@ -64,12 +62,6 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
-
-// K-step -> parity class ci = cx + 2 cy + 4 cz of the W1 rows it holds.
-__host__ __device__ constexpr int step_class(int st) {
-    constexpr int c[KSTEPS] = {0, 0, 0, 1, 2, 4, 3, 5, 6, 7};
-    return c[st];
-}
 
 // Offsets in the per-lane table (4-byte words per lane: LANE_WORDS).
 // float32 path:
@@ -865,19 +857,6 @@ __device__ __forceinline__ void nco_mfma_block(const typename Codec<S>::store_t*
 // TPW = 0: the six-wavefront tile of network_f32_psplit (16 nodes).
 constexpr int mfma_block_threads(int nodes, int tpw) { return tpw == 0 ? 6 * 64 : nodes / (16 * tpw) * 64; }
 
-// XCD-aware block order: workgroups are dispatched to the 8 XCDs in turn
-// (workgroup b to XCD b mod 8), each XCD with its own L2.  Block b takes
-// the logical block that makes the blocks of one XCD a contiguous run of
-// the lattice (XCD x: its i-th block is the i-th of the x-th run), so the
-// halo rows that neighbouring blocks share, and the second pull after the
-// network, meet in that XCD's L2.  A bijection of [0, n): the results do
-// not depend on it.
-__device__ __forceinline__ int xcd_block(int b, int n) {
-    constexpr int XCDS = 8;
-    const int x = b % XCDS, i = b / XCDS, q = n / XCDS, r = n % XCDS;
-    return x * q + min(x, r) + i;
-}
-
 // Waves per SIMD the register allocation must leave room for: 3 for the
 // split networks (156 VGPRs for tanh at depth 2; the others spill 12-57
 // registers into scratch and still run 1-7 % faster than at 2 waves, the
@@ -1585,29 +1564,6 @@ __global__ __launch_bounds__(256) void k_adjoint_mfma(const typename Codec<S>::s
         float v = 0.0f;
         for (int w = 0; w < 64; ++w) v += red[w * 32 + tid];
         out[OFF_B2 + tid] += (double)v;
-    }
-}
-
-// Parity class of row k of M (the bias row 27 and padding rows count as 0).
-int row_class(int k) {
-    if (k >= 27) return 0;
-    const int t = row_tensor(k);
-    return (t % 3) % 2 + 2 * (((t / 3) % 3) % 2) + 4 * ((t / 9) % 2);
-}
-
-// Canonical placement of the 28 K rows (27 moments + bias row 27) into the
-// 10 K-steps x 4 slots, grouped by parity class; -1 marks an empty slot.
-void class_slots(int slot_row[KSTEPS][4]) {
-    int fill[KSTEPS] = {0};
-    for (int st = 0; st < KSTEPS; ++st)
-        for (int q = 0; q < 4; ++q) slot_row[st][q] = -1;
-    for (int k = 0; k < 28; ++k) {
-        const int ci = row_class(k);
-        for (int st = 0; st < KSTEPS; ++st)
-            if (step_class(st) == ci && fill[st] < 4) {
-                slot_row[st][fill[st]++] = k;
-                break;
-            }
     }
 }
 
