@@ -1171,14 +1171,15 @@ __global__ __launch_bounds__(256) void k_adjoint_mfma(const typename Codec<S>::s
     const int wave = tid >> 6, lane = tid & 63, q = lane >> 4, c = lane & 15;
     // Phase B1: the network forward for tilde tau and the group sums, or the
     // values the forward step of this state kept (the same arithmetic on the
-    // same moments, so the same values).
+    // same moments, so the same values).  Places past the last node, which
+    // the forward step need not have written, read as zero.
     if (a.net_sums) {
         if (tid < NB) {
             const float* __restrict__ src = a.net_sums + ((size_t)blockIdx.x * NB + tid) * NET_SUMS_PER_NODE;
 #pragma unroll
-            for (int k = 0; k < 32; ++k) sdm[tid * 32 + k] = src[k];
+            for (int k = 0; k < 32; ++k) sdm[tid * 32 + k] = live ? src[k] : 0.0f;
 #pragma unroll
-            for (int n = 0; n < 4; ++n) sw[tid * 4 + n] = src[32 + n];
+            for (int n = 0; n < 4; ++n) sw[tid * 4 + n] = live ? src[32 + n] : 0.0f;
         }
     } else {
         network_f32<ACT, 2, TPW>(sm, sg, sw, lane_tab + lane * LANE_WORDS, wave, q, c, sdm);
