@@ -194,6 +194,7 @@ struct nco_lattice {
     // largest |k_x| of the modes.
     void* d_force = nullptr;
     int force_kx = 0;
+    int force_ky = 0;             // and the largest |k_y|
     // Velocity-dependent phase (Alvelius' rule): per-mode basis and |A|
     // [8 per mode], per-step draws phi, psi [steps][modes][2], mode-sum work
     // space and the coefficients of the current step.
@@ -438,7 +439,7 @@ int launch_one(nco_lattice* lat, const void* fin, void* fout, long t, int slot =
         // This step's coefficients from the velocity of the state it starts from.
         if (!replay)
             HIP_TRY(launch_force_phase(lat->storage, fin, lat->n, lat->nx, lat->ny, lat->nz, lat->d_fk,
-                                       lat->n_modes, lat->d_fpart, lat->d_fbasis,
+                                       lat->n_modes, lat->force_kx, lat->force_ky, lat->d_fpart, lat->d_fbasis,
                                        lat->d_fdraw + (size_t)(t % lat->force_steps) * lat->n_modes * 2, fh,
                                        slot >= 0 ? fh + 6 * lat->n_modes : nullptr, lat->stream));
         a.fhat = fh;
@@ -955,8 +956,11 @@ int nco_set_forcing_ex(nco_lattice* lat, int n_modes, const int* k, const double
     if (phase_rule && n_modes > 1024) return fail(NCO_E_INVALID, "at most 1024 modes with the phase rule");
     if (n_modes > 0 && lat->domain != NCO_DOMAIN_PERIODIC)
         return fail(NCO_E_UNSUPPORTED, "spectral forcing needs the periodic domain");
-    int kx_max = 0;
-    for (int m = 0; m < n_modes; ++m) kx_max = std::max(kx_max, std::abs(k[3 * m]));
+    int kx_max = 0, ky_max = 0;
+    for (int m = 0; m < n_modes; ++m) {
+        kx_max = std::max(kx_max, std::abs(k[3 * m]));
+        ky_max = std::max(ky_max, std::abs(k[3 * m + 1]));
+    }
     if (kx_max > FORCE_KX_MAX)
         return fail(NCO_E_UNSUPPORTED, "forced wavevectors need |k_x| <= %d (got %d)", FORCE_KX_MAX, kx_max);
     if (int rc = set_device(lat)) return rc;
@@ -1020,6 +1024,7 @@ int nco_set_forcing_ex(nco_lattice* lat, int n_modes, const int* k, const double
     }
     HIP_TRY(hipMalloc(&lat->d_force, 3 * (size_t)lat->n * (lat->storage == NCO_F64 ? sizeof(double) : sizeof(float))));
     lat->force_kx = kx_max;
+    lat->force_ky = ky_max;
     HIP_TRY(hipMalloc(&lat->d_fk, sizeof(int) * 3 * n_modes));
     HIP_TRY(hipMalloc(&lat->d_fhat, sizeof(double) * fh.size()));
     HIP_TRY(hipMemcpyAsync(lat->d_fk, k, sizeof(int) * 3 * n_modes, hipMemcpyHostToDevice, lat->stream));
@@ -1033,7 +1038,8 @@ int nco_set_forcing_ex(nco_lattice* lat, int n_modes, const int* k, const double
         }
         HIP_TRY(hipMalloc(&lat->d_fbasis, sizeof(double) * basis.size()));
         HIP_TRY(hipMalloc(&lat->d_fdraw, sizeof(double) * dr.size()));
-        HIP_TRY(hipMalloc(&lat->d_fpart, sizeof(double) * 6 * (size_t)n_modes * sums_partial_count(lat->n)));
+        HIP_TRY(hipMalloc(&lat->d_fpart, sizeof(double) * 6 * (size_t)n_modes *
+                                              mode_partial_blocks(lat->nx, lat->ny, lat->nz)));
         HIP_TRY(hipMalloc(&lat->d_fhat_cur, sizeof(double) * 6 * (size_t)n_modes));
         HIP_TRY(hipMalloc(&lat->d_fduhat, sizeof(double) * 6 * (size_t)n_modes));
         HIP_TRY(hipMemcpyAsync(lat->d_fbasis, basis.data(), sizeof(double) * basis.size(), hipMemcpyHostToDevice,
@@ -1317,8 +1323,8 @@ int backward(nco_lattice* lat, const double* dL_dk, int every, const double* dL_
             if (phase) {
                 // The force of step t also depends on x_t through its velocity modes.
                 const long ft = (lat->rec_force_t0 + t) % lat->force_steps;
-                HIP_TRY(launch_force_phase_adjoint(lat->storage, state(t - t0), lin, lout, a, lat->d_fpart,
-                                                   lat->d_fbasis, lat->d_fdraw + (size_t)ft * lat->n_modes * 2,
+                HIP_TRY(launch_force_phase_adjoint(lat->storage, state(t - t0), lin, lout, a, lat->force_kx,
+                                                   lat->force_ky, lat->d_fpart, lat->d_fbasis, lat->d_fdraw + (size_t)ft * lat->n_modes * 2,
                                                    phase_slot(lat, t) + 6 * lat->n_modes, lat->d_fduhat,
                                                    lat->stream));
             }

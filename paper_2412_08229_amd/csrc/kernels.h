@@ -47,11 +47,9 @@ struct StepArgs {
 };
 constexpr int NET_SUMS_PER_NODE = 36;
 
-// Phases of the spectral modes at a node, e^{i 2 pi (k_x x / nx + k_y y / ny
-// + k_z z / nz)}, as the product over the axes of integer powers of the
-// node's axis phasors e^{i 2 pi x / nx} (one sincospi of an exact fraction
-// per axis; binary powering, so a wavevector component k costs about
-// log2 |k| complex products).
+// Phases of the spectral modes: the phasor e^{i 2 pi x / n} of an axis (one
+// sincospi of an exact fraction) and its integer powers (binary powering, so
+// a wavevector component k costs about log2 |k| complex products).
 struct Phasor {
     double c, s;
 };
@@ -74,19 +72,6 @@ __device__ __forceinline__ Phasor phasor_pow(Phasor b, int k) {
         if (e > 1) p = phasor_mul(p, p);
     }
     return r;
-}
-
-struct NodePhasors {
-    Phasor x, y, z;
-};
-
-__device__ __forceinline__ NodePhasors node_phasors(int x, int y, int z, int nx, int ny, int nz) {
-    return NodePhasors{axis_phasor(x, nx), axis_phasor(y, ny), axis_phasor(z, nz)};
-}
-
-// e^{i k.x} for wavevector k (3 ints) at the node of `b`.
-__device__ __forceinline__ Phasor mode_phase(const int* k, const NodePhasors& b) {
-    return phasor_mul(phasor_mul(phasor_pow(b.x, k[0]), phasor_pow(b.y, k[1])), phasor_pow(b.z, k[2]));
 }
 
 // Force density at node idx for the current step, from the field
@@ -135,16 +120,19 @@ hipError_t launch_step(int storage, const void* fin, void* fout, const StepArgs&
 // periodic): phase 0 from the standard layout, phase 1 back to it.
 hipError_t launch_step_inplace(int storage, void* f, const StepArgs& a, int phase, hipStream_t st);
 // Velocity-dependent Alvelius phase: F_hat of this step's forced modes from
-// the state f (partial: nblocks(n) x n_modes x 6 doubles of work space), and
-// u_hat into uhat (6 doubles per mode) unless it is null.
+// the state f (partial: mode_partial_blocks x n_modes x 6 doubles of work
+// space; ky_max: the largest |k_y| of the modes), and u_hat into uhat (6
+// doubles per mode) unless it is null.
 // Force field of one step, F(x) = sum_m 2 Re(Fhat_m e^{i k_m . x}), on every
 // node in float64 arithmetic, written to out32 or out64 ([3][n]); kx_max
 // is the largest |k_x| of the modes (at most FORCE_KX_MAX).
 constexpr int FORCE_KX_MAX = 16;
 hipError_t launch_force_field(const StepArgs& a, int kx_max, float* out32, double* out64, hipStream_t st);
 hipError_t launch_force_phase(int storage, const void* f, int n, int nx, int ny, int nz, const int* fk,
-                              int n_modes, double* partial, const double* basis, const double* draw, double* fhat,
-                              double* uhat, hipStream_t st);
+                              int n_modes, int kx_max, int ky_max, double* partial, const double* basis,
+                              const double* draw, double* fhat, double* uhat, hipStream_t st);
+// Blocks of the mode sums on an nx x ny x nz lattice.
+int mode_partial_blocks(int nx, int ny, int nz);
 // Fine-to-coarse restriction (coarse extent x r = fine extent on every axis).
 hipError_t launch_restrict(int fine_storage, const void* fine, int fnx, int fny, int fnz, int coarse_storage,
                            void* coarse, int cnx, int cny, int cnz, int r, double factor, hipStream_t st);
@@ -201,11 +189,13 @@ hipError_t launch_grad_reduce_f64(const double* partial, int nblocks, double* st
 // state the step started from, lam_next = dL/d(state after it), a.fhat the
 // step's coefficients, uhat its u_hat, draw its (phi, psi) per mode;
 // lam_out (already holding the rest of dL/dx) gets the path x -> u_hat ->
-// theta1 -> F_hat -> source added.  partial: nblocks(n) x n_modes x 6
-// doubles of work space, duhat: 6 doubles per mode.  Float storages only.
+// theta1 -> F_hat -> source added.  partial: mode_partial_blocks x n_modes x 6
+// doubles of work space, duhat: 6 doubles per mode; kx_max, ky_max: the
+// largest |k_x| and |k_y| of the modes.  Float storages only.
 hipError_t launch_force_phase_adjoint(int storage, const void* x, const float* lam_next, float* lam_out,
-                                      const StepArgs& a, double* partial, const double* basis, const double* draw,
-                                      const double* uhat, double* duhat, hipStream_t st);
+                                      const StepArgs& a, int kx_max, int ky_max, double* partial,
+                                      const double* basis, const double* draw, const double* uhat, double* duhat,
+                                      hipStream_t st);
 
 // The same adjoint on the matrix cores (nco_mfma.hip): 256 nodes per block;
 // lane_tab and gtab are the float32 forward tables of mfma_prepare_tables,

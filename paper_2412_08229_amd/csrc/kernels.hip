@@ -11,6 +11,7 @@
 #include <algorithm>
 
 #include "kernels.h"
+#include "modes.h"
 #include "stream.h"
 
 namespace nco {
@@ -344,77 +345,19 @@ __global__ __launch_bounds__(256) void k_sums_partial(const typename Codec<S>::s
 }
 
 // Velocity-dependent forcing phase (Alvelius' rule, Sec. "Training Data -
-// Forced Isotropic Turbulence").  Stage 1: per block and forced mode m, the
-// partial sums of u(x) exp(-i k_m.x) over the block's nodes, six doubles
-// (Re, Im of u_x, u_y, u_z), at partial[(6 m + s) nblocks + block].  A
-// thread takes MODE_NPT nodes (coalesced, 256 apart) and keeps their
-// velocities in registers; the modes go in chunks of MODE_CHUNK, one block
-// reduction per chunk.
-constexpr int MODE_NPT = 8, MODE_CHUNK = 8, MODE_BLOCK_NODES = 256 * MODE_NPT;
-inline int mode_partial_blocks(int n) { return (n + MODE_BLOCK_NODES - 1) / MODE_BLOCK_NODES; }
-
+// Forced Isotropic Turbulence").  Stage 1: per block and forced mode, the
+// partial sums of u(x) exp(-i k_m.x) over the block's nodes.
 template <int S>
-__global__ __launch_bounds__(256) void k_mode_partials(const typename Codec<S>::store_t* __restrict__ f, int n,
-                                                       int nx, int ny, int nz, const int* __restrict__ fk,
-                                                       int n_modes, double* __restrict__ partial) {
-    __shared__ double part[6 * MODE_CHUNK][4];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    double u[MODE_NPT][3];
-    NodePhasors ph[MODE_NPT];
-#pragma unroll
-    for (int j = 0; j < MODE_NPT; ++j) {
-        const int idx = blockIdx.x * MODE_BLOCK_NODES + j * 256 + threadIdx.x;
-        u[j][0] = u[j][1] = u[j][2] = 0.0;
-        int x = 0, y = 0, z = 0;
-        if (idx < n) {
+__global__ __launch_bounds__(256) void k_mode_partials(const typename Codec<S>::store_t* __restrict__ f, int nx,
+                                                       int ny, int nz, ModeGrid g, const int* __restrict__ fk,
+                                                       int n_modes, int kx_max, int ky_max, double* __restrict__ partial) {
+    const int n = nx * ny * nz;
+    mode_partials(
+        [&](int idx, NodeIdx, double(&u)[3]) {
             double r;
-            macro_double<S>(f, n, idx, r, u[j][0], u[j][1], u[j][2]);
-            x = idx % nx;
-            y = (idx / nx) % ny;
-            z = idx / (nx * ny);
-        }
-        ph[j] = node_phasors(x, y, z, nx, ny, nz);
-    }
-    for (int m0 = 0; m0 < n_modes; m0 += MODE_CHUNK) {
-        double v[MODE_CHUNK][6];
-#pragma unroll
-        for (int c = 0; c < MODE_CHUNK; ++c) {
-#pragma unroll
-            for (int q = 0; q < 6; ++q) v[c][q] = 0.0;
-            const int m = m0 + c;
-            if (m < n_modes) {
-                const int* k = fk + 3 * m;
-#pragma unroll
-                for (int j = 0; j < MODE_NPT; ++j) {
-                    const Phasor e = mode_phase(k, ph[j]);
-#pragma unroll
-                    for (int d = 0; d < 3; ++d) {
-                        v[c][2 * d] += u[j][d] * e.c;
-                        v[c][2 * d + 1] -= u[j][d] * e.s;
-                    }
-                }
-            }
-        }
-#pragma unroll
-        for (int c = 0; c < MODE_CHUNK; ++c)
-#pragma unroll
-            for (int q = 0; q < 6; ++q)
-#pragma unroll
-                for (int off = 32; off > 0; off >>= 1) v[c][q] += __shfl_down(v[c][q], off, 64);
-        if (lane == 0)
-#pragma unroll
-            for (int c = 0; c < MODE_CHUNK; ++c)
-#pragma unroll
-                for (int q = 0; q < 6; ++q) part[6 * c + q][wave] = v[c][q];
-        __syncthreads();
-        if (threadIdx.x < 6 * MODE_CHUNK) {
-            const int e = threadIdx.x, m = m0 + e / 6;
-            if (m < n_modes)
-                partial[(size_t)(6 * m0 + e) * gridDim.x + blockIdx.x] =
-                    part[e][0] + part[e][1] + part[e][2] + part[e][3];
-        }
-        __syncthreads();
-    }
+            macro_double<S>(f, n, idx, r, u[0], u[1], u[2]);
+        },
+        nx, ny, nz, g, fk, n_modes, kx_max, ky_max, partial);
 }
 
 // Stage 2, one block per mode: u_hat = sum of the partials (fixed order) / N,
@@ -513,104 +456,18 @@ __global__ void k_check_sums(const double* __restrict__ sums, double mass0, doub
     if (bad) *flag = 1;
 }
 
-// Force field of one step, separable in x: with R_m(y, z) = 2 Fhat_m
-// e^{i 2 pi (k_y y / ny + k_z z / nz)},
-//   F(x, y, z) = sum_kx Re(S_kx(y, z) e^{i 2 pi kx x / nx}),
-//   S_kx(y, z) = sum of R_m over the modes m with k_x = kx (in mode order),
-// so a node sums 2 kx_max + 1 terms whatever the number of modes.  A block
-// serves `rows` consecutive (y, z) rows: its threads first form S for each
-// (row, kx) in LDS (one sincospi of an exact fraction per mode and row),
-// then each node takes its x phase e^{i 2 pi x / nx} (from an LDS table the
-// block fills, one sincospi per x) and the powers up to kx_max by
-// products.  float64 throughout.
-constexpr int FF_MAX_ROWS = 8;
-constexpr int FF_CHUNK = 32;
-constexpr int FF_XTAB = 1024;                   // x-phase table in LDS up to this extent
-
+// Force field of one step, F(x) = sum_m 2 Re(Fhat_m e^{i k_m.x}), on every
+// node.
 template <typename T>
-__global__ __launch_bounds__(256) void k_force_field(StepArgs a, int kx_max, int rows, T* __restrict__ out) {
-    __shared__ double2 S[FF_MAX_ROWS][2 * FORCE_KX_MAX + 1][3];
-    __shared__ double2 R[FF_MAX_ROWS][FF_CHUNK][3];
-    __shared__ int skx[FF_CHUNK];
-    __shared__ double2 xph[FF_XTAB];            // e^{i 2 pi x / nx}
-    const int row0 = blockIdx.x * rows;
-    const int nrows = a.ny * a.nz;
-    const int nk = 2 * kx_max + 1;
-    if (a.nx <= FF_XTAB)
-        for (int x = threadIdx.x; x < a.nx; x += blockDim.x) {
-            double sn, cs;
-            sincospi(2.0 * (double)x / (double)a.nx, &sn, &cs);
-            xph[x] = make_double2(cs, sn);
-        }
-    for (int e = threadIdx.x; e < rows * nk; e += blockDim.x)
-#pragma unroll
-        for (int d = 0; d < 3; ++d) S[e / nk][e % nk][d] = make_double2(0.0, 0.0);
-    for (int m0 = 0; m0 < a.n_modes; m0 += FF_CHUNK) {
-        const int mend = min(FF_CHUNK, a.n_modes - m0);
-        // R_m(row) for every (row, mode) of the chunk, one per thread.
-        for (int e = threadIdx.x; e < rows * FF_CHUNK; e += blockDim.x) {
-            const int rr = e / FF_CHUNK, c = e % FF_CHUNK, m = m0 + c, row = row0 + rr;
-            double2 v[3] = {make_double2(0.0, 0.0), make_double2(0.0, 0.0), make_double2(0.0, 0.0)};
-            if (c < mend && row < nrows) {
-                const int y = row % a.ny, z = row / a.ny;
-                const int* k = a.fk + 3 * m;
-                const long py = ((long)k[1] * y) % a.ny, pz = ((long)k[2] * z) % a.nz;
-                const double turn = (double)py / a.ny + (double)pz / a.nz;
-                double sn, cs;
-                sincospi(2.0 * turn, &sn, &cs);
-                const double* fh = a.fhat + 6 * m;
-#pragma unroll
-                for (int d = 0; d < 3; ++d)
-                    v[d] = make_double2(2.0 * (fh[2 * d] * cs - fh[2 * d + 1] * sn),
-                                        2.0 * (fh[2 * d] * sn + fh[2 * d + 1] * cs));
-            }
-#pragma unroll
-            for (int d = 0; d < 3; ++d) R[rr][c][d] = v[d];
-        }
-        if (threadIdx.x < FF_CHUNK) skx[threadIdx.x] = (int)threadIdx.x < mend ? a.fk[3 * (m0 + threadIdx.x)] : 0;
-        __syncthreads();
-        // S_kx += the chunk's modes with that k_x, in mode order.
-        for (int e = threadIdx.x; e < rows * nk; e += blockDim.x) {
-            const int rr = e / nk, kx = e % nk - kx_max;
-            double2 acc[3] = {S[rr][kx + kx_max][0], S[rr][kx + kx_max][1], S[rr][kx + kx_max][2]};
-            for (int c = 0; c < mend; ++c)
-                if (skx[c] == kx)
-#pragma unroll
-                    for (int d = 0; d < 3; ++d) {
-                        acc[d].x += R[rr][c][d].x;
-                        acc[d].y += R[rr][c][d].y;
-                    }
-#pragma unroll
-            for (int d = 0; d < 3; ++d) S[rr][kx + kx_max][d] = acc[d];
-        }
-        __syncthreads();
-    }
-    const int nodes = rows * a.nx;
-    for (int local = threadIdx.x; local < nodes; local += blockDim.x) {
+__global__ __launch_bounds__(256) void k_force_field(StepArgs a, int kx_max, T* __restrict__ out) {
+    __shared__ SynLds lds;
+    synthesis_rows(lds, a, kx_max, a.fhat, 2.0);
+    const int row0 = blockIdx.x * SYN_ROWS;
+    for (int local = threadIdx.x; local < SYN_ROWS * a.nx; local += blockDim.x) {
         const int r = local / a.nx, x = local - r * a.nx;
-        if (row0 + r >= nrows) break;
-        double sn, cs;
-        if (a.nx <= FF_XTAB) {
-            sn = xph[x].y;
-            cs = xph[x].x;
-        } else {
-            sincospi(2.0 * (double)x / (double)a.nx, &sn, &cs);
-        }
+        if (row0 + r >= a.ny * a.nz) break;
         double F[3];
-#pragma unroll
-        for (int d = 0; d < 3; ++d) F[d] = S[r][kx_max][d].x;
-        double pc = 1.0, ps = 0.0;                  // e^{i k theta}, k = 1 .. kx_max
-        for (int k = 1; k <= kx_max; ++k) {
-            const double t = pc * cs - ps * sn;
-            ps = pc * sn + ps * cs;
-            pc = t;
-#pragma unroll
-            for (int d = 0; d < 3; ++d) {
-                const double2 sp = S[r][kx_max + k][d], sm = S[r][kx_max - k][d];
-                // Re(sp e^{i k theta}) + Re(sm e^{-i k theta})
-                F[d] += (sp.x + sm.x) * pc - (sp.y - sm.y) * ps;
-            }
-        }
+        synthesis_node(lds, a.nx, kx_max, r, x, F);
         const size_t idx = (size_t)row0 * a.nx + local;
 #pragma unroll
         for (int d = 0; d < 3; ++d) out[(size_t)d * a.n + idx] = (T)F[d];
@@ -815,25 +672,26 @@ hipError_t launch_global_sums(int storage, const void* f, double* partial, doubl
 hipError_t launch_force_field(const StepArgs& a, int kx_max, float* out32, double* out64, hipStream_t st) {
     if (a.n_modes < 1 || !a.fk || !a.fhat || (!out32 && !out64) || kx_max < 0 || kx_max > FORCE_KX_MAX)
         return hipErrorInvalidValue;
-    const int rows = FF_MAX_ROWS;
-    const int nrows = a.ny * a.nz;
-    const unsigned nb = (unsigned)((nrows + rows - 1) / rows);
+    const unsigned nb = synthesis_blocks(a);
     if (out64)
-        hipLaunchKernelGGL(k_force_field<double>, dim3(nb), dim3(256), 0, st, a, kx_max, rows, out64);
+        hipLaunchKernelGGL(k_force_field<double>, dim3(nb), dim3(256), 0, st, a, kx_max, out64);
     else
-        hipLaunchKernelGGL(k_force_field<float>, dim3(nb), dim3(256), 0, st, a, kx_max, rows, out32);
+        hipLaunchKernelGGL(k_force_field<float>, dim3(nb), dim3(256), 0, st, a, kx_max, out32);
     return hipGetLastError();
 }
 
+int mode_partial_blocks(int nx, int ny, int nz) { return mode_grid(nx, ny, nz).blocks; }
+
 hipError_t launch_force_phase(int storage, const void* f, int n, int nx, int ny, int nz, const int* fk,
-                              int n_modes, double* partial, const double* basis, const double* draw, double* fhat,
-                              double* uhat, hipStream_t st) {
-    const int nb = mode_partial_blocks(n);
+                              int n_modes, int kx_max, int ky_max, double* partial, const double* basis, const double* draw,
+                              double* fhat, double* uhat, hipStream_t st) {
+    const ModeGrid g = mode_grid(nx, ny, nz);
     DISPATCH_STORAGE(storage, {
-        hipLaunchKernelGGL(k_mode_partials<SS>, dim3(nb), dim3(256), 0, st,
-                           static_cast<const typename Codec<SS>::store_t*>(f), n, nx, ny, nz, fk, n_modes, partial);
+        hipLaunchKernelGGL(k_mode_partials<SS>, dim3(g.blocks), dim3(256), 0, st,
+                           static_cast<const typename Codec<SS>::store_t*>(f), nx, ny, nz, g, fk, n_modes, kx_max, ky_max,
+                           partial);
         if (hipError_t e = hipGetLastError()) return e;
-        hipLaunchKernelGGL(k_force_phase, dim3(n_modes), dim3(256), 0, st, partial, nb, 1.0 / n, basis, draw,
+        hipLaunchKernelGGL(k_force_phase, dim3(n_modes), dim3(256), 0, st, partial, g.blocks, 1.0 / n, basis, draw,
                            fhat, uhat);
         return hipGetLastError();
     })
