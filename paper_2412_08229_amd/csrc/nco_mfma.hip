@@ -44,18 +44,16 @@
 #include <cstring>
 
 #include "adjoint.h"
-#include "fold.h"
 #include "kernels.h"
+#include "net_f32.h"
 #include "stream.h"
 
 namespace nco {
 
 namespace {
 
-constexpr int MW = 32;              // network width on this path
 constexpr int NODE_STRIDE = 29;     // LDS floats per node: 27 moments, 1.0, 0.0
 
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -63,15 +61,6 @@ typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 
-// Offsets in the per-lane table (4-byte words per lane: LANE_WORDS).
-// float32 path:
-constexpr int LT_A1 = 0;            // [t 2][st 10]    W1 rows / b1 as A operand
-constexpr int LT_A2 = 20;           // [u 2][t 2][r 4] W2 as A operand
-constexpr int LT_B2 = 36;           // [u 2][r 4]      b2 as accumulator init
-constexpr int LT_W3 = 44;           // [u 2][r 4][n 4] W3 / 48
-constexpr int LT_B3 = 76;           // [n 4]
-constexpr int LT_A2B = 80;          // [v 2][t 2][r 4] W2b as A operand (depth 3)
-constexpr int LT_B2B = 96;          // [v 2][r 4]      b2b as accumulator init (depth 3)
 // Split arithmetic (network_split): per layer the parts of its A operand as
 // packed pairs in the K slots of the 16x16x32 product ([t or u 2][part 3][4
 // words]: f16 head and remainder for tanh, bf16 head, middle and tail for
@@ -99,26 +88,6 @@ constexpr int LB_B3 = 56;           // [n 4]
 constexpr int LB_SM = 60;           // [bit 3][4 words] sign masks of classes with that bit
 constexpr int LB_A2B = 72;          // [v 2][4 words]  W2b (depth 3)
 constexpr int LB_B2B = 80;          // [v 2][r 4]      b2b (depth 3)
-constexpr int LANE_WORDS = 144;
-
-// Activation as evaluated on this path.  For tanh the pre-activation arrives
-// scaled by kappa = 2 log2(e) and the function returns r = 1 / (1 + 2^(kappa z)),
-// so that tanh(z) = 1 - 2 r; the affine map 1 - 2 r is folded into the next
-// layer's weights and bias on the host (and into W3, b3 for the group sum),
-// which leaves exp2, add and reciprocal per value.  r saturates correctly
-// (2^+inf = inf gives 0).
-template <int ACT>
-__device__ __forceinline__ float act_scaled(float x) {
-    if constexpr (ACT == ACT_RELU) {
-        return fmaxf(x, 0.0f);
-    } else {
-        return __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(x));
-    }
-}
-
-__device__ __forceinline__ f32x4 mfma4(float a, float b, f32x4 c) {
-    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-}
 
 __device__ __forceinline__ f32x4 mfma32(u32x4 a, u32x4 b, f32x4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a),
@@ -175,168 +144,13 @@ __device__ __forceinline__ float act_split(float x) {
     return __builtin_amdgcn_rcpf(fmaf(__builtin_amdgcn_exp2f(x), S, S));
 }
 
-// Output layer on the group sum of one node tile and the rate squashing;
-// lanes of group q = 0 write the four rates of node (tile, c) to LDS, or with
-// RAW the pre-squash outputs tilde tau_n (for the adjoint).
-template <bool RAW = false>
-__device__ __forceinline__ void output_layer(const f32x4 (&acc)[2], const float* __restrict__ w3,
-                                             const float* __restrict__ b3, int q, float* __restrict__ sw_node,
-                                             float* __restrict__ tt_node = nullptr) {
-    float pn[4];
-#pragma unroll
-    for (int n = 0; n < 4; ++n) {
-        float v = 0.0f;
-#pragma unroll
-        for (int u = 0; u < 2; ++u)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) v = fmaf(w3[(u * 4 + r) * 4 + n], acc[u][r], v);
-        v += __shfl_xor(v, 16, 64);
-        v += __shfl_xor(v, 32, 64);
-        pn[n] = v;
-    }
-    if (q == 0) {
-#pragma unroll
-        for (int n = 0; n < 4; ++n) {
-            const float t = pn[n] + b3[n];
-            sw_node[n] = RAW ? t : 1.0f / (0.5f + 0.5f / (1.0f + expf(t)));
-            if (tt_node) tt_node[n] = t;
-        }
-    }
-}
-
-// Layer 1 of one axis permutation on the float32 matrix cores for lane group
-// q of a node tile (mrow: the node's moment row, ge: the permutation's gather
-// slots of the group): the eight parity-class partial products over 10
-// K-steps, then their Walsh-Hadamard transform over the class index, after
-// which Y[s][t] is the pre-activation of reflection pattern s (hidden rows
-// 16 t + 4 q + r).
-__device__ __forceinline__ void layer1_reflections(const float (&A1)[2][KSTEPS], const float* __restrict__ mrow,
-                                                   const int* __restrict__ ge, f32x4 (&Y)[8][2]) {
-    // Moment operand of this permutation, one K-step per register.
-    float b[KSTEPS];
-#pragma unroll
-    for (int st = 0; st < KSTEPS; ++st) b[st] = mrow[ge[st]];
-#pragma unroll
-    for (int ci = 0; ci < 8; ++ci) {
-        Y[ci][0] = f32x4{0.f, 0.f, 0.f, 0.f};
-        Y[ci][1] = f32x4{0.f, 0.f, 0.f, 0.f};
-    }
-#pragma unroll
-    for (int st = 0; st < KSTEPS; ++st)
-#pragma unroll
-        for (int t = 0; t < 2; ++t) Y[step_class(st)][t] = mfma4(A1[t][st], b[st], Y[step_class(st)][t]);
-#pragma unroll
-    for (int bit = 1; bit < 8; bit <<= 1)
-#pragma unroll
-        for (int ci = 0; ci < 8; ++ci)
-            if (!(ci & bit))
-#pragma unroll
-                for (int t = 0; t < 2; ++t) {
-                    const f32x4 u0 = Y[ci][t], u1 = Y[ci | bit][t];
-                    Y[ci][t] = u0 + u1;
-                    Y[ci | bit][t] = u0 - u1;
-                }
-}
-
-// One axis permutation p of a node tile on the float32 matrix cores (ge:
-// the permutation's gather slots of lane group q), the arithmetic of one
-// pass of network_f32's permutation loop: layer 1 of the 8 reflections, the
-// hidden layers (DEPTH 2 or 3), and each activation of the last hidden layer
-// handed to sink(s, u, r, value) (reflection s, hidden row 16 u + 4 q + r)
-// in the order network_f32 adds it to the group sum.
-template <int ACT, int DEPTH, typename Sink>
-__device__ __forceinline__ void permutation_f32(const float (&A1)[2][KSTEPS], const float (&A2)[2][2][4],
-                                                const float (&B2)[2][4], const float* __restrict__ lt,
-                                                const float* __restrict__ mrow, const int* __restrict__ ge,
-                                                Sink&& sink) {
-    f32x4 Y[8][2];
-    layer1_reflections(A1, mrow, ge, Y);
-    if constexpr (DEPTH == 3) {
-        // Unrolled: Y[s] must stay in registers.
-#pragma unroll
-        for (int s = 0; s < 8; ++s) {
-            float h1v[2][4];
-#pragma unroll
-            for (int t = 0; t < 2; ++t)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) h1v[t][r] = act_scaled<ACT>(Y[s][t][r]);
-            f32x4 c2[2];
-#pragma unroll
-            for (int u = 0; u < 2; ++u) c2[u] = f32x4{B2[u][0], B2[u][1], B2[u][2], B2[u][3]};
-#pragma unroll
-            for (int t = 0; t < 2; ++t)
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-#pragma unroll
-                    for (int u = 0; u < 2; ++u) c2[u] = mfma4(A2[u][t][r], h1v[t][r], c2[u]);
-            float h2v[2][4];
-#pragma unroll
-            for (int u = 0; u < 2; ++u)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) h2v[u][r] = act_scaled<ACT>(c2[u][r]);
-            f32x4 c3[2];
-#pragma unroll
-            for (int v = 0; v < 2; ++v)
-                c3[v] = f32x4{lt[LT_B2B + v * 4], lt[LT_B2B + v * 4 + 1], lt[LT_B2B + v * 4 + 2],
-                              lt[LT_B2B + v * 4 + 3]};
-#pragma unroll
-            for (int t = 0; t < 2; ++t)
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-#pragma unroll
-                    for (int v = 0; v < 2; ++v) c3[v] = mfma4(lt[LT_A2B + v * 8 + t * 4 + r], h2v[t][r], c3[v]);
-#pragma unroll
-            for (int v = 0; v < 2; ++v)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) sink(s, v, r, act_scaled<ACT>(c3[v][r]));
-        }
-        return;
-    }
-    // Layer 2 and the two activations, software-pipelined over the
-    // reflections: while the 16 products of reflection s run on the matrix
-    // cores, the vector units activate layer 1 of reflection s + 1 and layer
-    // 2 of reflection s - 1 (independent of them).
-    f32x4 h1[2], c2p[2];
-#pragma unroll
-    for (int t = 0; t < 2; ++t)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) h1[t][r] = act_scaled<ACT>(Y[0][t][r]);
-#pragma unroll
-    for (int s = 0; s < 8; ++s) {
-        f32x4 c2[2];
-#pragma unroll
-        for (int u = 0; u < 2; ++u) c2[u] = f32x4{B2[u][0], B2[u][1], B2[u][2], B2[u][3]};
-#pragma unroll
-        for (int t = 0; t < 2; ++t)
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-#pragma unroll
-                for (int u = 0; u < 2; ++u) c2[u] = mfma4(A2[u][t][r], h1[t][r], c2[u]);
-        if (s > 0) {
-#pragma unroll
-            for (int u = 0; u < 2; ++u)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) sink(s - 1, u, r, act_scaled<ACT>(c2p[u][r]));
-        }
-        if (s < 7) {
-#pragma unroll
-            for (int t = 0; t < 2; ++t)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) h1[t][r] = act_scaled<ACT>(Y[s + 1][t][r]);
-        }
-#pragma unroll
-        for (int u = 0; u < 2; ++u) c2p[u] = c2[u];
-    }
-#pragma unroll
-    for (int u = 0; u < 2; ++u)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) sink(7, u, r, act_scaled<ACT>(c2p[u][r]));
-}
-
-// The float32 network's weights in registers, from the lane table.
+// The float32 network's weights in registers, from the lane table (the third
+// layer's stay in the table).
 struct NetF32Regs {
-    float A1[2][KSTEPS], A2[2][2][4], B2[2][4];
-    __device__ __forceinline__ explicit NetF32Regs(const float* __restrict__ lt) {
+    float A1[2][KSTEPS], A2[2][2][4];
+    f32x4 B2[2];
+    const float* __restrict__ lt;
+    __device__ __forceinline__ explicit NetF32Regs(const float* __restrict__ table) : lt(table) {
 #pragma unroll
         for (int t = 0; t < 2; ++t)
 #pragma unroll
@@ -352,12 +166,30 @@ struct NetF32Regs {
 #pragma unroll
             for (int r = 0; r < 4; ++r) B2[u][r] = lt[LT_B2 + u * 4 + r];
     }
+    // Layer 1 of one axis permutation for lane group q of a node tile (mrow:
+    // the node's moment row, ge: the permutation's gather slots of the group).
+    __device__ __forceinline__ void layer1(const float* __restrict__ mrow, const int* __restrict__ ge,
+                                           f32x4 (&Y)[8][2]) const {
+        layer1_f32([&](int t, int st) { return A1[t][st]; }, [&](int st) { return mrow[ge[st]]; }, Y);
+    }
+    template <int ACT, int DEPTH, int NS, typename Sink>
+    __device__ __forceinline__ void hidden(const f32x4 (&Y)[8][2], Sink&& sink) const {
+        f32x4 B2b[2] = {B2[0], B2[1]};
+        if constexpr (DEPTH == 3)
+#pragma unroll
+            for (int v = 0; v < 2; ++v)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) B2b[v][r] = lt[LT_B2B + v * 4 + r];
+        hidden_reflections<ACT, DEPTH, NS>([&](int u, int t, int r) { return A2[u][t][r]; }, B2,
+                                           [&](int v, int t, int r) { return lt[LT_A2B + v * 8 + t * 4 + r]; }, B2b, Y,
+                                           sink);
+    }
 };
 
 // The group sum of a node tile and what follows it: with sums (a step
 // whose adjoint follows) the sum and tilde tau into sums[node]
-// [NET_SUMS_PER_NODE] and the rates into sw, else the rates into sw; as at
-// the end of network_f32's tile loop.
+// [NET_SUMS_PER_NODE] (row 16 u + 4 q + r in lane (q, c)) and the rates into
+// sw, else the rates into sw.
 __device__ __forceinline__ void finish_tile(const f32x4 (&acc)[2], const float* __restrict__ lt, int q, int node,
                                             float* __restrict__ sw, float* __restrict__ sums) {
     if (sums) {
@@ -372,11 +204,9 @@ __device__ __forceinline__ void finish_tile(const f32x4 (&acc)[2], const float* 
     }
 }
 
-// s2 != nullptr (adjoint): sw receives tilde tau instead of the rates and
-// s2[node][32] the group sum of the folded second-layer activations (row
-// 16 u + 4 q + r in lane (q, c)).  sums != nullptr (a step whose adjoint
-// follows): sw receives the rates, and sums[node][NET_SUMS_PER_NODE] (global
-// memory, the block's nodes) the same group sums and tilde tau.
+// sums != nullptr (a step whose adjoint follows): the network values of the
+// block's nodes are kept (finish_tile).  s2 != nullptr (adjoint): sw receives
+// tilde tau instead of the rates and s2[node][32] the group sum.
 //
 // DEPTH = 3: a third hidden layer (W2b, b2b) between the second layer and
 // the group sum, one more product per group element whose B operand is the
@@ -386,24 +216,9 @@ __device__ __forceinline__ void finish_tile(const f32x4 (&acc)[2], const float* 
 template <int ACT, int DEPTH = 2, int TPW = 4>
 __device__ __forceinline__ void network_f32(const float* __restrict__ sm, const int* __restrict__ sg,
                                             float* __restrict__ sw, const float* __restrict__ lt, int wave,
-                                            int q, int c, float* __restrict__ s2 = nullptr,
-                                            float* __restrict__ sums = nullptr) {
-    float A1[2][KSTEPS], A2[2][2][4], B2[2][4];
-#pragma unroll
-    for (int t = 0; t < 2; ++t)
-#pragma unroll
-        for (int st = 0; st < KSTEPS; ++st) A1[t][st] = lt[LT_A1 + t * KSTEPS + st];
-#pragma unroll
-    for (int u = 0; u < 2; ++u)
-#pragma unroll
-        for (int t = 0; t < 2; ++t)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) A2[u][t][r] = lt[LT_A2 + u * 8 + t * 4 + r];
-#pragma unroll
-    for (int u = 0; u < 2; ++u)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) B2[u][r] = lt[LT_B2 + u * 4 + r];
-
+                                            int q, int c, float* __restrict__ sums = nullptr,
+                                            float* __restrict__ s2 = nullptr) {
+    const NetF32Regs w(lt);
 #pragma unroll 1
     for (int j = 0; j < TPW; ++j) {
         const int node = wave * 16 * TPW + j * 16 + c;
@@ -412,88 +227,9 @@ __device__ __forceinline__ void network_f32(const float* __restrict__ sm, const 
 #pragma unroll 1
         for (int p = 0; p < 6; ++p) {
             f32x4 Y[8][2];
-            layer1_reflections(A1, mrow, sg + (p * 4 + q) * GT_STRIDE, Y);
-            if constexpr (DEPTH == 3) {
-                // Unrolled: Y[s] must stay in registers.
-#pragma unroll
-                for (int s = 0; s < 8; ++s) {
-                    float h1v[2][4];
-#pragma unroll
-                    for (int t = 0; t < 2; ++t)
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) h1v[t][r] = act_scaled<ACT>(Y[s][t][r]);
-                    f32x4 c2[2];
-#pragma unroll
-                    for (int u = 0; u < 2; ++u) c2[u] = f32x4{B2[u][0], B2[u][1], B2[u][2], B2[u][3]};
-#pragma unroll
-                    for (int t = 0; t < 2; ++t)
-#pragma unroll
-                        for (int r = 0; r < 4; ++r)
-#pragma unroll
-                            for (int u = 0; u < 2; ++u) c2[u] = mfma4(A2[u][t][r], h1v[t][r], c2[u]);
-                    float h2v[2][4];
-#pragma unroll
-                    for (int u = 0; u < 2; ++u)
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) h2v[u][r] = act_scaled<ACT>(c2[u][r]);
-                    f32x4 c3[2];
-#pragma unroll
-                    for (int v = 0; v < 2; ++v)
-                        c3[v] = f32x4{lt[LT_B2B + v * 4], lt[LT_B2B + v * 4 + 1], lt[LT_B2B + v * 4 + 2],
-                                      lt[LT_B2B + v * 4 + 3]};
-#pragma unroll
-                    for (int t = 0; t < 2; ++t)
-#pragma unroll
-                        for (int r = 0; r < 4; ++r)
-#pragma unroll
-                            for (int v = 0; v < 2; ++v)
-                                c3[v] = mfma4(lt[LT_A2B + v * 8 + t * 4 + r], h2v[t][r], c3[v]);
-#pragma unroll
-                    for (int v = 0; v < 2; ++v)
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) acc[v][r] += act_scaled<ACT>(c3[v][r]);
-                }
-                continue;
-            }
-            // Layer 2 and the two activations, software-pipelined over the
-            // reflections: while the 16 products of reflection s run on the
-            // matrix cores, the vector units activate layer 1 of reflection
-            // s + 1 and layer 2 of reflection s - 1 (independent of them).
-            f32x4 h1[2], c2p[2];
-#pragma unroll
-            for (int t = 0; t < 2; ++t)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) h1[t][r] = act_scaled<ACT>(Y[0][t][r]);
-#pragma unroll
-            for (int s = 0; s < 8; ++s) {
-                f32x4 c2[2];
-#pragma unroll
-                for (int u = 0; u < 2; ++u) c2[u] = f32x4{B2[u][0], B2[u][1], B2[u][2], B2[u][3]};
-#pragma unroll
-                for (int t = 0; t < 2; ++t)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r)
-#pragma unroll
-                        for (int u = 0; u < 2; ++u) c2[u] = mfma4(A2[u][t][r], h1[t][r], c2[u]);
-                if (s > 0) {
-#pragma unroll
-                    for (int u = 0; u < 2; ++u)
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) acc[u][r] += act_scaled<ACT>(c2p[u][r]);
-                }
-                if (s < 7) {
-#pragma unroll
-                    for (int t = 0; t < 2; ++t)
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) h1[t][r] = act_scaled<ACT>(Y[s + 1][t][r]);
-                }
-#pragma unroll
-                for (int u = 0; u < 2; ++u) c2p[u] = c2[u];
-            }
-#pragma unroll
-            for (int u = 0; u < 2; ++u)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) acc[u][r] += act_scaled<ACT>(c2p[u][r]);
+            w.layer1(mrow, sg + (p * 4 + q) * GT_STRIDE, Y);
+            reflections(Y);
+            w.template hidden<ACT, DEPTH, 8>(Y, [&](int, const f32x4(&z)[2]) { add_act<ACT>(z, acc); });
         }
         if (s2) {
 #pragma unroll
@@ -501,54 +237,60 @@ __device__ __forceinline__ void network_f32(const float* __restrict__ sm, const 
 #pragma unroll
                 for (int r = 0; r < 4; ++r) s2[node * 32 + 16 * u + 4 * q + r] = acc[u][r];
             output_layer<true>(acc, lt + LT_W3, lt + LT_B3, q, sw + node * 4);
-        } else if (sums) {
-            float* __restrict__ row = sums + (size_t)node * NET_SUMS_PER_NODE;
-#pragma unroll
-            for (int u = 0; u < 2; ++u)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) row[16 * u + 4 * q + r] = acc[u][r];
-            output_layer(acc, lt + LT_W3, lt + LT_B3, q, sw + node * 4, row + 32);
         } else {
-            output_layer(acc, lt + LT_W3, lt + LT_B3, q, sw + node * 4);
+            finish_tile(acc, lt, q, node, sw, sums);
         }
     }
 }
 
-// Small lattices: one 16-node tile per block and its six axis permutations
-// on six wavefronts (wavefront p takes permutation p), where blocks of one
-// tile per wavefront leave most SIMDs idle and run the 48 group elements of
-// a tile in series.  Each wavefront writes the last-layer activations of its
-// permutation to vals[p][s][node][hidden] in LDS; wavefront 0 adds them in
-// the order (permutation, reflection) of network_f32, so the group sums, the
-// rates and the step equal those of the other block shapes bit for bit.
-constexpr int PSPLIT_ROW = 36;      // floats per (p, s, node) row of vals: 32 hidden, 16-byte aligned rows
-constexpr int PSPLIT_VALS = 6 * 8 * 16 * PSPLIT_ROW;
+// Small lattices: one 16-node tile per block on twelve wavefronts, three per
+// SIMD: wavefront w takes half w % 2 (four reflections) of axis permutation
+// w / 2, where blocks of one tile per wavefront leave most SIMDs idle and run
+// the 48 group elements of a tile in series.  Each wavefront leaves the
+// last-layer activations of its elements in LDS (vals [element][node]
+// [hidden]); 512 threads add one (node, hidden) each in the order of the
+// other block shapes, so the group sums, the rates and the step equal theirs
+// bit for bit.
+constexpr int PSPLIT_WAVES = 12;
+constexpr int PSPLIT_ROW = 36;      // floats per (element, node) row of vals: 32 hidden, 16-byte aligned rows
+constexpr int PSPLIT_VALS = 48 * 16 * PSPLIT_ROW;
 constexpr int PSPLIT_FROW = 28;     // floats per node of the pulled populations, after vals in LDS
 constexpr int PSPLIT_LDS = PSPLIT_VALS + 16 * PSPLIT_FROW;
 
 template <int ACT, int DEPTH>
 __device__ __forceinline__ void network_f32_psplit(const float* __restrict__ sm, const int* __restrict__ sg,
-                                                   float* __restrict__ sw, const float* __restrict__ lt, int wave,
+                                                   float* __restrict__ sw, const float* __restrict__ lt, int tid,
                                                    int q, int c, float* __restrict__ vals,
                                                    float* __restrict__ sums) {
-    const NetF32Regs w(lt);
-    permutation_f32<ACT, DEPTH>(w.A1, w.A2, w.B2, lt, sm + c * NODE_STRIDE, sg + (wave * 4 + q) * GT_STRIDE,
-                                [&](int s, int u, int r, float v) {
-                                    vals[((wave * 8 + s) * 16 + c) * PSPLIT_ROW + 16 * u + 4 * q + r] = v;
-                                });
+    const int wave = tid >> 6;
+    {
+        const NetF32Regs w(lt);
+        f32x4 Y[8][2];
+        w.layer1(sm + c * NODE_STRIDE, sg + ((wave >> 1) * 4 + q) * GT_STRIDE, Y);
+        reflections_half(Y, wave & 1);
+        float* __restrict__ mine = vals + (wave * 4 * 16 + c) * PSPLIT_ROW + 4 * q;
+        w.template hidden<ACT, DEPTH, 4>(Y, [&](int s, const f32x4(&z)[2]) {
+            f32x4 h[2];
+            act_f32<ACT>(z, h);
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+                *reinterpret_cast<f32x4*>(mine + s * 16 * PSPLIT_ROW + 16 * u) = h[u];
+        });
+    }
+    __syncthreads();
+    if (tid < 16 * 32) {
+        float* __restrict__ col = vals + (tid >> 5) * PSPLIT_ROW + (tid & 31);
+        float acc = 0.0f;
+#pragma unroll
+        for (int g = 0; g < 48; ++g) acc += col[g * 16 * PSPLIT_ROW];
+        *col = acc;
+    }
     __syncthreads();
     if (wave == 0) {
-        f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
-#pragma unroll 4
-        for (int ps = 0; ps < 48; ++ps) {
-            const float* __restrict__ row = vals + (ps * 16 + c) * PSPLIT_ROW + 4 * q;
+        f32x4 acc[2];
 #pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                const f32x4 v = *reinterpret_cast<const f32x4*>(row + 16 * u);
-#pragma unroll
-                for (int r = 0; r < 4; ++r) acc[u][r] += v[r];
-            }
-        }
+        for (int u = 0; u < 2; ++u)
+            acc[u] = *reinterpret_cast<const f32x4*>(vals + c * PSPLIT_ROW + 16 * u + 4 * q);
         finish_tile(acc, lt, q, c, sw, sums);
     }
 }
@@ -637,7 +379,7 @@ __device__ __forceinline__ void split_layer(const u32x4 (&A)[2][3], const float 
 // bf16 network (the reflections as sign flips of the moment operand's
 // parts, in Gray-code order) and scaled back by 1 / sigma_1; 12 products of
 // 16x16x32 per group element and 16-node tile at depth 2.  ReLU: layer 1 on
-// the float32 matrix cores with the Walsh-Hadamard fold (layer1_reflections;
+// the float32 matrix cores with the Walsh-Hadamard fold (layer1_f32, reflections;
 // split into three bf16 parts it would take 12 more products, and these
 // kernels are bound by the matrix cores), the hidden-to-hidden layers as 12
 // split bf16 products each.
@@ -698,7 +440,8 @@ __device__ __forceinline__ void network_split(const float* __restrict__ sm, cons
                 for (int i = 0; i < 8; ++i) x[i] = mrow[ge[i]];
                 split_input<ACT>(x, neg1, bp);
             } else {
-                layer1_reflections(A1, mrow, ge, Y);
+                layer1_f32([&](int t, int st) { return A1[t][st]; }, [&](int st) { return mrow[ge[st]]; }, Y);
+                reflections(Y);
             }
             // tanh: the 8 reflections in Gray-code order, consecutive ones
             // differing in one reflection bit: one mask XOR per word and part.
@@ -839,7 +582,7 @@ struct BlockLds {
     float* sm;      // [NODES][NODE_STRIDE] moments, then hidden activations
     int* sg;        // [GT_ENTRIES] gather table
     float* sw;      // [NODES][4] rates
-    float* vals = nullptr;  // [PSPLIT_VALS] last-layer activations (six-wavefront tiles)
+    float* vals = nullptr;  // [PSPLIT_LDS] activations and populations (twelve-wavefront tiles)
 };
 
 template <int S, int ACT, bool RATES, int PREC, int NODES, int DEPTH = 2, int TPW = 4, bool SUMS = false>
@@ -854,8 +597,8 @@ __device__ __forceinline__ void nco_mfma_block(const typename Codec<S>::store_t*
     __shared__ float lds_sw[(NODES) * 4];            \
     const BlockLds lds{lds_sm, lds_sg, lds_sw};
 
-// TPW = 0: the six-wavefront tile of network_f32_psplit (16 nodes).
-constexpr int mfma_block_threads(int nodes, int tpw) { return tpw == 0 ? 6 * 64 : nodes / (16 * tpw) * 64; }
+// TPW = 0: the twelve-wavefront tile of network_f32_psplit (16 nodes).
+constexpr int mfma_block_threads(int nodes, int tpw) { return tpw == 0 ? PSPLIT_WAVES * 64 : nodes / (16 * tpw) * 64; }
 
 // Waves per SIMD the register allocation must leave room for: 3 for the
 // split networks (156 VGPRs for tanh at depth 2; the others spill 12-57
@@ -926,10 +669,10 @@ __device__ __forceinline__ void nco_mfma_block(const typename Codec<S>::store_t*
 
     // Phase A: pull and transform to moments.
     if constexpr (TPW == 0) {
-        // Six-wavefront tiles: the tile's 16 x 27 pulls spread over the
+        // Twelve-wavefront tiles: the tile's 16 x 27 pulls spread over the
         // block's threads (each a load or a folded one at the faces of the
         // reduced cube), kept in LDS for the relaxation as well.
-        static_assert(!RATES, "six-wavefront tiles run steps");
+        static_assert(!RATES, "twelve-wavefront tiles run steps");
         float* __restrict__ fl = lds.vals + PSPLIT_VALS;
         for (int e = tid; e < NODES * Q; e += THREADS) {
             const int nd = e % NODES, i = e / NODES, id = blk * NODES + nd;
@@ -975,9 +718,9 @@ __device__ __forceinline__ void nco_mfma_block(const typename Codec<S>::store_t*
         const int lane = tid & 63;
         const float* __restrict__ lt = lane_tab + lane * LANE_WORDS;
         if constexpr (TPW == 0) {
-            static_assert(PREC == MLP_PREC_F32 && NODES == 16, "six-wavefront tiles: the float32 network");
+            static_assert(PREC == MLP_PREC_F32 && NODES == 16, "twelve-wavefront tiles: the float32 network");
             float* sums = SUMS && a.net_sums ? a.net_sums + (size_t)blk * NODES * NET_SUMS_PER_NODE : nullptr;
-            network_f32_psplit<ACT, DEPTH>(sm, sg, sw, lt, tid >> 6, lane >> 4, lane & 15, lds.vals, sums);
+            network_f32_psplit<ACT, DEPTH>(sm, sg, sw, lt, tid, lane >> 4, lane & 15, lds.vals, sums);
         } else if constexpr (PREC == MLP_PREC_BF16) {
             network_bf16<ACT, DEPTH, TPW>(sm, sg, sw, lt, tid >> 6, lane >> 4, lane & 15);
         } else if constexpr (PREC == MLP_PREC_F32S) {
@@ -987,7 +730,7 @@ __device__ __forceinline__ void nco_mfma_block(const typename Codec<S>::store_t*
             // Keeps the network values when a.net_sums is set, else a plain
             // step (a uniform branch after each tile).
             float* sums = a.net_sums ? a.net_sums + (size_t)blk * NODES * NET_SUMS_PER_NODE : nullptr;
-            network_f32<ACT, DEPTH, TPW>(sm, sg, sw, lt, tid >> 6, lane >> 4, lane & 15, nullptr, sums);
+            network_f32<ACT, DEPTH, TPW>(sm, sg, sw, lt, tid >> 6, lane >> 4, lane & 15, sums);
         } else {
             network_f32<ACT, DEPTH, TPW>(sm, sg, sw, lt, tid >> 6, lane >> 4, lane & 15);
         }
@@ -1182,7 +925,7 @@ __global__ __launch_bounds__(256) void k_adjoint_mfma(const typename Codec<S>::s
             for (int n = 0; n < 4; ++n) sw[tid * 4 + n] = live ? src[32 + n] : 0.0f;
         }
     } else {
-        network_f32<ACT, 2, TPW>(sm, sg, sw, lane_tab + lane * LANE_WORDS, wave, q, c, sdm);
+        network_f32<ACT, 2, TPW>(sm, sg, sw, lane_tab + lane * LANE_WORDS, wave, q, c, nullptr, sdm);
     }
     __syncthreads();
 
@@ -1926,7 +1669,7 @@ hipError_t launch_nco_mfma_grouped(int storage, int prec, int act, const LaunchG
 // 32^3 before the one-tile blocks existed, equal from 64^3 up).  Above, the
 // 256-node blocks.
 enum MfmaBlock { MFMA_BLOCK_256 = 0, MFMA_BLOCK_64 = 1, MFMA_BLOCK_64_TILE = 2 };
-// Float32-network steps of lattices up to this many nodes run six-wavefront
+// Float32-network steps of lattices up to this many nodes run twelve-wavefront
 // tiles (network_f32_psplit): 256 blocks, one round over the 256 CUs.  A
 // block holds 111 KB of LDS, one per CU, so beyond that the blocks run in
 // rounds and the one-tile-per-wavefront blocks are faster (16^3: 15 against
@@ -1949,7 +1692,7 @@ hipError_t launch_mfma_kind(int kind, const void* fin, void* fout, const StepArg
         // waves per SIMD, where the instantiation without it takes 230 and 2
         // waves and runs 3 % slower; at depth 3, 177 against 254 (with
         // mfma_min_waves, 3 waves).  Steps of lattices up to
-        // PSPLIT_MAX_NODES run six-wavefront tiles.
+        // PSPLIT_MAX_NODES run twelve-wavefront tiles.
         if (a.n <= PSPLIT_MAX_NODES)
             hipLaunchKernelGGL((k_nco_mfma<S, ACT, RR, PP, 16, DD, 0, true>), dim3((a.n + 15) / 16),
                                dim3(mfma_block_threads(16, 0)), 0, st, static_cast<const T*>(fin),
@@ -1965,18 +1708,19 @@ hipError_t launch_mfma_kind(int kind, const void* fin, void* fout, const StepArg
                                dim3(mfma_block_threads(256, 4)), 0, st, static_cast<const T*>(fin),
                                static_cast<T*>(fout), a, lane_tab, gtab, omega_out);
         return hipGetLastError();
+    } else {
+        if (a.net_sums) return hipErrorInvalidValue;
+        if (kind == MFMA_BLOCK_64_TILE)
+            hipLaunchKernelGGL((k_nco_mfma<S, ACT, RR, PP, 64, DD, 1>), dim3(grid), dim3(mfma_block_threads(64, 1)), 0,
+                               st, static_cast<const T*>(fin), static_cast<T*>(fout), a, lane_tab, gtab, omega_out);
+        else if (kind == MFMA_BLOCK_64)
+            hipLaunchKernelGGL((k_nco_mfma<S, ACT, RR, PP, 64, DD, 4>), dim3(grid), dim3(mfma_block_threads(64, 4)), 0,
+                               st, static_cast<const T*>(fin), static_cast<T*>(fout), a, lane_tab, gtab, omega_out);
+        else
+            hipLaunchKernelGGL((k_nco_mfma<S, ACT, RR, PP, 256, DD, 4>), dim3(grid), dim3(mfma_block_threads(256, 4)),
+                               0, st, static_cast<const T*>(fin), static_cast<T*>(fout), a, lane_tab, gtab, omega_out);
+        return hipGetLastError();
     }
-    if (a.net_sums) return hipErrorInvalidValue;
-    if (kind == MFMA_BLOCK_64_TILE)
-        hipLaunchKernelGGL((k_nco_mfma<S, ACT, RR, PP, 64, DD, 1>), dim3(grid), dim3(mfma_block_threads(64, 1)), 0,
-                           st, static_cast<const T*>(fin), static_cast<T*>(fout), a, lane_tab, gtab, omega_out);
-    else if (kind == MFMA_BLOCK_64)
-        hipLaunchKernelGGL((k_nco_mfma<S, ACT, RR, PP, 64, DD, 4>), dim3(grid), dim3(mfma_block_threads(64, 4)), 0,
-                           st, static_cast<const T*>(fin), static_cast<T*>(fout), a, lane_tab, gtab, omega_out);
-    else
-        hipLaunchKernelGGL((k_nco_mfma<S, ACT, RR, PP, 256, DD, 4>), dim3(grid), dim3(mfma_block_threads(256, 4)),
-                           0, st, static_cast<const T*>(fin), static_cast<T*>(fout), a, lane_tab, gtab, omega_out);
-    return hipGetLastError();
 }
 
 template <int S, int ACT, bool RR>

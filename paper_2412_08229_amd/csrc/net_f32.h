@@ -1,0 +1,196 @@
+// The float32 matrix-core network's device pieces, shared by the forward
+// step (nco_mfma.hip) and the reverse step (nco_adjoint.hip): both run the
+// same products in the same order, so the reverse step's own forward pass
+// gives the values the forward step keeps, bit for bit.
+#pragma once
+
+#include "fold.h"
+#include "kernels.h"
+
+namespace nco {
+
+constexpr int MW = 32;              // network width on the matrix-core paths
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+// Offsets in the per-lane table of the float32 network (4-byte words per
+// lane: LANE_WORDS).
+constexpr int LT_A1 = 0;            // [t 2][st 10]    W1 rows / b1 as A operand
+constexpr int LT_A2 = 20;           // [u 2][t 2][r 4] W2 as A operand
+constexpr int LT_B2 = 36;           // [u 2][r 4]      b2 as accumulator init
+constexpr int LT_W3 = 44;           // [u 2][r 4][n 4] W3 / 48
+constexpr int LT_B3 = 76;           // [n 4]
+constexpr int LT_A2B = 80;          // [v 2][t 2][r 4] W2b as A operand (depth 3)
+constexpr int LT_B2B = 96;          // [v 2][r 4]      b2b as accumulator init (depth 3)
+constexpr int LANE_WORDS = 144;
+
+// Activation as evaluated on the matrix-core paths.  For tanh the
+// pre-activation arrives scaled by kappa = 2 log2(e) and the function returns
+// r = 1 / (1 + 2^(kappa z)), so that tanh(z) = 1 - 2 r; the affine map 1 - 2 r
+// is folded into the next layer's weights and bias on the host (and into W3,
+// b3 for the group sum), which leaves exp2, add and reciprocal per value.  r
+// saturates correctly (2^+inf = inf gives 0).
+template <int ACT>
+__device__ __forceinline__ float act_scaled(float x) {
+    if constexpr (ACT == ACT_RELU) {
+        return fmaxf(x, 0.0f);
+    } else {
+        return __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(x));
+    }
+}
+
+__device__ __forceinline__ f32x4 mfma4(float a, float b, f32x4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+
+// The eight parity-class partial products of layer 1 of one axis permutation
+// over 10 K-steps (A1(t, st): W1's A operand, b(st): the moment operand), and
+// their Walsh-Hadamard transform over the class index, after which Y[s][t] is
+// the pre-activation of reflection pattern s (hidden rows 16 t + 4 q + r).
+template <typename A, typename B>
+__device__ __forceinline__ void layer1_f32(A&& A1, B&& b, f32x4 (&Y)[8][2]) {
+#pragma unroll
+    for (int ci = 0; ci < 8; ++ci) {
+        Y[ci][0] = f32x4{0.f, 0.f, 0.f, 0.f};
+        Y[ci][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+#pragma unroll
+    for (int st = 0; st < KSTEPS; ++st) {
+        const float x = b(st);
+#pragma unroll
+        for (int t = 0; t < 2; ++t) Y[step_class(st)][t] = mfma4(A1(t, st), x, Y[step_class(st)][t]);
+    }
+}
+
+__device__ __forceinline__ void reflections(f32x4 (&Y)[8][2]) {
+#pragma unroll
+    for (int bit = 1; bit < 8; bit <<= 1)
+#pragma unroll
+        for (int ci = 0; ci < 8; ++ci)
+            if (!(ci & bit))
+#pragma unroll
+                for (int t = 0; t < 2; ++t) {
+                    const f32x4 u0 = Y[ci][t], u1 = Y[ci | bit][t];
+                    Y[ci][t] = u0 + u1;
+                    Y[ci | bit][t] = u0 - u1;
+                }
+}
+
+// The reflections 4 half .. 4 half + 3 only (their transform's last level
+// keeps one side), into Y[0 .. 3].
+__device__ __forceinline__ void reflections_half(f32x4 (&Y)[8][2], int half) {
+#pragma unroll
+    for (int bit = 1; bit < 4; bit <<= 1)
+#pragma unroll
+        for (int ci = 0; ci < 8; ++ci)
+            if (!(ci & bit))
+#pragma unroll
+                for (int t = 0; t < 2; ++t) {
+                    const f32x4 u0 = Y[ci][t], u1 = Y[ci | bit][t];
+                    Y[ci][t] = u0 + u1;
+                    Y[ci | bit][t] = u0 - u1;
+                }
+    const float sign = half ? -1.0f : 1.0f;
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) Y[s][t][r] = fmaf(sign, Y[4 + s][t][r], Y[s][t][r]);
+}
+
+// One hidden-to-hidden layer, c[u] += A(u, t, r) h[t][r] over the 8 K-steps.
+template <typename A>
+__device__ __forceinline__ void hidden_f32(A&& A2, const f32x4 (&h)[2], f32x4 (&c)[2]) {
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int u = 0; u < 2; ++u) c[u] = mfma4(A2(u, t, r), h[t][r], c[u]);
+}
+
+template <int ACT>
+__device__ __forceinline__ void act_f32(const f32x4 (&z)[2], f32x4 (&h)[2]) {
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) h[t][r] = act_scaled<ACT>(z[t][r]);
+}
+
+// Reflections 0 .. NS - 1 (pre-activations Y) through the hidden layers; the
+// last layer's pre-activations of reflection s go to sink(s, z), in order.
+//
+// Depth 2 is software-pipelined over the reflections: while the 16 products
+// of reflection s run on the matrix cores, the vector units activate layer 1
+// of reflection s + 1 and layer 2 of reflection s - 1 (independent of them).
+template <int ACT, int DEPTH, int NS, typename A, typename AB, typename Sink>
+__device__ __forceinline__ void hidden_reflections(A&& A2, const f32x4 (&B2)[2], AB&& A2b, const f32x4 (&B2b)[2],
+                                                   const f32x4 (&Y)[8][2], Sink&& sink) {
+    if constexpr (DEPTH == 3) {
+        // Unrolled: Y[s] must stay in registers.
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            f32x4 h[2], c[2] = {B2[0], B2[1]}, c3[2] = {B2b[0], B2b[1]};
+            act_f32<ACT>(Y[s], h);
+            hidden_f32(A2, h, c);
+            act_f32<ACT>(c, h);
+            hidden_f32(A2b, h, c3);
+            sink(s, c3);
+        }
+        return;
+    }
+    f32x4 h[2], prev[2];
+    act_f32<ACT>(Y[0], h);
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+        f32x4 c[2] = {B2[0], B2[1]};
+        hidden_f32(A2, h, c);
+        if (s > 0) sink(s - 1, prev);
+        if (s < NS - 1) act_f32<ACT>(Y[s + 1], h);
+        prev[0] = c[0];
+        prev[1] = c[1];
+    }
+    sink(NS - 1, prev);
+}
+
+// The group sum adds the last layer's activations element by element, in the
+// order (permutation, reflection), in every block shape.
+template <int ACT>
+__device__ __forceinline__ void add_act(const f32x4 (&z)[2], f32x4 (&acc)[2]) {
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc[u][r] += act_scaled<ACT>(z[u][r]);
+}
+
+// Output layer on the group sum of one node tile and the rate squashing;
+// lanes of group q = 0 write the four rates of node (tile, c) to LDS, or with
+// RAW the pre-squash outputs tilde tau_n (for the adjoint).
+template <bool RAW = false>
+__device__ __forceinline__ void output_layer(const f32x4 (&acc)[2], const float* __restrict__ w3,
+                                             const float* __restrict__ b3, int q, float* __restrict__ sw_node,
+                                             float* __restrict__ tt_node = nullptr) {
+    float pn[4];
+#pragma unroll
+    for (int n = 0; n < 4; ++n) {
+        float v = 0.0f;
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) v = fmaf(w3[(u * 4 + r) * 4 + n], acc[u][r], v);
+        v += __shfl_xor(v, 16, 64);
+        v += __shfl_xor(v, 32, 64);
+        pn[n] = v;
+    }
+    if (q == 0) {
+#pragma unroll
+        for (int n = 0; n < 4; ++n) {
+            const float t = pn[n] + b3[n];
+            sw_node[n] = RAW ? t : 1.0f / (0.5f + 0.5f / (1.0f + expf(t)));
+            if (tt_node) tt_node[n] = t;
+        }
+    }
+}
+
+}  // namespace nco
