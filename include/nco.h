@@ -142,12 +142,12 @@ int nco_set_domain(nco_lattice* lat, int domain);
 int nco_set_stochastic_rounding(nco_lattice* lat, int enable, unsigned seed);
 
 /* Memory the reverse mode may use to keep network values between a forward
- * step and the adjoint of its state (float32 matrix-core networks of depth
- * 2, Sec. "Learning Task"): 144 bytes per node for each of the K - 1
+ * step and the adjoint of its state (float32 matrix-core networks,
+ * Sec. "Learning Task"): 144 bytes per node for each of the K - 1
  * recomputed states of a segment (K = ckpt_every), and as many for the last
  * state of each of the ceil(T / K) segments, which nco_forward_record keeps
  * when both fit.  Where they are kept (default budget 4 GiB), the adjoint
- * reads the group sums of the second layer and the pre-squash outputs
+ * reads the group sums of the last hidden layer and the pre-squash outputs
  * instead of running the network forward again; the gradient is the same
  * bit for bit.  With K = 1 every state is a checkpoint, nothing is
  * recomputed, and every adjoint reads kept values (T x 144 bytes per node
@@ -192,8 +192,8 @@ int nco_set_net_weights(nco_lattice* lat, int width, int act, int mlp_prec,
  * b1, W2[width][width], b2, W2b[width][width], b2b, W3[width][4], b3
  * (n_params = width*(27 + 2 width + 4) + 3 width + 4).  Depth 3 runs in
  * every network arithmetic (the matrix-core ones with narrower networks
- * zero-padded to width 32) and has the reverse mode (vector-unit adjoint): nco_backward
- * returns the gradient in this parameter order.  nco_batch_step refuses
+ * zero-padded to width 32) and has the reverse mode: nco_backward returns
+ * the gradient in this parameter order.  nco_batch_step refuses
  * depth-3 lattices.  Setting the weights drops a recorded run. */
 int nco_set_net_weights_depth(nco_lattice* lat, int depth, int width, int act, int mlp_prec,
                               const float* params, size_t n_params);
@@ -362,7 +362,7 @@ int nco_set_forcing_power(nco_lattice* lat, int n_modes, const int* k, const dou
 /* Run nsteps steps (NCO operator, width 32, float storage) keeping a
  * checkpoint of the state every ckpt_every steps in device memory, for a
  * following nco_backward (the gradient of Adam in Sec. "Learning Task").
- * With a float32 matrix-core network of depth 2 it also keeps the network
+ * With a float32 matrix-core network it also keeps the network
  * values of the last step of each checkpoint segment when the reverse-mode
  * budget allows (nco_set_reverse_cache); ckpt_every = 1 keeps every state
  * and nco_backward then recomputes nothing. */
@@ -384,9 +384,9 @@ int nco_forward_record_energy(nco_lattice* lat, int nsteps, int ckpt_every, int 
  * the result is deterministic (fixed-order reductions).  The recorded and
  * recomputed steps run the lattice's own network arithmetic; the adjoint
  * differentiates the network in float32: on the matrix cores for the
- * depth-2 matrix-core networks (NCO_MLP_F32_MFMA, and NCO_MLP_F32_SPLIT and
+ * matrix-core networks (NCO_MLP_F32_MFMA, and NCO_MLP_F32_SPLIT and
  * NCO_MLP_BF16, whose product rounding it does not differentiate), on the
- * vector units for NCO_MLP_F32 and depth 3. */
+ * vector units for NCO_MLP_F32. */
 int nco_backward(nco_lattice* lat, const double* dL_dE, int nbins, const double* dL_df, double* grad,
                  size_t n_params, double* dL_df0);
 

@@ -522,22 +522,22 @@ __global__ __launch_bounds__(256) void k_grad_reduce(const float* __restrict__ p
 }
 
 // stage[g][p] = sum of partial[64 g .. 64 g + 63][p] in row order.
-__global__ __launch_bounds__(256) void k_grad_stage(const double* __restrict__ partial, int nblocks,
+__global__ __launch_bounds__(256) void k_grad_stage(const double* __restrict__ partial, int nblocks, int npar,
                                                     double* __restrict__ stage) {
     const int pidx = blockIdx.x * blockDim.x + threadIdx.x;
-    if (pidx >= NPAR) return;
+    if (pidx >= npar) return;
     const int g = blockIdx.y, b0 = 64 * g, b1 = min(nblocks, b0 + 64);
     double s = 0.0;
-    for (int b = b0; b < b1; ++b) s += partial[(size_t)b * NPAR + pidx];
-    stage[(size_t)g * NPAR + pidx] = s;
+    for (int b = b0; b < b1; ++b) s += partial[(size_t)b * npar + pidx];
+    stage[(size_t)g * npar + pidx] = s;
 }
 
-__global__ __launch_bounds__(256) void k_grad_final(const double* __restrict__ stage, int ngroups,
+__global__ __launch_bounds__(256) void k_grad_final(const double* __restrict__ stage, int ngroups, int npar,
                                                     double* __restrict__ grad) {
     const int pidx = blockIdx.x * blockDim.x + threadIdx.x;
-    if (pidx >= NPAR) return;
+    if (pidx >= npar) return;
     double s = 0.0;
-    for (int g = 0; g < ngroups; ++g) s += stage[(size_t)g * NPAR + pidx];
+    for (int g = 0; g < ngroups; ++g) s += stage[(size_t)g * npar + pidx];
     grad[pidx] = s;
 }
 
@@ -844,11 +844,12 @@ hipError_t launch_grad_reduce(const float* partial, int nblocks, int npar, doubl
     return hipGetLastError();
 }
 
-hipError_t launch_grad_reduce_f64(const double* partial, int nblocks, double* stage, double* grad, hipStream_t st) {
+hipError_t launch_grad_reduce_f64(const double* partial, int nblocks, int npar, double* stage, double* grad,
+                                  hipStream_t st) {
     const int groups = (nblocks + 63) / 64;
-    hipLaunchKernelGGL(k_grad_stage, dim3((NPAR + 255) / 256, groups), dim3(256), 0, st, partial, nblocks, stage);
+    hipLaunchKernelGGL(k_grad_stage, dim3((npar + 255) / 256, groups), dim3(256), 0, st, partial, nblocks, npar, stage);
     if (hipError_t e = hipGetLastError()) return e;
-    hipLaunchKernelGGL(k_grad_final, dim3((NPAR + 255) / 256), dim3(256), 0, st, stage, groups, grad);
+    hipLaunchKernelGGL(k_grad_final, dim3((npar + 255) / 256), dim3(256), 0, st, stage, groups, npar, grad);
     return hipGetLastError();
 }
 

@@ -223,10 +223,11 @@ struct nco_lattice {
     double* d_grad = nullptr;
     double* d_dE = nullptr;
     int* d_gsrc = nullptr;        // [48][27] group source row | sign bit
-    // Matrix-core adjoint: float32 forward tables and the adjoint table
-    // (width-32 networks on matrix cores), float64 per-block gradient rows.
+    // Matrix-core adjoint: its table (width-32 networks on matrix cores),
+    // float64 per-block gradient rows.
     void* adj_tab = nullptr;
     double* adj_partial64 = nullptr;
+    size_t adj_partial64_doubles = 0;
     // Stability check: every check_every steps, the global sums are checked
     // on the device against the mass at the last initialisation; a failure
     // sets *flag, which nco_sync reports.
@@ -425,10 +426,8 @@ bool inplace_pair_ok(const nco_lattice* lat) {
 size_t net_values_stride(const nco_lattice* lat) { return (size_t)((lat->n + 255) / 256) * 256 * NET_SUMS_PER_NODE; }
 
 // The reverse mode runs on the matrix cores and can read kept network values
-// (float32 matrix-core network of depth 2).
-bool net_values_apply(const nco_lattice* lat) {
-    return lat->mlp_prec == NCO_MLP_F32_MFMA && lat->adj_tab && lat->depth == 2;
-}
+// (float32 matrix-core network).
+bool net_values_apply(const nco_lattice* lat) { return lat->mlp_prec == NCO_MLP_F32_MFMA && lat->adj_tab; }
 
 int launch_one(nco_lattice* lat, const void* fin, void* fout, long t, int slot = -1, bool replay = false,
                float* net_sums = nullptr) {
@@ -718,17 +717,12 @@ int nco_set_net_weights_depth(nco_lattice* lat, int depth, int width, int act, i
         if (!lat->mfma_tab) HIP_TRY(hipMalloc(&lat->mfma_tab, tab.size()));
         HIP_TRY(hipMemcpyAsync(lat->mfma_tab, tab.data(), tab.size(), hipMemcpyHostToDevice, lat->stream));
         HIP_TRY(hipStreamSynchronize(lat->stream));
-        if (W == 32 && depth == 2) {
-            // Reverse mode on the matrix cores: the float32 forward tables
-            // (also for a bf16 network) and the adjoint's own table.
-            const size_t na = mfma_adjoint_table_floats();
-            std::vector<char> at(sizeof(float) * (nf + na) + sizeof(int) * ni);
-            float* lt32 = reinterpret_cast<float*>(at.data());
-            int* gt32 = reinterpret_cast<int*>(at.data() + sizeof(float) * nf);
-            float* adj = reinterpret_cast<float*>(at.data() + sizeof(float) * nf + sizeof(int) * ni);
-            mfma_prepare_tables(params, act, NCO_MLP_F32_MFMA, G.src, lt32, gt32);
-            mfma_prepare_adjoint_table(params, adj);
-            if (!lat->adj_tab) HIP_TRY(hipMalloc(&lat->adj_tab, at.size()));
+        if (W == 32) {
+            // Reverse mode on the matrix cores, float32 (also for a bf16 or
+            // split network), whose table holds the float32 forward weights.
+            std::vector<char> at(mfma_adjoint_table_bytes(depth));
+            mfma_prepare_adjoint_table(params, act, depth, G.src, at.data());
+            if (!lat->adj_tab) HIP_TRY(hipMalloc(&lat->adj_tab, mfma_adjoint_table_bytes(3)));
             HIP_TRY(hipMemcpyAsync(lat->adj_tab, at.data(), at.size(), hipMemcpyHostToDevice, lat->stream));
             HIP_TRY(hipStreamSynchronize(lat->stream));
         }
@@ -1217,14 +1211,20 @@ int backward(nco_lattice* lat, const double* dL_dk, int every, const double* dL_
         if (!lat->lam[b]) HIP_TRY(hipMalloc(&lat->lam[b], sizeof(float) * nf));
     // Matrix-core adjoint for matrix-core networks, vector-unit adjoint for
     // the vector-unit network.
-    // (a depth-3 network takes the vector-unit adjoint)
-    const bool mfma = lat->mlp_prec != NCO_MLP_F32 && lat->adj_tab && lat->depth == 2;
-    const int npar = mfma ? adjoint_param_count() : adjoint_param_count_depth(lat->depth);
+    const bool mfma = lat->mlp_prec != NCO_MLP_F32 && lat->adj_tab;
+    const int npar = adjoint_param_count_depth(lat->depth);
     const int nblk = mfma ? adjoint_mfma_blocks(lat->n) : adjoint_blocks(lat->n, lat->depth);
     const int ngrp = (nblk + 63) / 64;
     if (mfma) {
-        if (!lat->adj_partial64)
-            HIP_TRY(hipMalloc(&lat->adj_partial64, sizeof(double) * (size_t)(nblk + ngrp) * npar));
+        const size_t rows = (size_t)(nblk + ngrp) * npar;
+        if (lat->adj_partial64_doubles < rows) {
+            HIP_TRY(hipStreamSynchronize(lat->stream));
+            if (lat->adj_partial64) HIP_TRY(hipFree(lat->adj_partial64));
+            lat->adj_partial64 = nullptr;
+            lat->adj_partial64_doubles = 0;
+            HIP_TRY(hipMalloc(&lat->adj_partial64, sizeof(double) * rows));
+            lat->adj_partial64_doubles = rows;
+        }
         HIP_TRY(launch_fill_f64(lat->adj_partial64, (size_t)nblk * npar, 0.0, lat->stream));
     } else if (lat->adj_partial_floats < (size_t)nblk * npar) {
         HIP_TRY(hipStreamSynchronize(lat->stream));
@@ -1308,13 +1308,8 @@ int backward(nco_lattice* lat, const double* dL_dk, int every, const double* dL_
             if (int rc = force_field(lat, a, lat->stream)) return rc;
             if (mfma) {
                 a.net_sums = t - t0 < len - 1 ? sums_of(t - t0) : end_of(sgi);
-                const char* tab = static_cast<const char*>(lat->adj_tab);
-                const float* lt32 = reinterpret_cast<const float*>(tab);
-                const int* gt32 = reinterpret_cast<const int*>(tab + sizeof(float) * mfma_lane_table_floats());
-                const float* adj = reinterpret_cast<const float*>(tab + sizeof(float) * mfma_lane_table_floats() +
-                                                                  sizeof(int) * mfma_group_table_ints());
-                HIP_TRY(launch_adjoint_mfma(lat->storage, lat->act, state(t - t0), lin, lout, a, lt32, gt32, adj,
-                                            lat->d_gsrc, lat->adj_partial64, lat->stream));
+                HIP_TRY(launch_adjoint_mfma(lat->storage, lat->act, state(t - t0), lin, lout, a, lat->adj_tab,
+                                            lat->adj_partial64, lat->stream));
             } else {
                 HIP_TRY(launch_adjoint(lat->storage, state(t - t0), lin, lout, a, lat->d_gsrc, lat->adj_partial,
                                        lat->adj_xwork, lat->stream));
@@ -1333,7 +1328,7 @@ int backward(nco_lattice* lat, const double* dL_dk, int every, const double* dL_
         }
     }
     if (mfma)
-        HIP_TRY(launch_grad_reduce_f64(lat->adj_partial64, nblk, lat->adj_partial64 + (size_t)nblk * npar,
+        HIP_TRY(launch_grad_reduce_f64(lat->adj_partial64, nblk, npar, lat->adj_partial64 + (size_t)nblk * npar,
                                        lat->d_grad, lat->stream));
     if (dL_df0) {
         if (int rc = ensure_staging(lat, 27)) return rc;

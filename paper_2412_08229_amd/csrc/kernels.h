@@ -182,9 +182,10 @@ hipError_t launch_grad_reduce(const float* partial, int nblocks, int npar, doubl
 int adjoint_param_count_depth(int depth);
 // lam += coef d(sum over nodes of |u|^2 / 2) / df for the state f (float64 arithmetic).
 hipError_t launch_add_energy_grad(int storage, const void* f, float* lam, double coef, int n, hipStream_t st);
-// grad = sum over rows of partial[nblocks][NPAR] (float64) in row order, in
+// grad = sum over rows of partial[nblocks][npar] (float64) in row order, in
 // two passes over groups of 64 rows; stage holds ceil(nblocks / 64) rows.
-hipError_t launch_grad_reduce_f64(const double* partial, int nblocks, double* stage, double* grad, hipStream_t st);
+hipError_t launch_grad_reduce_f64(const double* partial, int nblocks, int npar, double* stage, double* grad,
+                                  hipStream_t st);
 // Reverse mode of the velocity-dependent forcing phase of one step: x the
 // state the step started from, lam_next = dL/d(state after it), a.fhat the
 // step's coefficients, uhat its u_hat, draw its (phi, psi) per mode;
@@ -197,16 +198,16 @@ hipError_t launch_force_phase_adjoint(int storage, const void* x, const float* l
                                       const double* basis, const double* draw, const double* uhat, double* duhat,
                                       hipStream_t st);
 
-// The same adjoint on the matrix cores (nco_mfma.hip): 256 nodes per block;
-// lane_tab and gtab are the float32 forward tables of mfma_prepare_tables,
-// adj_tab the table of mfma_prepare_adjoint_table; the step's parameter
-// gradient is added to partial[block][NPAR].
-size_t mfma_adjoint_table_floats();
-void mfma_prepare_adjoint_table(const float* params, float* tab);
+// The same adjoint on the matrix cores (nco_adjoint.hip), depth 2 or 3:
+// table as mfma_prepare_adjoint_table leaves it (params: a width-32 network);
+// the step's parameter gradient is added to partial[block][row], rows of
+// adjoint_param_count_depth(depth).  With a.net_sums the network values the
+// forward step kept are read instead of computed again.
+size_t mfma_adjoint_table_bytes(int depth);
+void mfma_prepare_adjoint_table(const float* params, int act, int depth, const int (*gsrc)[27], void* table);
 int adjoint_mfma_blocks(int n);
 hipError_t launch_adjoint_mfma(int storage, int act, const void* xin, const float* lam_in, float* lam_out,
-                               const StepArgs& a, const float* lane_tab, const int* gtab, const float* adj_tab,
-                               const int* gsrc, double* partial, hipStream_t st);
+                               const StepArgs& a, const void* table, double* partial, hipStream_t st);
 hipError_t launch_fill_f32(float* p, size_t count, float v, hipStream_t st);
 hipError_t launch_fill_f64(double* p, size_t count, double v, hipStream_t st);
 hipError_t launch_add_f64_to_f32(float* dst, const double* src, size_t count, hipStream_t st);

@@ -43,7 +43,6 @@
 #include <cmath>
 #include <cstring>
 
-#include "adjoint.h"
 #include "kernels.h"
 #include "net_f32.h"
 #include "stream.h"
@@ -149,8 +148,8 @@ __device__ __forceinline__ float act_split(float x) {
 struct NetF32Regs {
     float A1[2][KSTEPS], A2[2][2][4];
     f32x4 B2[2];
-    const float* __restrict__ lt;
-    __device__ __forceinline__ explicit NetF32Regs(const float* __restrict__ table) : lt(table) {
+    LaneTab lt;
+    __device__ __forceinline__ explicit NetF32Regs(LaneTab table) : lt(table) {
 #pragma unroll
         for (int t = 0; t < 2; ++t)
 #pragma unroll
@@ -182,7 +181,7 @@ struct NetF32Regs {
                 for (int r = 0; r < 4; ++r) B2b[v][r] = lt[LT_B2B + v * 4 + r];
         hidden_reflections<ACT, DEPTH, NS>([&](int u, int t, int r) { return A2[u][t][r]; }, B2,
                                            [&](int v, int t, int r) { return lt[LT_A2B + v * 8 + t * 4 + r]; }, B2b, Y,
-                                           sink);
+                                           []() {}, sink);
     }
 };
 
@@ -190,7 +189,7 @@ struct NetF32Regs {
 // whose adjoint follows) the sum and tilde tau into sums[node]
 // [NET_SUMS_PER_NODE] (row 16 u + 4 q + r in lane (q, c)) and the rates into
 // sw, else the rates into sw.
-__device__ __forceinline__ void finish_tile(const f32x4 (&acc)[2], const float* __restrict__ lt, int q, int node,
+__device__ __forceinline__ void finish_tile(const f32x4 (&acc)[2], LaneTab lt, int q, int node,
                                             float* __restrict__ sw, float* __restrict__ sums) {
     if (sums) {
         float* __restrict__ row = sums + (size_t)node * NET_SUMS_PER_NODE;
@@ -198,15 +197,14 @@ __device__ __forceinline__ void finish_tile(const f32x4 (&acc)[2], const float* 
         for (int u = 0; u < 2; ++u)
 #pragma unroll
             for (int r = 0; r < 4; ++r) row[16 * u + 4 * q + r] = acc[u][r];
-        output_layer(acc, lt + LT_W3, lt + LT_B3, q, sw + node * 4, row + 32);
+        output_layer(acc, lt, LT_W3, LT_B3, q, sw + node * 4, row + 32);
     } else {
-        output_layer(acc, lt + LT_W3, lt + LT_B3, q, sw + node * 4);
+        output_layer(acc, lt, LT_W3, LT_B3, q, sw + node * 4);
     }
 }
 
 // sums != nullptr (a step whose adjoint follows): the network values of the
-// block's nodes are kept (finish_tile).  s2 != nullptr (adjoint): sw receives
-// tilde tau instead of the rates and s2[node][32] the group sum.
+// block's nodes are kept (finish_tile).
 //
 // DEPTH = 3: a third hidden layer (W2b, b2b) between the second layer and
 // the group sum, one more product per group element whose B operand is the
@@ -215,9 +213,8 @@ __device__ __forceinline__ void finish_tile(const f32x4 (&acc)[2], const float* 
 // [16 TPW w, 16 TPW (w + 1)) of the block.
 template <int ACT, int DEPTH = 2, int TPW = 4>
 __device__ __forceinline__ void network_f32(const float* __restrict__ sm, const int* __restrict__ sg,
-                                            float* __restrict__ sw, const float* __restrict__ lt, int wave,
-                                            int q, int c, float* __restrict__ sums = nullptr,
-                                            float* __restrict__ s2 = nullptr) {
+                                            float* __restrict__ sw, LaneTab lt, int wave,
+                                            int q, int c, float* __restrict__ sums = nullptr) {
     const NetF32Regs w(lt);
 #pragma unroll 1
     for (int j = 0; j < TPW; ++j) {
@@ -231,15 +228,7 @@ __device__ __forceinline__ void network_f32(const float* __restrict__ sm, const 
             reflections(Y);
             w.template hidden<ACT, DEPTH, 8>(Y, [&](int, const f32x4(&z)[2]) { add_act<ACT>(z, acc); });
         }
-        if (s2) {
-#pragma unroll
-            for (int u = 0; u < 2; ++u)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) s2[node * 32 + 16 * u + 4 * q + r] = acc[u][r];
-            output_layer<true>(acc, lt + LT_W3, lt + LT_B3, q, sw + node * 4);
-        } else {
-            finish_tile(acc, lt, q, node, sw, sums);
-        }
+        finish_tile(acc, lt, q, node, sw, sums);
     }
 }
 
@@ -259,7 +248,7 @@ constexpr int PSPLIT_LDS = PSPLIT_VALS + 16 * PSPLIT_FROW;
 
 template <int ACT, int DEPTH>
 __device__ __forceinline__ void network_f32_psplit(const float* __restrict__ sm, const int* __restrict__ sg,
-                                                   float* __restrict__ sw, const float* __restrict__ lt, int tid,
+                                                   float* __restrict__ sw, LaneTab lt, int tid,
                                                    int q, int c, float* __restrict__ vals,
                                                    float* __restrict__ sums) {
     const int wave = tid >> 6;
@@ -385,9 +374,10 @@ __device__ __forceinline__ void split_layer(const u32x4 (&A)[2][3], const float 
 // split bf16 products each.
 template <int ACT, int DEPTH = 2, int TPW = 4>
 __device__ __forceinline__ void network_split(const float* __restrict__ sm, const int* __restrict__ sg,
-                                              float* __restrict__ sw, const float* __restrict__ lt, int wave, int q,
+                                              float* __restrict__ sw, LaneTab lt, int wave, int q,
                                               int c) {
-    const unsigned* __restrict__ lw = reinterpret_cast<const unsigned*>(lt);
+    auto lw = [&](int w) { return __float_as_uint(lt[w]); };
+    auto lw4 = [&](int w) { return u32x4{lw(w), lw(w + 1), lw(w + 2), lw(w + 3)}; };
     constexpr int NP = ACT == ACT_TANH ? 2 : 3;
     float B2[2][4], B3[2][4], A1[2][KSTEPS];
     u32x4 AS1[2][3], AS2[2][3], AS3[2][3], SM[3];
@@ -395,20 +385,17 @@ __device__ __forceinline__ void network_split(const float* __restrict__ sm, cons
     for (int u = 0; u < 2; ++u)
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
-            const unsigned* w1 = lw + LS_A1 + 12 * u + 4 * k;
-            const unsigned* w2 = lw + LS_A2 + 12 * u + 4 * k;
             if constexpr (ACT == ACT_TANH)
-                AS1[u][k] = k < NP ? u32x4{w1[0], w1[1], w1[2], w1[3]} : u32x4{0u, 0u, 0u, 0u};
-            AS2[u][k] = k < NP ? u32x4{w2[0], w2[1], w2[2], w2[3]} : u32x4{0u, 0u, 0u, 0u};
+                AS1[u][k] = k < NP ? lw4(LS_A1 + 12 * u + 4 * k) : u32x4{0u, 0u, 0u, 0u};
+            AS2[u][k] = k < NP ? lw4(LS_A2 + 12 * u + 4 * k) : u32x4{0u, 0u, 0u, 0u};
             if constexpr (DEPTH == 3) {
-                const unsigned* w3 = lw + LS_A3 + 12 * u + 4 * k;
-                AS3[u][k] = k < NP ? u32x4{w3[0], w3[1], w3[2], w3[3]} : u32x4{0u, 0u, 0u, 0u};
+                AS3[u][k] = k < NP ? lw4(LS_A3 + 12 * u + 4 * k) : u32x4{0u, 0u, 0u, 0u};
             }
         }
     if constexpr (ACT == ACT_TANH) {
 #pragma unroll
         for (int b = 0; b < 3; ++b)
-            SM[b] = u32x4{lw[LS_SM + 4 * b], lw[LS_SM + 4 * b + 1], lw[LS_SM + 4 * b + 2], lw[LS_SM + 4 * b + 3]};
+            SM[b] = lw4(LS_SM + 4 * b);
     } else {
 #pragma unroll
         for (int t = 0; t < 2; ++t)
@@ -480,7 +467,7 @@ __device__ __forceinline__ void network_split(const float* __restrict__ sm, cons
                     for (int r = 0; r < 4; ++r) acc[u][r] += act_scaled<ACT>(cz[u][r]);
             }
         }
-        output_layer(acc, lt + LS_W3, lt + LS_B3O, q, sw + node * 4);
+        output_layer(acc, lt, LS_W3, LS_B3O, q, sw + node * 4);
     }
 }
 
@@ -488,20 +475,21 @@ __device__ __forceinline__ void network_split(const float* __restrict__ sm, cons
 // element, fed by the second layer's activations packed like the first's.
 template <int ACT, int DEPTH = 2, int TPW = 4>
 __device__ __forceinline__ void network_bf16(const float* __restrict__ sm, const int* __restrict__ sg,
-                                             float* __restrict__ sw, const float* __restrict__ lt, int wave,
+                                             float* __restrict__ sw, LaneTab lt, int wave,
                                              int q, int c) {
-    const unsigned* __restrict__ lw = reinterpret_cast<const unsigned*>(lt);
+    auto lw = [&](int w) { return __float_as_uint(lt[w]); };
+    auto lw4 = [&](int w) { return u32x4{lw(w), lw(w + 1), lw(w + 2), lw(w + 3)}; };
     u32x4 A1[2], A2[2], SM[3], A3[2];
     float B2[2][4], B3[2][4];
 #pragma unroll
     for (int t = 0; t < 2; ++t)
-        A1[t] = u32x4{lw[LB_A1 + 4 * t], lw[LB_A1 + 4 * t + 1], lw[LB_A1 + 4 * t + 2], lw[LB_A1 + 4 * t + 3]};
+        A1[t] = lw4(LB_A1 + 4 * t);
 #pragma unroll
     for (int u = 0; u < 2; ++u)
-        A2[u] = u32x4{lw[LB_A2 + 4 * u], lw[LB_A2 + 4 * u + 1], lw[LB_A2 + 4 * u + 2], lw[LB_A2 + 4 * u + 3]};
+        A2[u] = lw4(LB_A2 + 4 * u);
 #pragma unroll
     for (int b = 0; b < 3; ++b)
-        SM[b] = u32x4{lw[LB_SM + 4 * b], lw[LB_SM + 4 * b + 1], lw[LB_SM + 4 * b + 2], lw[LB_SM + 4 * b + 3]};
+        SM[b] = lw4(LB_SM + 4 * b);
 #pragma unroll
     for (int u = 0; u < 2; ++u)
 #pragma unroll
@@ -509,7 +497,7 @@ __device__ __forceinline__ void network_bf16(const float* __restrict__ sm, const
     if constexpr (DEPTH == 3) {
 #pragma unroll
         for (int v = 0; v < 2; ++v) {
-            A3[v] = u32x4{lw[LB_A2B + 4 * v], lw[LB_A2B + 4 * v + 1], lw[LB_A2B + 4 * v + 2], lw[LB_A2B + 4 * v + 3]};
+            A3[v] = lw4(LB_A2B + 4 * v);
 #pragma unroll
             for (int r = 0; r < 4; ++r) B3[v][r] = lt[LB_B2B + v * 4 + r];
         }
@@ -565,7 +553,7 @@ __device__ __forceinline__ void network_bf16(const float* __restrict__ sm, const
                     for (int r = 0; r < 4; ++r) acc[u][r] += act_scaled<ACT>(c2[u][r]);
             }
         }
-        output_layer(acc, lt + LB_W3, lt + LB_B3, q, sw + node * 4);
+        output_layer(acc, lt, LB_W3, LB_B3, q, sw + node * 4);
     }
 }
 
@@ -604,20 +592,22 @@ constexpr int mfma_block_threads(int nodes, int tpw) { return tpw == 0 ? PSPLIT_
 // split networks (156 VGPRs for tanh at depth 2; the others spill 12-57
 // registers into scratch and still run 1-7 % faster than at 2 waves, the
 // third wave keeping their vector instructions issuing) and for the float32
-// depth-3 steps (the instantiation with the network-value branch, 177
-// VGPRs unconstrained; at 168, 0-17 spilled, 4 % faster at 128^3 and 8 % on
-// a 16^3 lattice), 4 for the bf16 depth-3 steps (ReLU 132 VGPRs
+// steps (151-169 VGPRs unconstrained at depth 2, 177 at depth 3; at 168, 0-17
+// spilled, depth 3 4 % faster at 128^3 and 8 % on a 16^3 lattice) - but for
+// depth 2 with one tile per wavefront, where the lattice has no third wave to
+// offer a SIMD and the constraint only costs (24^3 30.2 against 32.7 us, 32^3
+// 53.5 against 57.8) -, 4 for the bf16 depth-3 steps (ReLU 132 VGPRs
 // unconstrained, 128 without spills at 4 waves, 2 % faster), no constraint
 // otherwise.
-constexpr int mfma_min_waves(int prec, int depth, bool sums) {
+constexpr int mfma_min_waves(int prec, int depth, int tpw, bool sums) {
     return prec == MLP_PREC_BF16 && depth == 3 ? 4
-           : prec == MLP_PREC_F32S || (prec == MLP_PREC_F32 && depth == 3 && sums) ? 3
-                                                                                     : 1;
+           : prec == MLP_PREC_F32S || (prec == MLP_PREC_F32 && sums && (depth == 3 || tpw != 1)) ? 3
+                                                                                                   : 1;
 }
 
 template <int S, int ACT, bool RATES, int PREC, int NODES, int DEPTH, int TPW, bool SUMS = false>
 __global__ __launch_bounds__(mfma_block_threads(NODES, TPW))
-__attribute__((amdgpu_waves_per_eu(mfma_min_waves(PREC, DEPTH, SUMS)))) void k_nco_mfma(
+__attribute__((amdgpu_waves_per_eu(mfma_min_waves(PREC, DEPTH, TPW, SUMS)))) void k_nco_mfma(
     const typename Codec<S>::store_t* __restrict__ fin, typename Codec<S>::store_t* __restrict__ fout,
     StepArgs a, const float* __restrict__ lane_tab, const int* __restrict__ gtab, double* __restrict__ omega_out) {
     NCO_BLOCK_LDS(NODES)
@@ -646,7 +636,8 @@ __device__ __forceinline__ void grouped_block(const GroupDesc& d, int blk, Block
 // One step of several lattices with the same storage, activation and
 // network arithmetic.
 template <int S, int ACT, int PREC>
-__global__ __launch_bounds__(256) void k_nco_mfma_grouped(LaunchGroup g) {
+__global__ __launch_bounds__(256)
+__attribute__((amdgpu_waves_per_eu(PREC == MLP_PREC_F32 ? 3 : 1))) void k_nco_mfma_grouped(LaunchGroup g) {
     NCO_BLOCK_LDS(256)
     const int i = group_member(g, blockIdx.x);
     grouped_block<S, ACT, PREC>(g.d[i], blockIdx.x - g.prefix[i], lds);
@@ -716,7 +707,7 @@ __device__ __forceinline__ void nco_mfma_block(const typename Codec<S>::store_t*
     // Phase B: the network, one wavefront per 64 nodes.
     {
         const int lane = tid & 63;
-        const float* __restrict__ lt = lane_tab + lane * LANE_WORDS;
+        const LaneTab lt(lane_tab, lane);
         if constexpr (TPW == 0) {
             static_assert(PREC == MLP_PREC_F32 && NODES == 16, "twelve-wavefront tiles: the float32 network");
             float* sums = SUMS && a.net_sums ? a.net_sums + (size_t)blk * NODES * NET_SUMS_PER_NODE : nullptr;
@@ -771,543 +762,6 @@ __device__ __forceinline__ void nco_mfma_block(const typename Codec<S>::store_t*
 #pragma unroll
         for (int i = 0; i < Q; ++i) f[i] -= df[i];
         store_local<S>(fout, a.n, idx, f, a.sr_key);
-    }
-}
-
-// ---------------------------------------------------------------- adjoint --
-//
-// Reverse mode of one step on the matrix cores (float32), the same
-// computation as the vector-unit adjoint (adjoint.hip): given lambda =
-// dL/dx_t+1, the pre-collision adjoint M^T g_m + lambda is scattered back
-// along the streaming, and the parameter gradient of this step is added to
-// the block's row of `partial` (float64, one row per block, each row touched
-// by its block only, so the sum over steps is in a fixed order).
-//
-// Per node tile of 16 and group element g = (pi, s), in the layout of the
-// forward network (hidden x nodes, lane (q, c) holding rows 4q..4q+3 of
-// node c):
-//   forward recompute   r1 = act(Z1), r2 = act(Z2)          (forward tables)
-//   dz2 = dh2 (.) act'(z2),   dh2 = W3 dtt / 48 (the same for every g)
-//   dh1 = W2 dz2,   dz1 = dh1 (.) act'(z1)                 (products whose
-//         B operands are the previous accumulators, as in the forward)
-//   Z_cl = sum_s chi_s(cl) dz1_s over the 8 reflections s of the
-//         permutation (Walsh-Hadamard transform), for the 8 parity classes
-//   dL/dm[src_pi(k)] += (W1 Z_class(k))[k]                   (through LDS)
-//   dW2 += h1 dz2^T per element, dW1 += x_pi Z_class^T per class (the bias
-//   row of x_pi gives db1), db2 += dz2                       (products over
-//         the 16 nodes of the tile: h1, dz2 and Z are transposed through
-//         a per-wave LDS buffer so that the node index becomes K)
-// For tanh, with r = 1 / (1 + 2^(kappa z)): h = 1 - 2 r, act' = 4 r (1 - r).
-
-// Per-lane table of the adjoint (4-byte words per lane).
-// The reverse step's input-row tiles hold the moment rows (and the bias row
-// 27) grouped by parity class, four classes per 16-row tile, so that the
-// products through the first layer run once per class (see k_adjoint_mfma):
-// positions 0-15 hold the classes 0 (with row 27), 1, 3, 7; positions 16-27
-// the classes 2, 4, 5, 6; positions 28-31 are empty (row 28, zero).
-__host__ __device__ constexpr int adj_tile_class(int kt, int i) {
-    constexpr int c[2][4] = {{0, 1, 3, 7}, {2, 4, 5, 6}};
-    return c[kt][i];
-}
-__host__ __device__ constexpr int moment_class(int k) {
-    return k >= 27 ? 0 : (row_tensor(k) % 3) % 2 + 2 * (((row_tensor(k) / 3) % 3) % 2) + 4 * ((row_tensor(k) / 9) % 2);
-}
-// Row of M (27 = bias row, 28 = empty) at tile position p.
-__host__ __device__ constexpr int adj_row(int p) {
-    for (int kt = 0; kt < 2; ++kt) {
-        int pos = 16 * kt;
-        for (int i = 0; i < 4; ++i)
-            for (int k = 0; k < 28; ++k)
-                if (moment_class(k) == adj_tile_class(kt, i)) {
-                    if (pos == p) return k;
-                    ++pos;
-                }
-        if (p < 16 * (kt + 1)) return 28;
-    }
-    return 28;
-}
-
-constexpr int AT_W2T = 0;           // [t 2][u 2][r 4]  W2[16 t + c][16 u + 4 q + r]
-constexpr int AT_W1T = 16;          // [kt 2][t 2][r 4] W1[adj_row(16 kt + c)][16 t + 4 q + r] (rows >= 27: 0)
-constexpr int AT_W3 = 32;           // [u 2][r 4][n 4]  W3[16 u + 4 q + r][n] / 48
-constexpr int AT_CLS = 64;          // [kt 2][r 4]      class of position 16 kt + 4 q + r (-1: empty) (int)
-constexpr int AT_CLSC = 72;         // [kt 2]           class of position 16 kt + c (-1: empty) (int)
-constexpr int AT_ROWO = 74;         // [kt 2][r 4]      adj_row(16 kt + 4 q + r) (int)
-constexpr int AT_ROWC = 82;         // [kt 2]           adj_row(16 kt + c) (int)
-constexpr int ADJ_WORDS = 84;
-constexpr int ADJ_ROWS_AT = 64 * ADJ_WORDS;   // then [32] adj_row(p) (int), shared by all lanes
-constexpr int TB = 32;              // row stride of the per-wave transpose buffers
-
-// Column swizzle of row n of a per-wave transpose buffer: element (n, h) is
-// kept at n TB + (h ^ tr_swz(n)).  The buffers are written as (node c,
-// hidden 16 t + 4 q + r) and read as (node 4 st + q, hidden 16 x + c) by
-// the lanes (q, c); with node bits 0, 1, 2, 3 sent to column bits 4, 0, 1, 3
-// both patterns reach 32 distinct banks in each half-wavefront.
-__device__ __forceinline__ int tr_swz(int n) {
-    return ((n & 1) << 4) | ((n >> 1) & 1) | (((n >> 2) & 1) << 1) | (((n >> 3) & 1) << 3);
-}
-
-
-template <int ACT>
-__device__ __forceinline__ float act_grad(float r) {
-    if constexpr (ACT == ACT_RELU)
-        return r > 0.0f ? 1.0f : 0.0f;
-    else
-        return 4.0f * r * (1.0f - r);
-}
-
-template <int ACT>
-__device__ __forceinline__ float act_value(float r) {
-    if constexpr (ACT == ACT_RELU)
-        return r;
-    else
-        return 1.0f - 2.0f * r;
-}
-
-// TPW = 4: 256 nodes per block, 4 tiles per wavefront; TPW = 1: 64 nodes
-// per block, one tile per wavefront (a 4x shorter serial chain for lattices
-// too small to fill the device with 256-node blocks).
-template <int S, int ACT, int TPW>
-__global__ __launch_bounds__(256) void k_adjoint_mfma(const typename Codec<S>::store_t* __restrict__ xin,
-                                                      const float* __restrict__ lam_in, float* __restrict__ lam_out,
-                                                      StepArgs a, const float* __restrict__ lane_tab,
-                                                      const int* __restrict__ gtab, const float* __restrict__ adj_tab,
-                                                      const int* __restrict__ gsrc, double* __restrict__ partial) {
-    __shared__ float sm[256 * NODE_STRIDE];     // moments (row order of M; [27] = 1, [28] = 0)
-    __shared__ int sg[GT_ENTRIES];              // forward gather table
-    __shared__ int sgs[6 * 27];                 // source rows of the reflection-free elements g = 8 pi
-    __shared__ float sw[256 * 4];               // tilde tau, then dL/d tilde tau
-    __shared__ float som[256 * 4];              // rates omega_3..omega_6
-    __shared__ float sF[256 * 3];               // body force
-    __shared__ float sdm[256 * 32];             // group sums of the second layer, then dL/dm (network part)
-    __shared__ float sbuf[4][3][16 * TB];       // per-wave transposes
-    const int tid = threadIdx.x;
-    constexpr int NB = 64 * TPW;                // nodes of the block
-    const int idx = blockIdx.x * NB + tid;
-    const bool live = (NB == 256 || tid < NB) && idx < a.n;
-    const NodeIdx p = node_of(live ? idx : 0, a.nx, a.ny);
-
-    for (int e = tid; e < GT_ENTRIES; e += 256) sg[e] = gtab[e];
-    for (int e = tid; e < 6 * 27; e += 256) sgs[e] = gsrc[(e / 27) * 8 * 27 + e % 27] & 31;
-    // Phase A: moments of the pulled state, body force.
-    {
-        float f[Q], m[Q];
-        if (live) {
-            pull<S>(xin, a, p, f);
-        } else {
-#pragma unroll
-            for (int i = 0; i < Q; ++i) f[i] = (float)weight_of(i);
-        }
-        to_moments(f, m);
-        float* row = sm + tid * NODE_STRIDE;
-#pragma unroll
-        for (int k = 0; k < Q; ++k) row[k] = m[row_tensor(k)];
-        row[27] = 1.0f;
-        row[28] = 0.0f;
-        float Fd[3] = {0.0f, 0.0f, 0.0f};
-        if (a.n_modes > 0 && live) read_force(a, idx, Fd[0], Fd[1], Fd[2]);
-#pragma unroll
-        for (int d = 0; d < 3; ++d) sF[tid * 3 + d] = Fd[d];
-    }
-    __syncthreads();
-
-    const int wave = tid >> 6, lane = tid & 63, q = lane >> 4, c = lane & 15;
-    // Phase B1: the network forward for tilde tau and the group sums, or the
-    // values the forward step of this state kept (the same arithmetic on the
-    // same moments, so the same values).  Places past the last node, which
-    // the forward step need not have written, read as zero.
-    if (a.net_sums) {
-        if (tid < NB) {
-            const float* __restrict__ src = a.net_sums + ((size_t)blockIdx.x * NB + tid) * NET_SUMS_PER_NODE;
-#pragma unroll
-            for (int k = 0; k < 32; ++k) sdm[tid * 32 + k] = live ? src[k] : 0.0f;
-#pragma unroll
-            for (int n = 0; n < 4; ++n) sw[tid * 4 + n] = live ? src[32 + n] : 0.0f;
-        }
-    } else {
-        network_f32<ACT, 2, TPW>(sm, sg, sw, lane_tab + lane * LANE_WORDS, wave, q, c, nullptr, sdm);
-    }
-    __syncthreads();
-
-    // Phase B2: per node, dL/d tilde tau from the node-local collision adjoint.
-    {
-        float m[Q], lam[Q], nu[Q], gm[Q], omega[4], tau[4], e[4], domega[4];
-        const float* row = sm + tid * NODE_STRIDE;
-#pragma unroll
-        for (int k = 0; k < Q; ++k) m[row_tensor(k)] = row[k];
-#pragma unroll
-        for (int n = 0; n < 4; ++n) {
-            e[n] = expf(sw[tid * 4 + n]);
-            tau[n] = 0.5f + 0.5f / (1.0f + e[n]);
-            omega[n] = 1.0f / tau[n];
-            som[tid * 4 + n] = omega[n];
-        }
-#pragma unroll
-        for (int i = 0; i < Q; ++i) lam[i] = live ? lam_in[(size_t)i * a.n + idx] : 0.0f;
-        inverse_T(lam, nu);
-        const float F[3] = {sF[tid * 3], sF[tid * 3 + 1], sF[tid * 3 + 2]};
-        collision_vjp_local(m, nu, a.omega_nu_f, omega, a.n_modes > 0, F, gm, domega);
-#pragma unroll
-        for (int n = 0; n < 4; ++n)
-            sw[tid * 4 + n] = domega[n] * 0.5f * e[n] / ((1.0f + e[n]) * (1.0f + e[n]) * tau[n] * tau[n]);
-    }
-    __syncthreads();
-
-    // Output layer: dW3 = sum (H2 / 48) dtt^T with H2 the group sum of the
-    // (unfolded) second-layer activations, db3 = sum dtt.
-    double* __restrict__ out = partial + (size_t)blockIdx.x * NPAR;
-    if (tid < 132) {
-        double sacc = 0.0;
-        if (tid < 128) {
-            const int o = tid >> 2, n = tid & 3;
-            float v = 0.0f;
-            for (int nd = 0; nd < NB; ++nd) {
-                const float acc = sdm[nd * 32 + o];
-                const float h2 = ACT == ACT_RELU ? acc : (float)NGROUP - 2.0f * acc;
-                v = fmaf(h2 * (1.0f / NGROUP), sw[nd * 4 + n], v);
-            }
-            sacc = v;
-            out[OFF_W3 + o * 4 + n] += sacc;
-        } else {
-            const int n = tid - 128;
-            float v = 0.0f;
-            for (int nd = 0; nd < NB; ++nd) v += sw[nd * 4 + n];
-            out[OFF_B3 + n] += (double)v;
-        }
-    }
-    __syncthreads();
-    for (int k = 0; k < 32; ++k) sdm[tid * 32 + k] = 0.0f;
-    __syncthreads();
-
-    // Phase B3: the network adjoint on the matrix cores.
-    f32x4 gW2[2][2], gW1[2][2];
-    float gb2[2][4];
-#pragma unroll
-    for (int x = 0; x < 2; ++x)
-#pragma unroll
-        for (int y = 0; y < 2; ++y) {
-            gW2[x][y] = f32x4{0.f, 0.f, 0.f, 0.f};
-            gW1[x][y] = f32x4{0.f, 0.f, 0.f, 0.f};
-        }
-#pragma unroll
-    for (int u = 0; u < 2; ++u)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) gb2[u][r] = 0.0f;
-    {
-        const float* __restrict__ lt = lane_tab + lane * LANE_WORDS;
-        const float* __restrict__ at = adj_tab + lane * ADJ_WORDS;
-        const int* __restrict__ ati = reinterpret_cast<const int*>(at);
-        float A1[2][KSTEPS], A2[2][2][4], B2[2][4], W2T[2][2][4], W1T[2][2][4];
-#pragma unroll
-        for (int t = 0; t < 2; ++t)
-#pragma unroll
-            for (int st = 0; st < KSTEPS; ++st) A1[t][st] = lt[LT_A1 + t * KSTEPS + st];
-#pragma unroll
-        for (int u = 0; u < 2; ++u)
-#pragma unroll
-            for (int t = 0; t < 2; ++t)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    A2[u][t][r] = lt[LT_A2 + u * 8 + t * 4 + r];
-                    W2T[t][u][r] = at[AT_W2T + t * 8 + u * 4 + r];
-                    W1T[u][t][r] = at[AT_W1T + u * 8 + t * 4 + r];
-                }
-#pragma unroll
-        for (int u = 0; u < 2; ++u)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) B2[u][r] = lt[LT_B2 + u * 4 + r];
-        int cls[2][4], clsc[2], rowo[2][4], rowc[2];
-#pragma unroll
-        for (int kt = 0; kt < 2; ++kt) {
-            clsc[kt] = ati[AT_CLSC + kt];
-            rowc[kt] = ati[AT_ROWC + kt];
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                cls[kt][r] = ati[AT_CLS + kt * 4 + r];
-                rowo[kt][r] = ati[AT_ROWO + kt * 4 + r];
-            }
-        }
-        float* __restrict__ bh = sbuf[wave][0];
-        float* __restrict__ bz2 = sbuf[wave][1];
-        float* __restrict__ bz1 = sbuf[wave][2];
-        const int swz_w = tr_swz(c);
-
-#pragma unroll 1
-        for (int j = 0; j < TPW; ++j) {
-            const int base = wave * 16 * TPW + j * 16;
-            const int node = base + c;
-            const float* __restrict__ mrow = sm + node * NODE_STRIDE;
-            // dh2 = W3 dtt / 48 for this lane's rows.
-            float dh2[2][4];
-            {
-                float dt[4];
-#pragma unroll
-                for (int n = 0; n < 4; ++n) dt[n] = sw[node * 4 + n];
-#pragma unroll
-                for (int u = 0; u < 2; ++u)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        float v = 0.0f;
-#pragma unroll
-                        for (int n = 0; n < 4; ++n) v = fmaf(at[AT_W3 + (u * 4 + r) * 4 + n], dt[n], v);
-                        dh2[u][r] = v;
-                    }
-            }
-#pragma unroll 1
-            for (int pi = 0; pi < 6; ++pi) {
-                // Layer 1 of the eight reflections (as in the forward).
-                const int* __restrict__ ge = sg + (pi * 4 + q) * GT_STRIDE;
-                float b[KSTEPS];
-#pragma unroll
-                for (int st = 0; st < KSTEPS; ++st) b[st] = mrow[ge[st]];
-                f32x4 Y[8][2];
-#pragma unroll
-                for (int ci = 0; ci < 8; ++ci) {
-                    Y[ci][0] = f32x4{0.f, 0.f, 0.f, 0.f};
-                    Y[ci][1] = f32x4{0.f, 0.f, 0.f, 0.f};
-                }
-#pragma unroll
-                for (int st = 0; st < KSTEPS; ++st)
-#pragma unroll
-                    for (int t = 0; t < 2; ++t) Y[step_class(st)][t] = mfma4(A1[t][st], b[st], Y[step_class(st)][t]);
-#pragma unroll
-                for (int bit = 1; bit < 8; bit <<= 1)
-#pragma unroll
-                    for (int ci = 0; ci < 8; ++ci)
-                        if (!(ci & bit))
-#pragma unroll
-                            for (int t = 0; t < 2; ++t) {
-                                const f32x4 u0 = Y[ci][t], u1 = Y[ci | bit][t];
-                                Y[ci][t] = u0 + u1;
-                                Y[ci | bit][t] = u0 - u1;
-                            }
-                // x_pi (reflection-free input) in the A layout of the dW1
-                // product: the row at position 16 kt + c, node 4 st + q of
-                // the tile.
-                float xa[2][4];
-#pragma unroll
-                for (int kt = 0; kt < 2; ++kt) {
-                    const int k = rowc[kt];
-                    const int src = k < 27 ? sgs[pi * 27 + k] : k;
-#pragma unroll
-                    for (int st = 0; st < 4; ++st) xa[kt][st] = sm[(base + 4 * st + q) * NODE_STRIDE + src];
-                }
-                f32x4 Z[8][2];                  // dz1 of reflection s, then its class transform
-
-#pragma unroll
-                for (int s = 0; s < 8; ++s) {
-                    float r1[2][4], d1[2][4];
-#pragma unroll
-                    for (int t = 0; t < 2; ++t)
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) {
-                            r1[t][r] = act_scaled<ACT>(Y[s][t][r]);
-                            d1[t][r] = act_grad<ACT>(r1[t][r]);
-                        }
-                    f32x4 c2[2];
-#pragma unroll
-                    for (int u = 0; u < 2; ++u) c2[u] = f32x4{B2[u][0], B2[u][1], B2[u][2], B2[u][3]};
-#pragma unroll
-                    for (int t = 0; t < 2; ++t)
-#pragma unroll
-                        for (int r = 0; r < 4; ++r)
-#pragma unroll
-                            for (int u = 0; u < 2; ++u) c2[u] = mfma4(A2[u][t][r], r1[t][r], c2[u]);
-                    float dz2[2][4];
-#pragma unroll
-                    for (int u = 0; u < 2; ++u)
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) {
-                            dz2[u][r] = dh2[u][r] * act_grad<ACT>(act_scaled<ACT>(c2[u][r]));
-                            gb2[u][r] += dz2[u][r];
-                        }
-                    // dh1 = W2 dz2, dz1 = dh1 act'(z1).
-                    f32x4 h[2];
-#pragma unroll
-                    for (int t = 0; t < 2; ++t) {
-                        h[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                        for (int u = 0; u < 2; ++u)
-#pragma unroll
-                            for (int r = 0; r < 4; ++r) h[t] = mfma4(W2T[t][u][r], dz2[u][r], h[t]);
-                    }
-#pragma unroll
-                    for (int t = 0; t < 2; ++t)
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) Z[s][t][r] = h[t][r] * d1[t][r];
-                    // Transposes: [node c][hidden] from the accumulator layout.
-#pragma unroll
-                    for (int t = 0; t < 2; ++t)
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) {
-                            const int o = c * TB + ((16 * t + 4 * q + r) ^ swz_w);
-                            bh[o] = act_value<ACT>(r1[t][r]);
-                            bz2[o] = dz2[t][r];
-                        }
-                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                    __builtin_amdgcn_wave_barrier();
-                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-                    float ha[2][4], zb2[2][4];
-#pragma unroll
-                    for (int x = 0; x < 2; ++x)
-#pragma unroll
-                        for (int st = 0; st < 4; ++st) {
-                            const int o = (4 * st + q) * TB + ((16 * x + c) ^ tr_swz(4 * st + q));
-                            ha[x][st] = bh[o];
-                            zb2[x][st] = bz2[o];
-                        }
-                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                    __builtin_amdgcn_wave_barrier();
-                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-                    // dW2[j][o] += sum over the tile's nodes h1[j] dz2[o].
-#pragma unroll
-                    for (int x = 0; x < 2; ++x)
-#pragma unroll
-                        for (int y = 0; y < 2; ++y)
-#pragma unroll
-                            for (int st = 0; st < 4; ++st) gW2[x][y] = mfma4(ha[x][st], zb2[y][st], gW2[x][y]);
-                }
-                // The first layer's input x_g = chi_s x_pi differs between
-                // the reflections only by the sign chi_s(class k) of each
-                // row, so dx_g and the dW1 terms of the 8 reflections need
-                // dz1 only through Z_cl = sum_s chi_s(cl) dz1_s (the
-                // Walsh-Hadamard transform over s, the same butterfly as
-                // the forward's): dL/dm[k] = (W1 Z_class(k))[k] and
-                // dW1[k][j] += x_pi[k] Z_class(k)[j].  With the rows grouped
-                // by class, four classes per 16-row tile, each runs once
-                // per class instead of once per reflection.
-#pragma unroll
-                for (int bit = 1; bit < 8; bit <<= 1)
-#pragma unroll
-                    for (int ci = 0; ci < 8; ++ci)
-                        if (!(ci & bit))
-#pragma unroll
-                            for (int t = 0; t < 2; ++t) {
-                                const f32x4 u0 = Z[ci][t], u1 = Z[ci | bit][t];
-                                Z[ci][t] = u0 + u1;
-                                Z[ci | bit][t] = u0 - u1;
-                            }
-                // dL/dm of this permutation: the row at position
-                // 16 kt + 4 q + r feeds from moment src_pi(row).
-#pragma unroll
-                for (int kt = 0; kt < 2; ++kt) {
-                    float D[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const int cl = adj_tile_class(kt, i);
-                        f32x4 dx = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                        for (int t = 0; t < 2; ++t)
-#pragma unroll
-                            for (int r = 0; r < 4; ++r) dx = mfma4(W1T[kt][t][r], Z[cl][t][r], dx);
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) D[r] = cls[kt][r] == cl ? dx[r] : D[r];
-                    }
-#pragma unroll
-                    for (int r = 0; r < 4; ++r)
-                        if (rowo[kt][r] < 27) sdm[node * 32 + sgs[pi * 27 + rowo[kt][r]]] += D[r];
-                }
-                // dW1 per class: A = the tile's x_pi rows of that class.
-#pragma unroll
-                for (int cl = 0; cl < 8; ++cl) {
-                    const int x = (cl == 0 || cl == 1 || cl == 3 || cl == 7) ? 0 : 1;
-#pragma unroll
-                    for (int t = 0; t < 2; ++t)
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) bz1[c * TB + ((16 * t + 4 * q + r) ^ swz_w)] = Z[cl][t][r];
-                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                    __builtin_amdgcn_wave_barrier();
-                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-                    float zb1[2][4];
-#pragma unroll
-                    for (int y = 0; y < 2; ++y)
-#pragma unroll
-                        for (int st = 0; st < 4; ++st)
-                            zb1[y][st] = bz1[(4 * st + q) * TB + ((16 * y + c) ^ tr_swz(4 * st + q))];
-                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                    __builtin_amdgcn_wave_barrier();
-                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-                    const bool mine = clsc[x] == cl;
-#pragma unroll
-                    for (int y = 0; y < 2; ++y)
-#pragma unroll
-                        for (int st = 0; st < 4; ++st)
-                            gW1[x][y] = mfma4(mine ? xa[x][st] : 0.0f, zb1[y][st], gW1[x][y]);
-                }
-            }
-        }
-    }
-    __syncthreads();
-
-    // Phase C: the full collision adjoint per node, scattered along the streaming.
-    {
-        float m[Q], lam[Q], nu[Q], gm[Q], omega[4], domega[4];
-        const float* row = sm + tid * NODE_STRIDE;
-#pragma unroll
-        for (int k = 0; k < Q; ++k) m[row_tensor(k)] = row[k];
-#pragma unroll
-        for (int n = 0; n < 4; ++n) omega[n] = som[tid * 4 + n];
-#pragma unroll
-        for (int i = 0; i < Q; ++i) lam[i] = live ? lam_in[(size_t)i * a.n + idx] : 0.0f;
-        inverse_T(lam, nu);
-        const float F[3] = {sF[tid * 3], sF[tid * 3 + 1], sF[tid * 3 + 2]};
-        collision_vjp_local(m, nu, a.omega_nu_f, omega, a.n_modes > 0, F, gm, domega);
-#pragma unroll
-        for (int k = 0; k < Q; ++k) gm[row_tensor(k)] += sdm[tid * 32 + k];
-        float gf[Q];
-        moments_T(gm, gf);
-        if (live) {
-            float v[Q];
-#pragma unroll
-            for (int i = 0; i < Q; ++i) v[i] = lam[i] + gf[i];
-            scatter_to_sources(lam_out, a, p, v);
-        }
-    }
-    __syncthreads();
-
-    // Block sums of the waves' gradients, in wave order, added to the block's row.
-    float* red = sm;                            // 4 waves x 1024 floats (reuses the moment tile)
-    // dW2: lane (q, c) holds [j = 16 x + 4 q + r][o = 16 y + c].
-#pragma unroll
-    for (int x = 0; x < 2; ++x)
-#pragma unroll
-        for (int y = 0; y < 2; ++y)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) red[wave * 1024 + (16 * x + 4 * q + r) * 32 + 16 * y + c] = gW2[x][y][r];
-    __syncthreads();
-    for (int e = tid; e < 1024; e += 256) {
-        const float v = red[e] + red[1024 + e] + red[2048 + e] + red[3072 + e];
-        out[OFF_W2 + e] += (double)v;
-    }
-    __syncthreads();
-    // dW1 and db1: lane (q, c) holds [position 16 x + 4 q + r][j = 16 y + c];
-    // the position's row is adj_row (27 is b1, 28 empty).
-#pragma unroll
-    for (int x = 0; x < 2; ++x)
-#pragma unroll
-        for (int y = 0; y < 2; ++y)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) red[wave * 1024 + (16 * x + 4 * q + r) * 32 + 16 * y + c] = gW1[x][y][r];
-    __syncthreads();
-    // Rows are tile positions (class-grouped): back to the parameter order.
-    const int* __restrict__ adj_rows = reinterpret_cast<const int*>(adj_tab + ADJ_ROWS_AT);
-    for (int e = tid; e < 32 * 32; e += 256) {
-        const int k = adj_rows[e >> 5], j = e & 31;
-        if (k > 27) continue;
-        const float v = red[e] + red[1024 + e] + red[2048 + e] + red[3072 + e];
-        out[(k < 27 ? OFF_W1 + k * 32 + j : OFF_B1 + j)] += (double)v;
-    }
-    __syncthreads();
-    // db2: lane (q, c) holds rows o = 16 u + 4 q + r summed over its nodes c.
-#pragma unroll
-    for (int u = 0; u < 2; ++u)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) red[(wave * 16 + c) * 32 + 16 * u + 4 * q + r] = gb2[u][r];
-    __syncthreads();
-    if (tid < 32) {
-        float v = 0.0f;
-        for (int w = 0; w < 64; ++w) v += red[w * 32 + tid];
-        out[OFF_B2 + tid] += (double)v;
     }
 }
 
@@ -1402,8 +856,8 @@ void mfma_prepare_tables(const float* params, int act, int prec, const int (*gsr
     class_slots(slot_row);
     for (int lane = 0; lane < 64; ++lane) {
         const int q = lane >> 4, c = lane & 15;
-        float* lt = lane_tab + lane * LANE_WORDS;
-        unsigned* lw = reinterpret_cast<unsigned*>(lt);
+        const LaneTabT<float> lt(lane_tab, lane);
+        const LaneTabT<unsigned> lw(reinterpret_cast<unsigned*>(lane_tab), lane);
         for (int i = 0; i < LANE_WORDS; ++i) lt[i] = 0.0f;
         if (prec == MLP_PREC_F32S) {
             // Parts of each layer's A operand in the K slots of its product:
@@ -1552,87 +1006,6 @@ void mfma_prepare_tables(const float* params, int act, int prec, const int (*gsr
             }
 }
 
-size_t mfma_adjoint_table_floats() { return 64 * ADJ_WORDS + 32; }
-
-// Per-lane table of the matrix-core adjoint from the flat parameters of a
-// width-32 network (unfolded weights: the adjoint works with h = tanh(z)).
-void mfma_prepare_adjoint_table(const float* params, float* tab) {
-    const int W = MW;
-    const float* W1 = params;
-    const float* W2 = W1 + 27 * W + W;
-    const float* W3 = W2 + W * W + W;
-    for (int lane = 0; lane < 64; ++lane) {
-        const int q = lane >> 4, c = lane & 15;
-        float* at = tab + lane * ADJ_WORDS;
-        int* ai = reinterpret_cast<int*>(at);
-        for (int t = 0; t < 2; ++t)
-            for (int u = 0; u < 2; ++u)
-                for (int r = 0; r < 4; ++r) at[AT_W2T + t * 8 + u * 4 + r] = W2[(16 * t + c) * W + 16 * u + 4 * q + r];
-        for (int kt = 0; kt < 2; ++kt)
-            for (int t = 0; t < 2; ++t)
-                for (int r = 0; r < 4; ++r) {
-                    const int k = adj_row(16 * kt + c);
-                    at[AT_W1T + kt * 8 + t * 4 + r] = k < 27 ? W1[k * W + 16 * t + 4 * q + r] : 0.0f;
-                }
-        for (int u = 0; u < 2; ++u)
-            for (int r = 0; r < 4; ++r)
-                for (int n = 0; n < 4; ++n)
-                    at[AT_W3 + (u * 4 + r) * 4 + n] = W3[(16 * u + 4 * q + r) * 4 + n] / (float)NGROUP;
-        for (int kt = 0; kt < 2; ++kt) {
-            for (int r = 0; r < 4; ++r) {
-                const int k = adj_row(16 * kt + 4 * q + r);
-                ai[AT_CLS + kt * 4 + r] = k < 28 ? moment_class(k) : -1;
-                ai[AT_ROWO + kt * 4 + r] = k;
-            }
-            const int k = adj_row(16 * kt + c);
-            ai[AT_CLSC + kt] = k < 28 ? moment_class(k) : -1;
-            ai[AT_ROWC + kt] = k;
-        }
-    }
-    int* rows = reinterpret_cast<int*>(tab + ADJ_ROWS_AT);
-    for (int p = 0; p < 32; ++p) rows[p] = adj_row(p);
-}
-
-// One 4-wavefront block per CU (the kernel's registers): with 256-node
-// blocks each wavefront runs 4 tiles per round, with 64-node blocks one tile
-// and 4x the blocks, so below 256 CUs x 256 nodes the small blocks finish in
-// fewer tile-rounds (4x fewer up to 16384 nodes) and above it they tie.
-constexpr int ADJM_SMALL_NODES = 65536;
-int adjoint_mfma_blocks(int n) { return n < ADJM_SMALL_NODES ? (n + 63) / 64 : (n + 255) / 256; }
-
-hipError_t launch_adjoint_mfma(int storage, int act, const void* xin, const float* lam_in, float* lam_out,
-                               const StepArgs& a, const float* lane_tab, const int* gtab, const float* adj_tab,
-                               const int* gsrc, double* partial, hipStream_t st) {
-    const bool small = a.n < ADJM_SMALL_NODES;
-    const dim3 grid(adjoint_mfma_blocks(a.n)), block(256);
-#define ADJM_LAUNCH(SS, ACT, TPW)                                                                                \
-    hipLaunchKernelGGL((k_adjoint_mfma<SS, ACT, TPW>), grid, block, 0, st,                                      \
-                       static_cast<const typename Codec<SS>::store_t*>(xin), lam_in, lam_out, a, lane_tab, gtab,  \
-                       adj_tab, gsrc, partial)
-#define ADJM_CASE(SS)                                                                                            \
-    case SS:                                                                                                     \
-        if (act == ACT_TANH) {                                                                                   \
-            if (small)                                                                                           \
-                ADJM_LAUNCH(SS, ACT_TANH, 1);                                                                    \
-            else                                                                                                 \
-                ADJM_LAUNCH(SS, ACT_TANH, 4);                                                                    \
-        } else {                                                                                                 \
-            if (small)                                                                                           \
-                ADJM_LAUNCH(SS, ACT_RELU, 1);                                                                    \
-            else                                                                                                 \
-                ADJM_LAUNCH(SS, ACT_RELU, 4);                                                                    \
-        }                                                                                                        \
-        return hipGetLastError();
-    switch (storage) {
-        ADJM_CASE(ST_F32)
-        ADJM_CASE(ST_F16)
-        ADJM_CASE(ST_BF16)
-        default: return hipErrorInvalidValue;
-    }
-#undef ADJM_CASE
-#undef ADJM_LAUNCH
-}
-
 // omega_out == nullptr: one stream-collide step fin -> fout.  Otherwise the
 // rates of the state in fin are written to omega_out and fout is untouched.
 hipError_t launch_nco_mfma_grouped(int storage, int prec, int act, const LaunchGroup& g, hipStream_t st) {
@@ -1672,8 +1045,8 @@ enum MfmaBlock { MFMA_BLOCK_256 = 0, MFMA_BLOCK_64 = 1, MFMA_BLOCK_64_TILE = 2 }
 // Float32-network steps of lattices up to this many nodes run twelve-wavefront
 // tiles (network_f32_psplit): 256 blocks, one round over the 256 CUs.  A
 // block holds 111 KB of LDS, one per CU, so beyond that the blocks run in
-// rounds and the one-tile-per-wavefront blocks are faster (16^3: 15 against
-// 30 us per step; 24^3: 53 against 31).
+// rounds and the one-tile-per-wavefront blocks are faster (16^3: 12.6 against
+// 30 us per step; in six-wavefront tiles of the same rounds, 24^3: 53 against 31).
 constexpr int PSPLIT_MAX_NODES = 4096;
 int mfma_block_kind(int n) {
     return n < 65536 ? MFMA_BLOCK_64_TILE : n < 2 * 256 * 256 ? MFMA_BLOCK_64 : MFMA_BLOCK_256;
@@ -1687,7 +1060,7 @@ hipError_t launch_mfma_kind(int kind, const void* fin, void* fout, const StepArg
     const dim3 grid((a.n + nodes - 1) / nodes);
     if constexpr (!RR && PP == MLP_PREC_F32) {
         // The instantiation that can keep the network values for the adjoint
-        // (when a.net_sums is set; depth 2) runs the plain steps too: with
+        // (when a.net_sums is set) runs the plain steps too: with
         // that branch the compiler allocates 154-161 VGPRs at depth 2, 3
         // waves per SIMD, where the instantiation without it takes 230 and 2
         // waves and runs 3 % slower; at depth 3, 177 against 254 (with

@@ -13,8 +13,22 @@ constexpr int MW = 32;              // network width on the matrix-core paths
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-// Offsets in the per-lane table of the float32 network (4-byte words per
-// lane: LANE_WORDS).
+// The per-lane table of a matrix-core network: LANE_WORDS 4-byte words per
+// lane, in one run.  (Quads of words interleaved over the lanes, so that a
+// wavefront's loads are contiguous, gave 1-2 % on the depth-2 networks and
+// cost 1-7 % on the others: the loads are short and cached, and the four-word
+// register tuples they arrive in raise the register count.)
+constexpr int LANE_WORDS = 144;
+
+template <typename T>
+struct LaneTabT {
+    T* p;
+    __host__ __device__ LaneTabT(T* table, int lane) : p(table + LANE_WORDS * lane) {}
+    __host__ __device__ __forceinline__ T& operator[](int w) const { return p[w]; }
+};
+using LaneTab = LaneTabT<const float>;
+
+// Offsets in the per-lane table of the float32 network.
 constexpr int LT_A1 = 0;            // [t 2][st 10]    W1 rows / b1 as A operand
 constexpr int LT_A2 = 20;           // [u 2][t 2][r 4] W2 as A operand
 constexpr int LT_B2 = 36;           // [u 2][r 4]      b2 as accumulator init
@@ -22,7 +36,6 @@ constexpr int LT_W3 = 44;           // [u 2][r 4][n 4] W3 / 48
 constexpr int LT_B3 = 76;           // [n 4]
 constexpr int LT_A2B = 80;          // [v 2][t 2][r 4] W2b as A operand (depth 3)
 constexpr int LT_B2B = 96;          // [v 2][r 4]      b2b as accumulator init (depth 3)
-constexpr int LANE_WORDS = 144;
 
 // Activation as evaluated on the matrix-core paths.  For tanh the
 // pre-activation arrives scaled by kappa = 2 log2(e) and the function returns
@@ -49,17 +62,19 @@ __device__ __forceinline__ f32x4 mfma4(float a, float b, f32x4 c) {
 // the pre-activation of reflection pattern s (hidden rows 16 t + 4 q + r).
 template <typename A, typename B>
 __device__ __forceinline__ void layer1_f32(A&& A1, B&& b, f32x4 (&Y)[8][2]) {
+    // Moment operand of this permutation, one K-step per register.
+    float x[KSTEPS];
+#pragma unroll
+    for (int st = 0; st < KSTEPS; ++st) x[st] = b(st);
 #pragma unroll
     for (int ci = 0; ci < 8; ++ci) {
         Y[ci][0] = f32x4{0.f, 0.f, 0.f, 0.f};
         Y[ci][1] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
 #pragma unroll
-    for (int st = 0; st < KSTEPS; ++st) {
-        const float x = b(st);
+    for (int st = 0; st < KSTEPS; ++st)
 #pragma unroll
-        for (int t = 0; t < 2; ++t) Y[step_class(st)][t] = mfma4(A1(t, st), x, Y[step_class(st)][t]);
-    }
+        for (int t = 0; t < 2; ++t) Y[step_class(st)][t] = mfma4(A1(t, st), x[st], Y[step_class(st)][t]);
 }
 
 __device__ __forceinline__ void reflections(f32x4 (&Y)[8][2]) {
@@ -118,20 +133,27 @@ __device__ __forceinline__ void act_f32(const f32x4 (&z)[2], f32x4 (&h)[2]) {
         for (int r = 0; r < 4; ++r) h[t][r] = act_scaled<ACT>(z[t][r]);
 }
 
+// Hides a lane's place in a weight table from the compiler, so that weights
+// read through it from here on are read where they are used instead of being
+// kept in registers for the whole reflection loop.
+__device__ __forceinline__ void fresh_lane(int& place) { asm("" : "+v"(place)); }
+
 // Reflections 0 .. NS - 1 (pre-activations Y) through the hidden layers; the
 // last layer's pre-activations of reflection s go to sink(s, z), in order.
 //
 // Depth 2 is software-pipelined over the reflections: while the 16 products
 // of reflection s run on the matrix cores, the vector units activate layer 1
 // of reflection s + 1 and layer 2 of reflection s - 1 (independent of them).
-template <int ACT, int DEPTH, int NS, typename A, typename AB, typename Sink>
+// fresh() runs before each reflection (see fresh_lane).
+template <int ACT, int DEPTH, int NS, typename A, typename AB, typename Fresh, typename Sink>
 __device__ __forceinline__ void hidden_reflections(A&& A2, const f32x4 (&B2)[2], AB&& A2b, const f32x4 (&B2b)[2],
-                                                   const f32x4 (&Y)[8][2], Sink&& sink) {
+                                                   const f32x4 (&Y)[8][2], Fresh&& fresh, Sink&& sink) {
     if constexpr (DEPTH == 3) {
         // Unrolled: Y[s] must stay in registers.
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
             f32x4 h[2], c[2] = {B2[0], B2[1]}, c3[2] = {B2b[0], B2b[1]};
+            fresh();
             act_f32<ACT>(Y[s], h);
             hidden_f32(A2, h, c);
             act_f32<ACT>(c, h);
@@ -165,11 +187,11 @@ __device__ __forceinline__ void add_act(const f32x4 (&z)[2], f32x4 (&acc)[2]) {
 }
 
 // Output layer on the group sum of one node tile and the rate squashing;
-// lanes of group q = 0 write the four rates of node (tile, c) to LDS, or with
-// RAW the pre-squash outputs tilde tau_n (for the adjoint).
-template <bool RAW = false>
-__device__ __forceinline__ void output_layer(const f32x4 (&acc)[2], const float* __restrict__ w3,
-                                             const float* __restrict__ b3, int q, float* __restrict__ sw_node,
+// w3 and b3 are the layer's offsets in the lane's table; the lanes of group
+// q = 0 write the four rates of node (tile, c) to LDS, and the pre-squash
+// outputs tilde tau_n to tt_node unless it is null.
+__device__ __forceinline__ void output_layer(const f32x4 (&acc)[2], LaneTab lt, int w3, int b3, int q,
+                                             float* __restrict__ sw_node,
                                              float* __restrict__ tt_node = nullptr) {
     float pn[4];
 #pragma unroll
@@ -178,7 +200,7 @@ __device__ __forceinline__ void output_layer(const f32x4 (&acc)[2], const float*
 #pragma unroll
         for (int u = 0; u < 2; ++u)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) v = fmaf(w3[(u * 4 + r) * 4 + n], acc[u][r], v);
+            for (int r = 0; r < 4; ++r) v = fmaf(lt[w3 + (u * 4 + r) * 4 + n], acc[u][r], v);
         v += __shfl_xor(v, 16, 64);
         v += __shfl_xor(v, 32, 64);
         pn[n] = v;
@@ -186,8 +208,8 @@ __device__ __forceinline__ void output_layer(const f32x4 (&acc)[2], const float*
     if (q == 0) {
 #pragma unroll
         for (int n = 0; n < 4; ++n) {
-            const float t = pn[n] + b3[n];
-            sw_node[n] = RAW ? t : 1.0f / (0.5f + 0.5f / (1.0f + expf(t)));
+            const float t = pn[n] + lt[b3 + n];
+            sw_node[n] = 1.0f / (0.5f + 0.5f / (1.0f + expf(t)));
             if (tt_node) tt_node[n] = t;
         }
     }

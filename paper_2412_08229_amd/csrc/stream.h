@@ -143,6 +143,20 @@ __device__ __forceinline__ void scatter_to_sources(float* __restrict__ out, cons
     }
 }
 
+// One of scatter_to_sources' 27 stores.
+__device__ __forceinline__ void scatter_one(float* __restrict__ out, const StepArgs& a, NodeIdx p, int i, float v) {
+    const int cx = cx_of(i), cy = cy_of(i), cz = cz_of(i);
+    if (on_octant_face(a, p)) {
+        const Slot s = fold_octant(a.nx, p.x - cx, p.y - cy, p.z - cz, cx, cy, cz);
+        out[(size_t)s.plane * a.n + s.node] = v;
+        return;
+    }
+    const int x = cx < 0 ? (p.x == a.nx - 1 ? 0 : p.x + 1) : cx > 0 ? (p.x == 0 ? a.nx - 1 : p.x - 1) : p.x;
+    const int y = cy < 0 ? (p.y == a.ny - 1 ? 0 : p.y + 1) : cy > 0 ? (p.y == 0 ? a.ny - 1 : p.y - 1) : p.y;
+    const int z = cz < 0 ? (p.z == a.nz - 1 ? 0 : p.z + 1) : cz > 0 ? (p.z == 0 ? a.nz - 1 : p.z - 1) : p.z;
+    out[(size_t)i * a.n + ((size_t)z * a.ny + y) * a.nx + x] = v;
+}
+
 template <int S>
 __device__ __forceinline__ void load_local(const typename Codec<S>::store_t* __restrict__ fin,
                                            int n, int idx, typename Codec<S>::real (&f)[Q]) {

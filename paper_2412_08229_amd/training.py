@@ -107,8 +107,7 @@ class DissipationUnroll:
     domain: 'periodic' (the box itself) or 'tgv_octant', the reduced cube of
     Appendix A, whose n nodes per edge stand for the N = 4n box (fields from
     ``inputs.tgv3d_octant``).  depth: hidden layers of the network (3 adds
-    the paper's extra layer for this training; vector-unit network, mlp
-    'f32')."""
+    the paper's extra layer for this training)."""
 
     def __init__(self, shape, tau, rho, u, u0, nsteps, ckpt_every, every, eps_ref, t_min=1.0,
                  storage="f32", act="tanh", mlp="f32_mfma", width=32, stream=None, domain="periodic", depth=2):

@@ -1,0 +1,54 @@
+"""The matrix-core reverse step at the edges of its tiles, blocks and shapes,
+at both depths: against the oracle on a few nodes, against the vector-unit
+adjoint on both sides of the switch between its block shapes and where a block
+takes several groups of nodes."""
+import numpy as np
+import pytest
+
+from oracle import adjoint, collision
+from paper_2412_08229_amd import Lattice, inputs
+
+pytestmark = pytest.mark.gpu
+
+
+def _gradient(shape, width, depth, act, mlp, T, K, cache=None):
+    params = inputs.mlp_params(width, 21, depth=depth)
+    f0 = inputs.random_populations(shape, seed=22, lo=0.9, hi=1.1)
+    w = np.random.Generator(np.random.PCG64(23)).standard_normal((27,) + shape)
+    with Lattice(shape, "f32", "nco", 0.57) as lat:
+        lat.set_net_weights(params, width, act, mlp, depth=depth)
+        if cache is not None:
+            lat.set_reverse_cache(cache)
+        lat.init_populations(f0)
+        fs = lat.populations()
+        lat.forward_record(T, K)
+        g, df0 = lat.backward(dL_df=w, want_df0=True)
+    return params, fs, w, g, df0
+
+
+@pytest.mark.parametrize("width,depth,act", [(32, 2, "tanh"), (32, 2, "relu"), (20, 3, "relu"), (32, 3, "tanh")])
+@pytest.mark.parametrize("shape", [(1, 1, 1), (3, 1, 5), (1, 17, 1), (7, 3, 3), (5, 13, 1)])
+def test_gradient_matches_oracle_at_tile_edges(shape, width, depth, act):
+    """1, 15, 17, 63 and 65 nodes, 3 steps in segments of 2: float32 sums of
+    at most 65 x 48 terms of either sign, a few 1e-6 of the gradient's norm."""
+    params, fs, w, g, df0 = _gradient(shape, width, depth, act, "f32_mfma", 3, 2)
+    layers = collision.unpack_params(params, width, depth=depth)
+    _, go, gfo = adjoint.run_and_grad(fs, 0.57, layers, act, 3, lambda x: (float((w * x).sum()), w))
+    go = adjoint.flatten(go)
+    assert np.linalg.norm(g - go) < 2e-5 * np.linalg.norm(go)
+    assert np.linalg.norm(df0 - gfo) < 2e-5 * np.linalg.norm(gfo)
+
+
+@pytest.mark.parametrize("width,depth,act", [(32, 2, "relu"), (20, 3, "relu"), (32, 3, "tanh")])
+@pytest.mark.parametrize("shape", [(8, 32, 32), (8, 32, 33), (33, 64, 64)])
+def test_gradient_matches_vector_adjoint_at_shape_switches(shape, width, depth, act):
+    """8192 nodes (tiles), 8448 (64-node blocks), 135168 (two groups per
+    block, the last block half empty); one step, so that both adjoints see
+    the same state.  With kept network values or without, the gradient is the
+    same bit for bit."""
+    _, _, _, g, df0 = _gradient(shape, width, depth, act, "f32_mfma", 1, 1)
+    _, _, _, g0, df00 = _gradient(shape, width, depth, act, "f32_mfma", 1, 1, cache=0)
+    assert np.array_equal(g, g0) and np.array_equal(df0, df00)
+    _, _, _, gv, dfv = _gradient(shape, width, depth, act, "f32", 1, 1)
+    assert np.linalg.norm(g - gv) < 1e-4 * np.linalg.norm(gv)
+    assert np.linalg.norm(df0 - dfv) < 2e-6 * np.linalg.norm(dfv)
