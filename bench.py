@@ -43,7 +43,7 @@ VARIANTS = {
     "nco_f16store_bf16net": ("nco", "f16", "bf16", "tanh"),
     "nco_bf16store_bf16net": ("nco", "bf16", "bf16", "tanh"),
     "nco_relu_bf16net": ("nco", "f32", "bf16", "relu"),
-    "nco_valu": ("nco", "f32", "f32", "tanh"),
+    "nco_f32full": ("nco", "f32", "f32", "tanh"),
     "bgk": ("bgk", "f32", None, None),
     "bgk_f16store": ("bgk", "f16", None, None),
     "bgk_bf16store": ("bgk", "bf16", None, None),
@@ -64,11 +64,11 @@ NET_WIDTH = {"nco_w20_relu": 20, "nco_w20_relu_bf16net": 20, "nco_w20_relu_f32sp
 # The paper's network for the dissipation training, 27-20-20-20-4 ReLU (third
 # hidden layer; on the matrix cores zero-padded to width 32).
 VARIANTS["nco_d3_w20_relu"] = ("nco", "f32", "f32_mfma", "relu")
-VARIANTS["nco_d3_w20_relu_valu"] = ("nco", "f32", "f32", "relu")
+VARIANTS["nco_d3_w20_relu_f32full"] = ("nco", "f32", "f32", "relu")
 VARIANTS["nco_d3_w20_relu_f32split"] = ("nco", "f32", "f32_split", "relu")
 VARIANTS["nco_d3_w20_relu_bf16net"] = ("nco", "f32", "bf16", "relu")
 NET_DEPTH = {}
-for _v in ("nco_d3_w20_relu", "nco_d3_w20_relu_valu", "nco_d3_w20_relu_f32split", "nco_d3_w20_relu_bf16net"):
+for _v in ("nco_d3_w20_relu", "nco_d3_w20_relu_f32full", "nco_d3_w20_relu_f32split", "nco_d3_w20_relu_bf16net"):
     NET_WIDTH[_v], NET_DEPTH[_v] = 20, 3
 # The same Taylor-Green vortex on the reduced cube of Appendix A: an n/4
 # cube standing for the n box (the node grid is offset by half a spacing).
@@ -351,8 +351,7 @@ def tgv_training(cubes, res, mas, ref_cube, epochs, lr, t_end=15.0, samples=100,
     before and after training, for the fixed-rate operator and BGK (or the
     time they became unstable), and the time per epoch.  The network is
     27-width-...-4 with ``depth`` hidden layers (depth 3 with width 20 and
-    ReLU is the paper's network for this training; it runs on the vector
-    units, mlp 'f32').  Prints one JSON line."""
+    ReLU is the paper's network for this training).  Prints one JSON line."""
     from paper_2412_08229_amd import inputs
     from paper_2412_08229_amd.training import DissipationUnroll, tgv_cube_energy, train_batched
 
@@ -726,11 +725,8 @@ def main():
         if kind == "mrt":
             lat.set_rates([4.0 / 3.0] * 4)
         lat.init_equilibrium(rho_op, u_op)
-        # The per-node vector-unit network is kept as a reference variant; it
-        # is two orders slower, so it is timed on fewer steps.
-        slow = kind == "nco" and mlp == "f32"
-        steps = min(args.steps, 10) if slow else args.steps
-        ms = time_op(lat, steps, min(args.warmup, 2) if slow else args.warmup, torch, tstream)
+        steps = args.steps
+        ms = time_op(lat, steps, args.warmup, torch, tstream)
         s = lat.global_sums()
         if not np.all(np.isfinite(s)):
             raise RuntimeError("non-finite state after the %s run" % op)

@@ -63,9 +63,11 @@ typedef enum { NCO_F32 = 0, NCO_F16_DEV = 1, NCO_BF16_DEV = 2, NCO_F64 = 3 } nco
 
 typedef enum { NCO_OP_BGK = 0, NCO_OP_MRT = 1, NCO_OP_NCO = 2, NCO_OP_STREAM = 3 } nco_op;
 
-/* Arithmetic of the network: float32 (VALU; in float64, on the matrix cores,
- * for NCO_F64 storage), float32 matrix cores, bf16
- * matrix-core products with float32 accumulation, or float32 split over the
+/* Arithmetic of the network, on the matrix cores: float32 with tanh itself to
+ * the last place or two (NCO_MLP_F32; in float64 for NCO_F64 storage),
+ * float32 with tanh folded into the weights (NCO_MLP_F32_MFMA: about 1e-7
+ * absolute, 1.6 x as fast), bf16
+ * products with float32 accumulation, or float32 split over the
  * 16-bit matrix cores (NCO_MLP_F32_SPLIT: the first layer on the float32
  * matrix cores; each hidden-to-hidden layer's weights and activations split
  * into parts whose products, accumulated in float32, give the float32
@@ -180,9 +182,10 @@ int nco_set_rates(nco_lattice* lat, const double omega_high[4]);
  * (each W stored [in][out] row-major).  The input is the full moment vector
  * m^(g) = M Pi_g f in the row order of M; the output is tilde tau_n for the
  * orders 3..6.  width must be 8, 16, 20 or 32 (the paper's network is
- * width 20 with ReLU).  The matrix-core arithmetics (NCO_MLP_F32_MFMA,
- * NCO_MLP_BF16, NCO_MLP_F32_SPLIT) need float32 or 16-bit storage and run
- * narrower networks zero-padded to width 32, at the cost of width 32. */
+ * width 20 with ReLU).  NCO_MLP_F32_MFMA, NCO_MLP_BF16 and
+ * NCO_MLP_F32_SPLIT need float32 or 16-bit storage and run narrower networks
+ * zero-padded to width 32, at the cost of width 32 (NCO_MLP_F32: to 16 or
+ * 32). */
 int nco_set_net_weights(nco_lattice* lat, int width, int act, int mlp_prec,
                         const float* params, size_t n_params);
 
@@ -191,8 +194,7 @@ int nco_set_net_weights(nco_lattice* lat, int width, int act, int mlp_prec,
  * 27 -> width -> width -> width -> 4, params in the order W1[27][width],
  * b1, W2[width][width], b2, W2b[width][width], b2b, W3[width][4], b3
  * (n_params = width*(27 + 2 width + 4) + 3 width + 4).  Depth 3 runs in
- * every network arithmetic (the matrix-core ones with narrower networks
- * zero-padded to width 32) and has the reverse mode: nco_backward returns
+ * every network arithmetic (narrower networks zero-padded to width 32) and has the reverse mode: nco_backward returns
  * the gradient in this parameter order.  nco_batch_step refuses
  * depth-3 lattices.  Setting the weights drops a recorded run. */
 int nco_set_net_weights_depth(nco_lattice* lat, int depth, int width, int act, int mlp_prec,

@@ -173,7 +173,10 @@ struct nco_lattice {
     size_t pop_bytes = 0;
     double omega_high[4] = {1.0, 1.0, 1.0, 1.0};
     float* net = nullptr;
-    void* mfma_tab = nullptr;     // per-lane operand table + group gather table
+    // Per-lane operand table + group gather table of the network in its
+    // arithmetic (mfma_tab; not for NCO_MLP_F32) and in full float32.
+    void* mfma_tab = nullptr;
+    void* full_tab = nullptr;
     void* f64_tab = nullptr;      // network table of float64 storage
     int width = 0, act = 0, mlp_prec = 0;
     int depth = 2;                // hidden layers
@@ -338,10 +341,14 @@ bool use_mfma(const nco_lattice* lat) {
     return lat->op == NCO_OP_NCO && lat->mlp_prec != NCO_MLP_F32 && lat->mfma_tab;
 }
 bool use_f64_net(const nco_lattice* lat) { return lat->op == NCO_OP_NCO && lat->storage == NCO_F64; }
-const float* mfma_lane_tab(const nco_lattice* lat) { return static_cast<const float*>(lat->mfma_tab); }
-const int* mfma_group_tab(const nco_lattice* lat) {
-    return reinterpret_cast<const int*>(static_cast<const char*>(lat->mfma_tab) +
-                                        sizeof(float) * mfma_lane_table_floats());
+// Matrix-core network of a step or of rates, in the lattice's arithmetic or in
+// full float32.
+hipError_t launch_net(const nco_lattice* lat, int prec, const void* fin, void* fout, const StepArgs& a,
+                      double* omega_out) {
+    const char* tab = static_cast<const char*>(prec == NCO_MLP_F32 ? lat->full_tab : lat->mfma_tab);
+    return launch_nco_mfma(lat->storage, prec, fin, fout, a, reinterpret_cast<const float*>(tab),
+                           reinterpret_cast<const int*>(tab + sizeof(float) * mfma_lane_table_floats()), omega_out,
+                           lat->stream);
 }
 
 StepArgs step_args(const nco_lattice* lat) {
@@ -444,11 +451,10 @@ int launch_one(nco_lattice* lat, const void* fin, void* fout, long t, int slot =
         a.fhat = fh;
     }
     if (int rc = force_field(lat, a, lat->stream)) return rc;
-    if (use_mfma(lat))
-        HIP_TRY(launch_nco_mfma(lat->storage, lat->mlp_prec, fin, fout, a, mfma_lane_tab(lat), mfma_group_tab(lat),
-                                nullptr, lat->stream));
-    else if (use_f64_net(lat))
+    if (use_f64_net(lat))
         HIP_TRY(launch_nco_f64(fin, fout, a, lat->f64_tab, nullptr, lat->stream));
+    else if (lat->op == NCO_OP_NCO)
+        HIP_TRY(launch_net(lat, lat->mlp_prec, fin, fout, a, nullptr));
     else
         HIP_TRY(launch_step(lat->storage, fin, fout, a, lat->stream));
     return NCO_OK;
@@ -530,6 +536,7 @@ int nco_lattice_destroy(nco_lattice* lat) {
         if (lat->f[b]) hipFree(lat->f[b]);
     if (lat->net) hipFree(lat->net);
     if (lat->mfma_tab) hipFree(lat->mfma_tab);
+    if (lat->full_tab) hipFree(lat->full_tab);
     if (lat->f64_tab) hipFree(lat->f64_tab);
     if (lat->staging) hipFree(lat->staging);
     if (lat->partial) hipFree(lat->partial);
@@ -640,10 +647,7 @@ int nco_set_net_weights_depth(nco_lattice* lat, int depth, int width, int act, i
         std::memcpy(&buf[net_off_w2b(W)], W2b, sizeof(float) * W * W);
         std::memcpy(&buf[net_off_b2b(W)], b2b, sizeof(float) * W);
     }
-    for (int g = 0; g < NGROUP; ++g)
-        for (int k = 0; k < 27; ++k)
-            for (int h = 0; h < W; ++h)
-                buf[g * 27 * W + G.src[g][k] * W + h] = G.sign[g][k] * W1[k * W + h];
+    std::memcpy(&buf[0], W1, sizeof(float) * 27 * W);
     std::memcpy(&buf[net_off_b1(W)], b1, sizeof(float) * W);
     std::memcpy(&buf[net_off_w2(W)], W2, sizeof(float) * W * W);
     std::memcpy(&buf[net_off_b2(W)], b2, sizeof(float) * W);
@@ -684,7 +688,7 @@ int nco_set_net_weights_depth(nco_lattice* lat, int depth, int width, int act, i
         HIP_TRY(hipMemcpyAsync(lat->d_gsrc, gs, sizeof(gs), hipMemcpyHostToDevice, lat->stream));
         HIP_TRY(hipStreamSynchronize(lat->stream));
     }
-    if (mlp_prec != NCO_MLP_F32) {
+    if (lat->storage != NCO_F64) {
         const size_t nf = mfma_lane_table_floats(), ni = mfma_group_table_ints();
         std::vector<char> tab(sizeof(float) * nf + sizeof(int) * ni);
         // Narrower networks run zero-padded to width 32: a padded hidden unit
@@ -693,31 +697,21 @@ int nco_set_net_weights_depth(nco_lattice* lat, int depth, int width, int act, i
         std::vector<float> padded;
         const float* p32 = params;
         if (W < 32) {
-            const int P = 32;
-            padded.assign(n_params_for(P), 0.0f);
-            float* q = padded.data();
-            for (int k = 0; k < 27; ++k)
-                for (int h = 0; h < W; ++h) q[k * P + h] = W1[k * W + h];
-            q += 27 * P;
-            for (int h = 0; h < W; ++h) q[h] = b1[h];
-            q += P;
-            for (int i = 0; i < W; ++i)
-                for (int o = 0; o < W; ++o) q[i * P + o] = W2[i * W + o];
-            q += P * P;
-            for (int o = 0; o < W; ++o) q[o] = b2[o];
-            q += P;
-            for (int i = 0; i < W; ++i)
-                for (int n = 0; n < 4; ++n) q[i * 4 + n] = W3[i * 4 + n];
-            q += 4 * P;
-            for (int n = 0; n < 4; ++n) q[n] = b3[n];
+            padded = pad_params(params, W, 2, 32);
             p32 = padded.data();
         }
-        mfma_prepare_tables(p32, act, mlp_prec, G.src, reinterpret_cast<float*>(tab.data()),
-                            reinterpret_cast<int*>(tab.data() + sizeof(float) * nf), depth);
-        if (!lat->mfma_tab) HIP_TRY(hipMalloc(&lat->mfma_tab, tab.size()));
-        HIP_TRY(hipMemcpyAsync(lat->mfma_tab, tab.data(), tab.size(), hipMemcpyHostToDevice, lat->stream));
-        HIP_TRY(hipStreamSynchronize(lat->stream));
-        if (W == 32) {
+        auto upload = [&](int prec, void** dst) -> int {
+            mfma_prepare_tables(p32, act, prec, G.src, reinterpret_cast<float*>(tab.data()),
+                                reinterpret_cast<int*>(tab.data() + sizeof(float) * nf), depth);
+            if (!*dst) HIP_TRY(hipMalloc(dst, tab.size()));
+            HIP_TRY(hipMemcpyAsync(*dst, tab.data(), tab.size(), hipMemcpyHostToDevice, lat->stream));
+            HIP_TRY(hipStreamSynchronize(lat->stream));
+            return NCO_OK;
+        };
+        if (int rc = upload(NCO_MLP_F32, &lat->full_tab)) return rc;
+        if (mlp_prec != NCO_MLP_F32)
+            if (int rc = upload(mlp_prec, &lat->mfma_tab)) return rc;
+        if (W == 32 && mlp_prec != NCO_MLP_F32) {
             // Reverse mode on the matrix cores, float32 (also for a bf16 or
             // split network), whose table holds the float32 forward weights.
             std::vector<char> at(mfma_adjoint_table_bytes(depth));
@@ -912,8 +906,9 @@ int nco_batch_step(nco_lattice** lats, int n, const int* nsteps) {
                 d.fout = lat->f[1 - lat->cur];
                 d.a = step_args_at(lat, lat->force_t);
                 if (int rc = force_field(lat, d.a, st)) return rc;
-                d.lane_tab = lat->op == NCO_OP_NCO ? mfma_lane_tab(lat) : nullptr;
-                d.gtab = lat->op == NCO_OP_NCO ? mfma_group_tab(lat) : nullptr;
+                const char* tab = lat->op == NCO_OP_NCO ? static_cast<const char*>(lat->mfma_tab) : nullptr;
+                d.lane_tab = reinterpret_cast<const float*>(tab);
+                d.gtab = tab ? reinterpret_cast<const int*>(tab + sizeof(float) * mfma_lane_table_floats()) : nullptr;
                 g.prefix[g.count + 1] = g.prefix[g.count] + (lat->n + 255) / 256;
                 ++g.count;
                 lat->cur = 1 - lat->cur;
@@ -1404,13 +1399,11 @@ int nco_read_rates(nco_lattice* lat, double* omega) {
     if (int rc = set_device(lat)) return rc;
     if (int rc = ensure_staging(lat, 4)) return rc;
     const StepArgs a = step_args(lat);
-    if (use_mfma(lat))
-        HIP_TRY(launch_nco_mfma(lat->storage, lat->mlp_prec, lat->f[lat->cur], nullptr, a, mfma_lane_tab(lat),
-                                mfma_group_tab(lat), lat->staging, lat->stream));
-    else if (lat->storage == NCO_F64)
+    if (lat->storage == NCO_F64)
         HIP_TRY(launch_nco_f64(lat->f[lat->cur], nullptr, a, lat->f64_tab, lat->staging, lat->stream));
     else
-        HIP_TRY(launch_rates(lat->storage, lat->f[lat->cur], lat->staging, a, lat->stream));
+        HIP_TRY(launch_net(lat, use_mfma(lat) ? lat->mlp_prec : NCO_MLP_F32, lat->f[lat->cur], nullptr, a,
+                           lat->staging));
     HIP_TRY(hipMemcpyAsync(omega, lat->staging, sizeof(double) * 4 * (size_t)lat->n, hipMemcpyDeviceToHost,
                            lat->stream));
     HIP_TRY(hipStreamSynchronize(lat->stream));

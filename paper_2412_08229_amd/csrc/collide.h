@@ -10,11 +10,9 @@
 //  * Kupershtokh exact-difference source (Sec. II.A): f^eq(rho, u + F/rho) -
 //    f^eq(rho, u) only changes the first- and second-order equilibrium
 //    moments, by sqrt(3) F_a and 3 (j_a F_b + j_b F_a + F_a F_b) / rho.
-//  * The invariant network of Eq. gconv_m evaluated per node on the vector
-//    units: tilde tau = (1/48) sum_g Phi(m^(g)), with the group action folded
-//    into 48 stacked first-layer matrices (m^(g) = M Pi_g f is a signed
-//    permutation of m, so W1^T m^(g) = W1_g^T m).  The last layer is affine,
-//    so the mean of the outputs equals W3^T mean_g(h2_g) + b3.
+//  * The invariant network of Eq. gconv_m, tilde tau = (1/48) sum_g Phi(m^(g)),
+//    gives the omega_n of the learned operator; it runs on the matrix cores
+//    (nco_mfma.hip, nco_f64.hip).
 #pragma once
 
 #include "d3q27.h"
@@ -22,15 +20,18 @@
 namespace nco {
 
 enum Op { OP_BGK = 0, OP_MRT = 1, OP_NCO = 2, OP_NONE = 3 };
-enum Act { ACT_TANH = 0, ACT_RELU = 1 };
+// In the kernels of the float32 network (net_f32.h): ACT_TANH_FULL is tanh
+// itself to the last place or two where ACT_TANH evaluates a folded form of
+// it; the HALF forms are for networks of at most 16 hidden units.
+enum Act { ACT_TANH = 0, ACT_RELU = 1, ACT_TANH_FULL = 2, ACT_TANH_HALF = 3, ACT_RELU_HALF = 4 };
 // Matrix-core network arithmetic (values of nco_mlp_prec).
-enum MlpPrec { MLP_PREC_F32 = 1, MLP_PREC_BF16 = 2, MLP_PREC_F32S = 3 };
+enum MlpPrec { MLP_PREC_F32_FULL = 0, MLP_PREC_F32 = 1, MLP_PREC_BF16 = 2, MLP_PREC_F32S = 3 };
 
 constexpr int NGROUP = 48;
 
-// Layout of the device network buffer for width W (floats):
-// W1 stacked per group [48][27][W], b1[W], W2[W][W], b2[W], W3[W][4], b3[4].
-__host__ __device__ constexpr int net_off_b1(int W) { return NGROUP * 27 * W; }
+// Layout of the vector-unit adjoint's network buffer for width W (floats):
+// W1[27][W], b1[W], W2[W][W], b2[W], W3[W][4], b3[4].
+__host__ __device__ constexpr int net_off_b1(int W) { return 27 * W; }
 __host__ __device__ constexpr int net_off_w2(int W) { return net_off_b1(W) + W; }
 __host__ __device__ constexpr int net_off_b2(int W) { return net_off_w2(W) + W * W; }
 __host__ __device__ constexpr int net_off_w3(int W) { return net_off_b2(W) + W; }
@@ -43,85 +44,11 @@ __host__ __device__ constexpr int net_floats_depth(int W, int depth) {
     return depth == 3 ? net_off_b2b(W) + W : net_floats(W);
 }
 
-template <int ACT, typename R>
-__device__ __forceinline__ R activate(R x) {
-    if constexpr (ACT == ACT_RELU) {
-        return x > R(0) ? x : R(0);
-    } else {
-        return tanh(x);
-    }
-}
-
 // Rate squashing of Sec. II.B: tau = 1/(2 (1 + e^t)) + 1/2, omega = 1/tau.
 template <typename R>
 __device__ __forceinline__ R squash_rate(R t) {
     const R tau = R(0.5) + R(0.5) / (R(1) + exp(t));
     return R(1) / tau;
-}
-
-// omega_3..omega_6 of one node from its moments (tensor order), with
-// DEPTH = 2 or 3 hidden layers.
-template <typename R, int W, int ACT, int DEPTH = 2>
-__device__ __forceinline__ void net_rates(const R (&m)[Q], const float* __restrict__ net,
-                                          R (&omega)[4]) {
-    R x[Q];
-#pragma unroll
-    for (int k = 0; k < Q; ++k) x[k] = m[row_tensor(k)];
-    const float* __restrict__ b1 = net + net_off_b1(W);
-    const float* __restrict__ w2 = net + net_off_w2(W);
-    const float* __restrict__ b2 = net + net_off_b2(W);
-    const float* __restrict__ w3 = net + net_off_w3(W);
-    const float* __restrict__ b3 = net + net_off_b3(W);
-    R acc[W];
-#pragma unroll
-    for (int o = 0; o < W; ++o) acc[o] = R(0);
-#pragma unroll 1
-    for (int g = 0; g < NGROUP; ++g) {
-        const float* __restrict__ wg = net + g * (27 * W);
-        R h[W];
-#pragma unroll
-        for (int j = 0; j < W; ++j) h[j] = (R)b1[j];
-#pragma unroll
-        for (int k = 0; k < Q; ++k)
-#pragma unroll
-            for (int j = 0; j < W; ++j) h[j] = fma((R)wg[k * W + j], x[k], h[j]);
-#pragma unroll
-        for (int j = 0; j < W; ++j) h[j] = activate<ACT>(h[j]);
-        if constexpr (DEPTH == 2) {
-#pragma unroll
-            for (int o = 0; o < W; ++o) {
-                R s = (R)b2[o];
-#pragma unroll
-                for (int j = 0; j < W; ++j) s = fma((R)w2[j * W + o], h[j], s);
-                acc[o] += activate<ACT>(s);
-            }
-        } else {
-            const float* __restrict__ w2b = net + net_off_w2b(W);
-            const float* __restrict__ b2b = net + net_off_b2b(W);
-            R h2[W];
-#pragma unroll
-            for (int o = 0; o < W; ++o) {
-                R s = (R)b2[o];
-#pragma unroll
-                for (int j = 0; j < W; ++j) s = fma((R)w2[j * W + o], h[j], s);
-                h2[o] = activate<ACT>(s);
-            }
-#pragma unroll
-            for (int o = 0; o < W; ++o) {
-                R s = (R)b2b[o];
-#pragma unroll
-                for (int j = 0; j < W; ++j) s = fma((R)w2b[j * W + o], h2[j], s);
-                acc[o] += activate<ACT>(s);
-            }
-        }
-    }
-#pragma unroll
-    for (int n = 0; n < 4; ++n) {
-        R t = R(0);
-#pragma unroll
-        for (int o = 0; o < W; ++o) t = fma((R)w3[o * 4 + n], acc[o], t);
-        omega[n] = squash_rate(t * R(1.0 / NGROUP) + (R)b3[n]);
-    }
 }
 
 // Second-order equilibrium moment of tensor index t (order 2) from the

@@ -18,7 +18,7 @@ struct StepArgs {
     int op;                  // OP_BGK / OP_MRT / OP_NCO
     int domain;              // DOMAIN_PERIODIC / DOMAIN_TGV_OCTANT (nx = ny = nz)
     int width, act;          // network shape (OP_NCO)
-    int depth;               // hidden layers: 2, or 3 (vector-unit network, width 32)
+    int depth;               // hidden layers: 2, or 3 (at width 32)
     double omega_nu;         // 1 / tau
     float omega_nu_f;
     double omega_high[4];    // fixed rates of orders 3..6 (OP_MRT)
@@ -138,7 +138,6 @@ hipError_t launch_restrict(int fine_storage, const void* fine, int fnx, int fny,
                            void* coarse, int cnx, int cny, int cnz, int r, double factor, hipStream_t st);
 // BGK and fixed-rate lattices (op in a.op of every member, same storage).
 hipError_t launch_step_grouped(int storage, int op, const LaunchGroup& g, hipStream_t st);
-hipError_t launch_rates(int storage, const void* fin, double* omega, const StepArgs& a, hipStream_t st);
 // f = f^eq(rho, u); rho == nullptr: rho = 1; u == nullptr: u = 0.
 hipError_t launch_init_equilibrium(int storage, void* f, const double* rho, const double* u, int n,
                                    hipStream_t st);

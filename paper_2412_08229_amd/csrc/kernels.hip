@@ -23,8 +23,8 @@ template <> __device__ __forceinline__ float pick<float>(float f, double) { retu
 template <> __device__ __forceinline__ double pick<double>(float, double d) { return d; }
 
 // Collision of one node in place (plus the Kupershtokh source of force F when
-// FORCED); OP and W/ACT select the operator.
-template <typename R, int OP, int W, int ACT, bool FORCED, int DEPTH = 2>
+// FORCED).
+template <typename R, int OP, bool FORCED>
 __device__ __forceinline__ void collide_node(R (&f)[Q], const StepArgs& a, R Fx, R Fy, R Fz) {
     const R omega_nu = pick<R>(a.omega_nu_f, a.omega_nu);
     if constexpr (OP == OP_BGK) {
@@ -33,12 +33,8 @@ __device__ __forceinline__ void collide_node(R (&f)[Q], const StepArgs& a, R Fx,
         R m[Q];
         to_moments(f, m);
         R omega[4];
-        if constexpr (OP == OP_NCO) {
-            net_rates<R, W, ACT, DEPTH>(m, a.net, omega);
-        } else {
 #pragma unroll
-            for (int n = 0; n < 4; ++n) omega[n] = pick<R>(a.omega_high_f[n], a.omega_high[n]);
-        }
+        for (int n = 0; n < 4; ++n) omega[n] = pick<R>(a.omega_high_f[n], a.omega_high[n]);
         R dm[Q], df[Q];
         collision_delta<R, FORCED>(m, omega_nu, omega, Fx, Fy, Fz, dm);
         from_moments(dm, df);
@@ -47,16 +43,16 @@ __device__ __forceinline__ void collide_node(R (&f)[Q], const StepArgs& a, R Fx,
     }
 }
 
-template <int S, int OP, int W, int ACT, int DEPTH = 2>
+template <int S, int OP>
 __device__ __forceinline__ void stream_collide_node(const typename Codec<S>::store_t* __restrict__ fin,
                                                     typename Codec<S>::store_t* __restrict__ fout,
                                                     const StepArgs& a, int idx);
 
-template <int S, int OP, int W, int ACT, int DEPTH = 2>
+template <int S, int OP>
 __global__ __launch_bounds__(256) void k_stream_collide(const typename Codec<S>::store_t* __restrict__ fin,
                                                         typename Codec<S>::store_t* __restrict__ fout,
                                                         StepArgs a) {
-    stream_collide_node<S, OP, W, ACT, DEPTH>(fin, fout, a, blockIdx.x * blockDim.x + threadIdx.x);
+    stream_collide_node<S, OP>(fin, fout, a, blockIdx.x * blockDim.x + threadIdx.x);
 }
 
 // One step of several lattices of the same kind in one dispatch.
@@ -65,11 +61,11 @@ __global__ __launch_bounds__(256) void k_stream_collide_grouped(LaunchGroup g) {
     using T = typename Codec<S>::store_t;
     const int i = group_member(g, blockIdx.x);
     const GroupDesc& d = g.d[i];
-    stream_collide_node<S, OP, 8, ACT_TANH>(static_cast<const T*>(d.fin), static_cast<T*>(d.fout), d.a,
-                                            (blockIdx.x - g.prefix[i]) * blockDim.x + threadIdx.x);
+    stream_collide_node<S, OP>(static_cast<const T*>(d.fin), static_cast<T*>(d.fout), d.a,
+                               (blockIdx.x - g.prefix[i]) * blockDim.x + threadIdx.x);
 }
 
-template <int S, int OP, int W, int ACT, int DEPTH>
+template <int S, int OP>
 __device__ __forceinline__ void stream_collide_node(const typename Codec<S>::store_t* __restrict__ fin,
                                                     typename Codec<S>::store_t* __restrict__ fout,
                                                     const StepArgs& a, int idx) {
@@ -81,9 +77,9 @@ __device__ __forceinline__ void stream_collide_node(const typename Codec<S>::sto
     if (a.n_modes > 0) {
         R Fx, Fy, Fz;
         read_force(a, idx, Fx, Fy, Fz);
-        collide_node<R, OP, W, ACT, true, DEPTH>(f, a, Fx, Fy, Fz);
+        collide_node<R, OP, true>(f, a, Fx, Fy, Fz);
     } else {
-        collide_node<R, OP, W, ACT, false, DEPTH>(f, a, R(0), R(0), R(0));
+        collide_node<R, OP, false>(f, a, R(0), R(0), R(0));
     }
     store_local<S>(fout, a.n, idx, f, a.sr_key);
 }
@@ -117,9 +113,9 @@ __global__ __launch_bounds__(256) void k_stream_collide_inplace(typename Codec<S
     if (a.n_modes > 0) {
         R Fx, Fy, Fz;
         read_force(a, idx, Fx, Fy, Fz);
-        collide_node<R, OP, 8, ACT_TANH, true>(v, a, Fx, Fy, Fz);
+        collide_node<R, OP, true>(v, a, Fx, Fy, Fz);
     } else {
-        collide_node<R, OP, 8, ACT_TANH, false>(v, a, R(0), R(0), R(0));
+        collide_node<R, OP, false>(v, a, R(0), R(0), R(0));
     }
     if constexpr (PHASE == 0) {
         // Destination coordinate for c = -1, 0, +1 is x - 1, x, x + 1.
@@ -169,20 +165,6 @@ __global__ __launch_bounds__(256) void k_stream_only(const typename Codec<S>::st
         const int src = zs[cz_of(i) + 1] + ys[cy_of(i) + 1] + xs[cx_of(i) + 1];
         fout[(size_t)i * a.n + idx] = fin[(size_t)i * a.n + src];
     }
-}
-
-template <int S, int W, int ACT, int DEPTH = 2>
-__global__ __launch_bounds__(256) void k_rates(const typename Codec<S>::store_t* __restrict__ fin,
-                                               double* __restrict__ omega_out, StepArgs a) {
-    using R = typename Codec<S>::real;
-    const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= a.n) return;
-    R f[Q], m[Q], omega[4];
-    load_local<S>(fin, a.n, idx, f);
-    to_moments(f, m);
-    net_rates<R, W, ACT, DEPTH>(m, a.net, omega);
-#pragma unroll
-    for (int k = 0; k < 4; ++k) omega_out[(size_t)k * a.n + idx] = (double)omega[k];
 }
 
 // Fine-to-coarse restriction by acoustic scaling (Sec. "Learning Task"):
@@ -481,55 +463,11 @@ hipError_t launch_step_op(const void* fin, void* fout, const StepArgs& a, hipStr
     using T = typename Codec<S>::store_t;
     const T* in = static_cast<const T*>(fin);
     T* out = static_cast<T*>(fout);
-    if constexpr (OP == OP_NONE) {
+    if constexpr (OP == OP_NONE)
         hipLaunchKernelGGL((k_stream_only<S>), dim3(nblocks(a.n)), dim3(256), 0, st, in, out, a);
-    } else if constexpr (OP != OP_NCO) {
-        hipLaunchKernelGGL((k_stream_collide<S, OP, 8, ACT_TANH>), dim3(nblocks(a.n)), dim3(256), 0, st, in, out, a);
-    } else {
-#define NCO_CASE(WW, AA)                                                                               \
-    if (a.depth == 2 && a.width == WW && a.act == AA) {                                                \
-        hipLaunchKernelGGL((k_stream_collide<S, OP, WW, AA>), dim3(nblocks(a.n)), dim3(256), 0, st, in, \
-                           out, a);                                                                    \
-        return hipGetLastError();                                                                      \
-    }
-        // Depth 3 runs at width 32 (narrower networks are zero-padded).
-        if (a.depth == 3 && a.width == 32) {
-            if (a.act == ACT_TANH)
-                hipLaunchKernelGGL((k_stream_collide<S, OP, 32, ACT_TANH, 3>), dim3(nblocks(a.n)), dim3(256), 0, st,
-                                   in, out, a);
-            else
-                hipLaunchKernelGGL((k_stream_collide<S, OP, 32, ACT_RELU, 3>), dim3(nblocks(a.n)), dim3(256), 0, st,
-                                   in, out, a);
-            return hipGetLastError();
-        }
-        NCO_CASE(8, ACT_TANH) NCO_CASE(16, ACT_TANH) NCO_CASE(20, ACT_TANH) NCO_CASE(32, ACT_TANH)
-        NCO_CASE(8, ACT_RELU) NCO_CASE(16, ACT_RELU) NCO_CASE(20, ACT_RELU) NCO_CASE(32, ACT_RELU)
-#undef NCO_CASE
-        return hipErrorInvalidValue;
-    }
+    else
+        hipLaunchKernelGGL((k_stream_collide<S, OP>), dim3(nblocks(a.n)), dim3(256), 0, st, in, out, a);
     return hipGetLastError();
-}
-
-template <int S>
-hipError_t launch_rates_s(const void* fin, double* out, const StepArgs& a, hipStream_t st) {
-    using T = typename Codec<S>::store_t;
-    const T* in = static_cast<const T*>(fin);
-    if (a.depth == 3 && a.width == 32) {
-        if (a.act == ACT_TANH)
-            hipLaunchKernelGGL((k_rates<S, 32, ACT_TANH, 3>), dim3(nblocks(a.n)), dim3(256), 0, st, in, out, a);
-        else
-            hipLaunchKernelGGL((k_rates<S, 32, ACT_RELU, 3>), dim3(nblocks(a.n)), dim3(256), 0, st, in, out, a);
-        return hipGetLastError();
-    }
-#define RATE_CASE(WW, AA)                                                                            \
-    if (a.depth == 2 && a.width == WW && a.act == AA) {                                                              \
-        hipLaunchKernelGGL((k_rates<S, WW, AA>), dim3(nblocks(a.n)), dim3(256), 0, st, in, out, a); \
-        return hipGetLastError();                                                                    \
-    }
-    RATE_CASE(8, ACT_TANH) RATE_CASE(16, ACT_TANH) RATE_CASE(20, ACT_TANH) RATE_CASE(32, ACT_TANH)
-    RATE_CASE(8, ACT_RELU) RATE_CASE(16, ACT_RELU) RATE_CASE(20, ACT_RELU) RATE_CASE(32, ACT_RELU)
-#undef RATE_CASE
-    return hipErrorInvalidValue;
 }
 
 }  // namespace
@@ -547,12 +485,6 @@ hipError_t launch_step(int storage, const void* fin, void* fout, const StepArgs&
     switch (a.op) {
         case OP_BGK: DISPATCH_STORAGE(storage, return (launch_step_op<SS, OP_BGK>(fin, fout, a, st)))
         case OP_MRT: DISPATCH_STORAGE(storage, return (launch_step_op<SS, OP_MRT>(fin, fout, a, st)))
-        case OP_NCO:
-            // Vector-unit network; float64 lattices run launch_nco_f64.
-            if (storage == ST_F32) return launch_step_op<ST_F32, OP_NCO>(fin, fout, a, st);
-            if (storage == ST_F16) return launch_step_op<ST_F16, OP_NCO>(fin, fout, a, st);
-            if (storage == ST_BF16) return launch_step_op<ST_BF16, OP_NCO>(fin, fout, a, st);
-            return hipErrorInvalidValue;
         case OP_NONE: DISPATCH_STORAGE(storage, return (launch_step_op<SS, OP_NONE>(fin, fout, a, st)))
         default: return hipErrorInvalidValue;
     }
@@ -593,13 +525,6 @@ hipError_t launch_step_grouped(int storage, int op, const LaunchGroup& g, hipStr
             })
         default: return hipErrorInvalidValue;
     }
-}
-
-hipError_t launch_rates(int storage, const void* fin, double* omega, const StepArgs& a, hipStream_t st) {
-    if (storage == ST_F32) return launch_rates_s<ST_F32>(fin, omega, a, st);
-    if (storage == ST_F16) return launch_rates_s<ST_F16>(fin, omega, a, st);
-    if (storage == ST_BF16) return launch_rates_s<ST_BF16>(fin, omega, a, st);
-    return hipErrorInvalidValue;
 }
 
 hipError_t launch_init_equilibrium(int storage, void* f, const double* rho, const double* u, int n,

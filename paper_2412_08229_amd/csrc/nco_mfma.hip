@@ -167,9 +167,10 @@ struct NetF32Regs {
     }
     // Layer 1 of one axis permutation for lane group q of a node tile (mrow:
     // the node's moment row, ge: the permutation's gather slots of the group).
+    template <int ACT>
     __device__ __forceinline__ void layer1(const float* __restrict__ mrow, const int* __restrict__ ge,
                                            f32x4 (&Y)[8][2]) const {
-        layer1_f32([&](int t, int st) { return A1[t][st]; }, [&](int st) { return mrow[ge[st]]; }, Y);
+        layer1_f32<act_tiles(ACT)>([&](int t, int st) { return A1[t][st]; }, [&](int st) { return mrow[ge[st]]; }, Y);
     }
     template <int ACT, int DEPTH, int NS, typename Sink>
     __device__ __forceinline__ void hidden(const f32x4 (&Y)[8][2], Sink&& sink) const {
@@ -224,7 +225,7 @@ __device__ __forceinline__ void network_f32(const float* __restrict__ sm, const 
 #pragma unroll 1
         for (int p = 0; p < 6; ++p) {
             f32x4 Y[8][2];
-            w.layer1(mrow, sg + (p * 4 + q) * GT_STRIDE, Y);
+            w.template layer1<ACT>(mrow, sg + (p * 4 + q) * GT_STRIDE, Y);
             reflections(Y);
             w.template hidden<ACT, DEPTH, 8>(Y, [&](int, const f32x4(&z)[2]) { add_act<ACT>(z, acc); });
         }
@@ -255,7 +256,7 @@ __device__ __forceinline__ void network_f32_psplit(const float* __restrict__ sm,
     {
         const NetF32Regs w(lt);
         f32x4 Y[8][2];
-        w.layer1(sm + c * NODE_STRIDE, sg + ((wave >> 1) * 4 + q) * GT_STRIDE, Y);
+        w.template layer1<ACT>(sm + c * NODE_STRIDE, sg + ((wave >> 1) * 4 + q) * GT_STRIDE, Y);
         reflections_half(Y, wave & 1);
         float* __restrict__ mine = vals + (wave * 4 * 16 + c) * PSPLIT_ROW + 4 * q;
         w.template hidden<ACT, DEPTH, 4>(Y, [&](int s, const f32x4(&z)[2]) {
@@ -807,7 +808,7 @@ void mfma_prepare_tables(const float* params, int act, int prec, const int (*gsr
     const float* b2b = W2b + W * W;
     const float* W3 = depth == 3 ? b2b + W : b2 + W;
     const float* b3 = W3 + 4 * W;
-    const bool th = act == ACT_TANH;
+    const bool th = act == ACT_TANH && prec != MLP_PREC_F32_FULL;
     const float kappa = th ? (float)(2.0 / 0.69314718055994530942) : 1.0f;
     // tanh = 1 - 2 r folded into the consumer of each activation:
     // W2 -> -2 W2, b2 -> b2 + sum_h W2[h][:], W3 -> -2 W3, b3 -> b3 + sum_h W3[h][:]
@@ -916,7 +917,7 @@ void mfma_prepare_tables(const float* params, int act, int prec, const int (*gsr
                     for (int n = 0; n < 4; ++n)
                         lt[LS_W3 + (u * 4 + r) * 4 + n] = fold * W3[(16 * u + 4 * q + r) * 4 + n] / (float)NGROUP;
             for (int n = 0; n < 4; ++n) lt[LS_B3O + n] = b3f[n];
-        } else if (prec == MLP_PREC_F32) {
+        } else if (prec == MLP_PREC_F32 || prec == MLP_PREC_F32_FULL) {
             for (int t = 0; t < 2; ++t)
                 for (int st = 0; st < KSTEPS; ++st) {
                     const int k = slot_row[st][q];
@@ -994,7 +995,7 @@ void mfma_prepare_tables(const float* params, int act, int prec, const int (*gsr
             for (int i = 0; i < GT_STRIDE; ++i) {
                 // Row k placed in this slot; 27 is the constant-1 row, 28 zero.
                 int k = -1;
-                if (prec == MLP_PREC_F32 || (prec == MLP_PREC_F32S && !th)) {
+                if (prec == MLP_PREC_F32 || prec == MLP_PREC_F32_FULL || (prec == MLP_PREC_F32S && !th)) {
                     if (i < KSTEPS) k = slot_row[i][q];
                 } else if (i < 8) {
                     k = 8 * q + i;
@@ -1115,9 +1116,57 @@ hipError_t launch_mfma_prec(int prec, const void* fin, void* fout, const StepArg
     return launch_mfma_kind<S, ACT, RR, MLP_PREC_F32, 2>(kind, fin, fout, a, lane_tab, gtab, omega_out, st);
 }
 
+// The float32 network in full (no folding, tanh itself): steps in twelve-
+// wavefront tiles, one-tile or four-tile wavefronts by size as above (256-node
+// blocks tie with the latter), rates in one shape; half the products where
+// the network has at most 16 hidden units (width 8, 64^3: 0.26
+// against 0.48 ms for tanh, 0.11 against 0.28 for ReLU).
+//
+// It replaces a vector-unit network, one lane per node and its 48 elements in
+// series: width 32, tanh, depth 2 16^3 3.68 ms -> 17 us, 40^3 3.69 -> 0.15 ms,
+// 64^3 11.8 -> 0.59; width 20, ReLU, depth 3 64^3 2.97 -> 0.47; width 8, ReLU
+// 64^3 0.154 -> 0.108 - with the same errors of the rates against float64
+// (root mean square 4.0e-8, largest 1.2e-7; the folded form: 4.2e-8, 1.5e-7).
+template <int S, int ACT, int DD>
+hipError_t launch_full_kind(const void* fin, void* fout, const StepArgs& a, const float* lane_tab, const int* gtab,
+                            double* omega_out, hipStream_t st) {
+    using T = typename Codec<S>::store_t;
+    const T* in = static_cast<const T*>(fin);
+    T* out = static_cast<T*>(fout);
+    const dim3 grid((a.n + 63) / 64);
+    if (omega_out)
+        hipLaunchKernelGGL((k_nco_mfma<S, ACT, true, MLP_PREC_F32, 64, DD, 1>), grid, dim3(mfma_block_threads(64, 1)),
+                           0, st, in, out, a, lane_tab, gtab, omega_out);
+    else if (a.n <= PSPLIT_MAX_NODES)
+        hipLaunchKernelGGL((k_nco_mfma<S, ACT, false, MLP_PREC_F32, 16, DD, 0, true>), dim3((a.n + 15) / 16),
+                           dim3(mfma_block_threads(16, 0)), 0, st, in, out, a, lane_tab, gtab, omega_out);
+    else if (mfma_block_kind(a.n) == MFMA_BLOCK_64_TILE)
+        hipLaunchKernelGGL((k_nco_mfma<S, ACT, false, MLP_PREC_F32, 64, DD, 1, true>), grid,
+                           dim3(mfma_block_threads(64, 1)), 0, st, in, out, a, lane_tab, gtab, omega_out);
+    else
+        hipLaunchKernelGGL((k_nco_mfma<S, ACT, false, MLP_PREC_F32, 64, DD, 4, true>), grid,
+                           dim3(mfma_block_threads(64, 4)), 0, st, in, out, a, lane_tab, gtab, omega_out);
+    return hipGetLastError();
+}
+
+template <int S>
+hipError_t launch_full(const void* fin, void* fout, const StepArgs& a, const float* lane_tab, const int* gtab,
+                       double* omega_out, hipStream_t st) {
+    const bool th = a.act == ACT_TANH;
+    if (a.depth == 3)
+        return th ? launch_full_kind<S, ACT_TANH_FULL, 3>(fin, fout, a, lane_tab, gtab, omega_out, st)
+                  : launch_full_kind<S, ACT_RELU, 3>(fin, fout, a, lane_tab, gtab, omega_out, st);
+    if (a.width <= 16)
+        return th ? launch_full_kind<S, ACT_TANH_HALF, 2>(fin, fout, a, lane_tab, gtab, omega_out, st)
+                  : launch_full_kind<S, ACT_RELU_HALF, 2>(fin, fout, a, lane_tab, gtab, omega_out, st);
+    return th ? launch_full_kind<S, ACT_TANH_FULL, 2>(fin, fout, a, lane_tab, gtab, omega_out, st)
+              : launch_full_kind<S, ACT_RELU, 2>(fin, fout, a, lane_tab, gtab, omega_out, st);
+}
+
 template <int S>
 hipError_t launch_mfma_storage(int prec, const void* fin, void* fout, const StepArgs& a, const float* lane_tab,
                                const int* gtab, double* omega_out, hipStream_t st) {
+    if (prec == MLP_PREC_F32_FULL) return launch_full<S>(fin, fout, a, lane_tab, gtab, omega_out, st);
     if (omega_out)
         return a.act == ACT_TANH ? launch_mfma_prec<S, ACT_TANH, true>(prec, fin, fout, a, lane_tab, gtab, omega_out, st)
                                  : launch_mfma_prec<S, ACT_RELU, true>(prec, fin, fout, a, lane_tab, gtab, omega_out, st);

@@ -43,10 +43,31 @@ constexpr int LT_B2B = 96;          // [v 2][r 4]      b2b as accumulator init (
 // is folded into the next layer's weights and bias on the host (and into W3,
 // b3 for the group sum), which leaves exp2, add and reciprocal per value.  r
 // saturates correctly (2^+inf = inf gives 0).
+//
+// ACT_TANH_FULL (the float32 network that is not folded): tanh within 1.3
+// units of the last place plus the hardware exp2's and reciprocal's, against
+// the folded form's absolute 1e-7.  |x| < 0.9: x + x s P(s), s = x^2, P the
+// degree-5 least-maximum fit of (tanh(x) / x - 1) / s (1.6e-8 relative);
+// above, 1 - 2 / (1 + e^(2 |x|)) with x's sign.  Both sides are evaluated:
+// 22 issue slots, two of the instructions at quarter rate.
+// The HALF forms leave out the hidden units 16 .. 31 (zero padding): products,
+// activations and sums that add exact zeros.
+constexpr int act_tiles(int act) { return act == ACT_TANH_HALF || act == ACT_RELU_HALF ? 1 : 2; }
+
 template <int ACT>
 __device__ __forceinline__ float act_scaled(float x) {
-    if constexpr (ACT == ACT_RELU) {
+    if constexpr (ACT == ACT_RELU || ACT == ACT_RELU_HALF) {
         return fmaxf(x, 0.0f);
+    } else if constexpr (ACT == ACT_TANH_FULL || ACT == ACT_TANH_HALF) {
+        const float a = fabsf(x), s = x * x;
+        float p = fmaf(1.30395428e-3f, s, -6.86004246e-3f);
+        p = fmaf(p, s, 2.09041145e-2f);
+        p = fmaf(p, s, -5.37214838e-2f);
+        p = fmaf(p, s, 1.33303598e-1f);
+        p = fmaf(p, s, -3.33332121e-1f);
+        const float e = __builtin_amdgcn_exp2f(a * (float)(2.0 / 0.69314718055994530942));
+        const float big = copysignf(fmaf(-2.0f, __builtin_amdgcn_rcpf(1.0f + e), 1.0f), x);
+        return a < 0.9f ? fmaf(p * s, x, x) : big;
     } else {
         return __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(x));
     }
@@ -60,7 +81,8 @@ __device__ __forceinline__ f32x4 mfma4(float a, float b, f32x4 c) {
 // over 10 K-steps (A1(t, st): W1's A operand, b(st): the moment operand), and
 // their Walsh-Hadamard transform over the class index, after which Y[s][t] is
 // the pre-activation of reflection pattern s (hidden rows 16 t + 4 q + r).
-template <typename A, typename B>
+// NT: 16-row tiles of hidden units (Y[.][1] = 0 with one).
+template <int NT = 2, typename A, typename B>
 __device__ __forceinline__ void layer1_f32(A&& A1, B&& b, f32x4 (&Y)[8][2]) {
     // Moment operand of this permutation, one K-step per register.
     float x[KSTEPS];
@@ -74,7 +96,7 @@ __device__ __forceinline__ void layer1_f32(A&& A1, B&& b, f32x4 (&Y)[8][2]) {
 #pragma unroll
     for (int st = 0; st < KSTEPS; ++st)
 #pragma unroll
-        for (int t = 0; t < 2; ++t) Y[step_class(st)][t] = mfma4(A1(t, st), x[st], Y[step_class(st)][t]);
+        for (int t = 0; t < NT; ++t) Y[step_class(st)][t] = mfma4(A1(t, st), x[st], Y[step_class(st)][t]);
 }
 
 __device__ __forceinline__ void reflections(f32x4 (&Y)[8][2]) {
@@ -115,14 +137,14 @@ __device__ __forceinline__ void reflections_half(f32x4 (&Y)[8][2], int half) {
 }
 
 // One hidden-to-hidden layer, c[u] += A(u, t, r) h[t][r] over the 8 K-steps.
-template <typename A>
+template <int NT = 2, typename A>
 __device__ __forceinline__ void hidden_f32(A&& A2, const f32x4 (&h)[2], f32x4 (&c)[2]) {
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
+    for (int t = 0; t < NT; ++t)
 #pragma unroll
         for (int r = 0; r < 4; ++r)
 #pragma unroll
-            for (int u = 0; u < 2; ++u) c[u] = mfma4(A2(u, t, r), h[t][r], c[u]);
+            for (int u = 0; u < NT; ++u) c[u] = mfma4(A2(u, t, r), h[t][r], c[u]);
 }
 
 template <int ACT>
@@ -130,7 +152,7 @@ __device__ __forceinline__ void act_f32(const f32x4 (&z)[2], f32x4 (&h)[2]) {
 #pragma unroll
     for (int t = 0; t < 2; ++t)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) h[t][r] = act_scaled<ACT>(z[t][r]);
+        for (int r = 0; r < 4; ++r) h[t][r] = t < act_tiles(ACT) ? act_scaled<ACT>(z[t][r]) : 0.0f;
 }
 
 // Hides a lane's place in a weight table from the compiler, so that weights
@@ -155,9 +177,9 @@ __device__ __forceinline__ void hidden_reflections(A&& A2, const f32x4 (&B2)[2],
             f32x4 h[2], c[2] = {B2[0], B2[1]}, c3[2] = {B2b[0], B2b[1]};
             fresh();
             act_f32<ACT>(Y[s], h);
-            hidden_f32(A2, h, c);
+            hidden_f32<act_tiles(ACT)>(A2, h, c);
             act_f32<ACT>(c, h);
-            hidden_f32(A2b, h, c3);
+            hidden_f32<act_tiles(ACT)>(A2b, h, c3);
             sink(s, c3);
         }
         return;
@@ -167,7 +189,7 @@ __device__ __forceinline__ void hidden_reflections(A&& A2, const f32x4 (&B2)[2],
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
         f32x4 c[2] = {B2[0], B2[1]};
-        hidden_f32(A2, h, c);
+        hidden_f32<act_tiles(ACT)>(A2, h, c);
         if (s > 0) sink(s - 1, prev);
         if (s < NS - 1) act_f32<ACT>(Y[s + 1], h);
         prev[0] = c[0];
@@ -181,7 +203,7 @@ __device__ __forceinline__ void hidden_reflections(A&& A2, const f32x4 (&B2)[2],
 template <int ACT>
 __device__ __forceinline__ void add_act(const f32x4 (&z)[2], f32x4 (&acc)[2]) {
 #pragma unroll
-    for (int u = 0; u < 2; ++u)
+    for (int u = 0; u < act_tiles(ACT); ++u)
 #pragma unroll
         for (int r = 0; r < 4; ++r) acc[u][r] += act_scaled<ACT>(z[u][r]);
 }
