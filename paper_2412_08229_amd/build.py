@@ -13,7 +13,8 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(ROOT, "_build", "obj")
 LIB = os.path.join(HERE, "libnco.so")
-SOURCES = ["api.hip", "kernels.hip", "spectrum.hip", "nco_mfma.hip", "nco_f64.hip", "nco_adjoint.hip", "adjoint.hip"]
+SOURCES = ["api.hip", "kernels.hip", "spectrum.hip", "nco_mfma.hip", "nco_mfma_full.hip",
+           "nco_mfma_split.hip", "nco_mfma_bf16.hip", "nco_f64.hip", "nco_adjoint.hip", "adjoint.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",

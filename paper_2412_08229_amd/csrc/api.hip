@@ -360,6 +360,7 @@ StepArgs step_args(const nco_lattice* lat) {
     a.op = lat->op;
     a.domain = lat->domain;
     a.width = lat->width;
+    a.units = lat->user_width;
     a.depth = lat->depth;
     a.act = lat->act;
     a.omega_nu = 1.0 / lat->tau;
@@ -702,7 +703,7 @@ int nco_set_net_weights_depth(nco_lattice* lat, int depth, int width, int act, i
         }
         auto upload = [&](int prec, void** dst) -> int {
             mfma_prepare_tables(p32, act, prec, G.src, reinterpret_cast<float*>(tab.data()),
-                                reinterpret_cast<int*>(tab.data() + sizeof(float) * nf), depth);
+                                reinterpret_cast<int*>(tab.data() + sizeof(float) * nf), depth, width);
             if (!*dst) HIP_TRY(hipMalloc(dst, tab.size()));
             HIP_TRY(hipMemcpyAsync(*dst, tab.data(), tab.size(), hipMemcpyHostToDevice, lat->stream));
             HIP_TRY(hipStreamSynchronize(lat->stream));
@@ -861,7 +862,7 @@ int nco_batch_step(nco_lattice** lats, int n, const int* nsteps) {
     // Kernel kind of each lattice; chunks of up to GROUP_MAX lattices of one
     // kind share a dispatch per step.
     auto kind = [](const nco_lattice* l) {
-        return l->op == NCO_OP_NCO ? 1000 + 100 * l->storage + 10 * l->mlp_prec + l->act : 10 * l->storage + l->op;
+        return l->op == NCO_OP_NCO ? 1000 + 100 * l->storage + 10 * l->mlp_prec + 2 * (l->user_width <= 20) + l->act : 10 * l->storage + l->op;
     };
     std::vector<int> order(n);
     for (int i = 0; i < n; ++i) order[i] = i;
@@ -916,7 +917,7 @@ int nco_batch_step(nco_lattice** lats, int n, const int* nsteps) {
                 ++lat->steps_since_record;
             }
             if (l0->op == NCO_OP_NCO)
-                HIP_TRY(launch_nco_mfma_grouped(l0->storage, l0->mlp_prec, l0->act, g, st));
+                HIP_TRY(launch_nco_mfma_grouped(l0->storage, l0->mlp_prec, l0->act, l0->user_width, g, st));
             else
                 HIP_TRY(launch_step_grouped(l0->storage, l0->op, g, st));
             for (int idx : mem)

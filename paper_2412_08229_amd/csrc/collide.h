@@ -20,10 +20,11 @@
 namespace nco {
 
 enum Op { OP_BGK = 0, OP_MRT = 1, OP_NCO = 2, OP_NONE = 3 };
-// In the kernels of the float32 network (net_f32.h): ACT_TANH_FULL is tanh
+// In the kernels of the float32 network (net_f32.h), ACT_TANH_FULL is tanh
 // itself to the last place or two where ACT_TANH evaluates a folded form of
-// it; the HALF forms are for networks of at most 16 hidden units.
-enum Act { ACT_TANH = 0, ACT_RELU = 1, ACT_TANH_FULL = 2, ACT_TANH_HALF = 3, ACT_RELU_HALF = 4 };
+// it.  In the matrix-core kernels UNITS_20 or UNITS_16 is added for networks of
+// at most 20 or 16 hidden units (act_tail).
+enum Act { ACT_TANH = 0, ACT_RELU = 1, ACT_TANH_FULL = 2, UNITS_20 = 8, UNITS_16 = 16 };
 // Matrix-core network arithmetic (values of nco_mlp_prec).
 enum MlpPrec { MLP_PREC_F32_FULL = 0, MLP_PREC_F32 = 1, MLP_PREC_BF16 = 2, MLP_PREC_F32S = 3 };
 

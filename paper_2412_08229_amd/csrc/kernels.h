@@ -18,6 +18,7 @@ struct StepArgs {
     int op;                  // OP_BGK / OP_MRT / OP_NCO
     int domain;              // DOMAIN_PERIODIC / DOMAIN_TGV_OCTANT (nx = ny = nz)
     int width, act;          // network shape (OP_NCO)
+    int units;               // hidden units as given (width: with the padding it is stored with)
     int depth;               // hidden layers: 2, or 3 (at width 32)
     double omega_nu;         // 1 / tau
     float omega_nu_f;
@@ -152,14 +153,15 @@ hipError_t launch_global_sums(int storage, const void* f, double* partial, doubl
 hipError_t launch_check_state(int storage, const void* f, double* partial, double* sums, int n, double mass0,
                               double tol, int* flag, hipStream_t st);
 
-// Matrix-core network path (nco_mfma.hip), width 32, float32 or bf16 operands.
+// Matrix-core network path (nco_mfma.hip), params at width 32, of whose hidden
+// units all from `units` on are zero padding.
 size_t mfma_lane_table_floats();
 size_t mfma_group_table_ints();
 void mfma_prepare_tables(const float* params, int act, int prec, const int (*gsrc)[27], float* lane_tab,
-                         int* gtab, int depth = 2);
+                         int* gtab, int depth, int units);
 hipError_t launch_nco_mfma(int storage, int prec, const void* fin, void* fout, const StepArgs& a,
                            const float* lane_tab, const int* gtab, double* omega_out, hipStream_t st);
-hipError_t launch_nco_mfma_grouped(int storage, int prec, int act, const LaunchGroup& g, hipStream_t st);
+hipError_t launch_nco_mfma_grouped(int storage, int prec, int act, int units, const LaunchGroup& g, hipStream_t st);
 
 // NCO step of float64 lattices on the float64 matrix cores (nco_f64.hip);
 // omega_out != nullptr: the rates of the state in fin instead of a step.

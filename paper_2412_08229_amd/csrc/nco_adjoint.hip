@@ -572,7 +572,7 @@ void mfma_prepare_adjoint_table(const float* params, int act, int depth, const i
     // forward step's own table (the same roundings).
     std::vector<float> fwd(mfma_lane_table_floats());
     std::vector<int> gather(mfma_group_table_ints());
-    mfma_prepare_tables(params, act, MLP_PREC_F32, gsrc, fwd.data(), gather.data(), depth);
+    mfma_prepare_tables(params, act, MLP_PREC_F32, gsrc, fwd.data(), gather.data(), depth, MW);
     const float slope = act == ACT_TANH ? 4.0f : 1.0f;
     for (int lane = 0; lane < 64; ++lane) {
         const LaneTabT<float> lt(fwd.data(), lane);

@@ -37,6 +37,35 @@ constexpr int LT_B3 = 76;           // [n 4]
 constexpr int LT_A2B = 80;          // [v 2][t 2][r 4] W2b as A operand (depth 3)
 constexpr int LT_B2B = 96;          // [v 2][r 4]      b2b as accumulator init (depth 3)
 
+// Hidden units of a layer lie in two 16-row tiles; a lane (q, c) holds rows
+// 4 q .. 4 q + 3 of each.  Tile 0 is units 0 .. 15 in order.  Tile 1 is units
+// 16 .. 31 in order (tail 4), or, in networks of at most 20 units, unit 16 + j
+// in row 4 j and nothing else (UNITS_20, tail 1), so that every lane holds one
+// of them in its first register: five activations per lane and layer instead
+// of eight, and five K-steps of a float32 product instead of eight (the
+// products of the other rows would add exact zeros).  UNITS_16 (tail 0) leaves
+// tile 1 out.
+constexpr int act_base(int act) { return act & 7; }
+constexpr int act_tail(int act) { return act & UNITS_16 ? 0 : act & UNITS_20 ? 1 : 4; }
+constexpr int act_values(int act, int t) { return t == 0 ? 4 : act_tail(act); }
+// The unit in row 4 q + r of tile t, -1 for none.
+constexpr int tile_unit(bool units20, int t, int q, int r) {
+    return t == 0 ? 4 * q + r : !units20 ? 16 + 4 * q + r : r == 0 ? 16 + q : -1;
+}
+
+// A group sum in the order of tail 4, from lanes in the order of ACT.
+template <int ACT>
+__device__ __forceinline__ void units_in_order(f32x4 (&acc)[2], int q, int c) {
+    if constexpr (act_tail(ACT) == 1) {
+        const float v = acc[1][0];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const float w = __shfl(v, 16 * r + c, 64);
+            acc[1][r] = q == 0 ? w : 0.0f;
+        }
+    }
+}
+
 // Activation as evaluated on the matrix-core paths.  For tanh the
 // pre-activation arrives scaled by kappa = 2 log2(e) and the function returns
 // r = 1 / (1 + 2^(kappa z)), so that tanh(z) = 1 - 2 r; the affine map 1 - 2 r
@@ -50,15 +79,11 @@ constexpr int LT_B2B = 96;          // [v 2][r 4]      b2b as accumulator init (
 // degree-5 least-maximum fit of (tanh(x) / x - 1) / s (1.6e-8 relative);
 // above, 1 - 2 / (1 + e^(2 |x|)) with x's sign.  Both sides are evaluated:
 // 22 issue slots, two of the instructions at quarter rate.
-// The HALF forms leave out the hidden units 16 .. 31 (zero padding): products,
-// activations and sums that add exact zeros.
-constexpr int act_tiles(int act) { return act == ACT_TANH_HALF || act == ACT_RELU_HALF ? 1 : 2; }
-
 template <int ACT>
 __device__ __forceinline__ float act_scaled(float x) {
-    if constexpr (ACT == ACT_RELU || ACT == ACT_RELU_HALF) {
+    if constexpr (act_base(ACT) == ACT_RELU) {
         return fmaxf(x, 0.0f);
-    } else if constexpr (ACT == ACT_TANH_FULL || ACT == ACT_TANH_HALF) {
+    } else if constexpr (act_base(ACT) == ACT_TANH_FULL) {
         const float a = fabsf(x), s = x * x;
         float p = fmaf(1.30395428e-3f, s, -6.86004246e-3f);
         p = fmaf(p, s, 2.09041145e-2f);
@@ -81,8 +106,8 @@ __device__ __forceinline__ f32x4 mfma4(float a, float b, f32x4 c) {
 // over 10 K-steps (A1(t, st): W1's A operand, b(st): the moment operand), and
 // their Walsh-Hadamard transform over the class index, after which Y[s][t] is
 // the pre-activation of reflection pattern s (hidden rows 16 t + 4 q + r).
-// NT: 16-row tiles of hidden units (Y[.][1] = 0 with one).
-template <int NT = 2, typename A, typename B>
+// TAIL as act_tail (0: Y[.][1] = 0).
+template <int TAIL = 4, typename A, typename B>
 __device__ __forceinline__ void layer1_f32(A&& A1, B&& b, f32x4 (&Y)[8][2]) {
     // Moment operand of this permutation, one K-step per register.
     float x[KSTEPS];
@@ -96,7 +121,7 @@ __device__ __forceinline__ void layer1_f32(A&& A1, B&& b, f32x4 (&Y)[8][2]) {
 #pragma unroll
     for (int st = 0; st < KSTEPS; ++st)
 #pragma unroll
-        for (int t = 0; t < NT; ++t) Y[step_class(st)][t] = mfma4(A1(t, st), x[st], Y[step_class(st)][t]);
+        for (int t = 0; t < (TAIL ? 2 : 1); ++t) Y[step_class(st)][t] = mfma4(A1(t, st), x[st], Y[step_class(st)][t]);
 }
 
 __device__ __forceinline__ void reflections(f32x4 (&Y)[8][2]) {
@@ -136,15 +161,15 @@ __device__ __forceinline__ void reflections_half(f32x4 (&Y)[8][2], int half) {
             for (int r = 0; r < 4; ++r) Y[s][t][r] = fmaf(sign, Y[4 + s][t][r], Y[s][t][r]);
 }
 
-// One hidden-to-hidden layer, c[u] += A(u, t, r) h[t][r] over the 8 K-steps.
-template <int NT = 2, typename A>
+// One hidden-to-hidden layer, c[u] += A(u, t, r) h[t][r] over its K-steps.
+template <int TAIL = 4, typename A>
 __device__ __forceinline__ void hidden_f32(A&& A2, const f32x4 (&h)[2], f32x4 (&c)[2]) {
 #pragma unroll
-    for (int t = 0; t < NT; ++t)
+    for (int t = 0; t < 2; ++t)
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
+        for (int r = 0; r < (t == 0 ? 4 : TAIL); ++r)
 #pragma unroll
-            for (int u = 0; u < NT; ++u) c[u] = mfma4(A2(u, t, r), h[t][r], c[u]);
+            for (int u = 0; u < (TAIL ? 2 : 1); ++u) c[u] = mfma4(A2(u, t, r), h[t][r], c[u]);
 }
 
 template <int ACT>
@@ -152,7 +177,7 @@ __device__ __forceinline__ void act_f32(const f32x4 (&z)[2], f32x4 (&h)[2]) {
 #pragma unroll
     for (int t = 0; t < 2; ++t)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) h[t][r] = t < act_tiles(ACT) ? act_scaled<ACT>(z[t][r]) : 0.0f;
+        for (int r = 0; r < 4; ++r) h[t][r] = r < act_values(ACT, t) ? act_scaled<ACT>(z[t][r]) : 0.0f;
 }
 
 // Hides a lane's place in a weight table from the compiler, so that weights
@@ -177,9 +202,9 @@ __device__ __forceinline__ void hidden_reflections(A&& A2, const f32x4 (&B2)[2],
             f32x4 h[2], c[2] = {B2[0], B2[1]}, c3[2] = {B2b[0], B2b[1]};
             fresh();
             act_f32<ACT>(Y[s], h);
-            hidden_f32<act_tiles(ACT)>(A2, h, c);
+            hidden_f32<act_tail(ACT)>(A2, h, c);
             act_f32<ACT>(c, h);
-            hidden_f32<act_tiles(ACT)>(A2b, h, c3);
+            hidden_f32<act_tail(ACT)>(A2b, h, c3);
             sink(s, c3);
         }
         return;
@@ -189,7 +214,7 @@ __device__ __forceinline__ void hidden_reflections(A&& A2, const f32x4 (&B2)[2],
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
         f32x4 c[2] = {B2[0], B2[1]};
-        hidden_f32<act_tiles(ACT)>(A2, h, c);
+        hidden_f32<act_tail(ACT)>(A2, h, c);
         if (s > 0) sink(s - 1, prev);
         if (s < NS - 1) act_f32<ACT>(Y[s + 1], h);
         prev[0] = c[0];
@@ -203,9 +228,9 @@ __device__ __forceinline__ void hidden_reflections(A&& A2, const f32x4 (&B2)[2],
 template <int ACT>
 __device__ __forceinline__ void add_act(const f32x4 (&z)[2], f32x4 (&acc)[2]) {
 #pragma unroll
-    for (int u = 0; u < act_tiles(ACT); ++u)
+    for (int u = 0; u < 2; ++u)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) acc[u][r] += act_scaled<ACT>(z[u][r]);
+        for (int r = 0; r < act_values(ACT, u); ++r) acc[u][r] += act_scaled<ACT>(z[u][r]);
 }
 
 // Output layer on the group sum of one node tile and the rate squashing;
