@@ -296,7 +296,7 @@ __device__ __forceinline__ float act_into_split(float x) {
     if constexpr (act_base(ACT) == ACT_TANH)
         return act_split(x);
     else
-        return fmaxf(x, 0.0f);
+        return relu(x);
 }
 
 // The parts of the moment operand of one axis permutation (K slot 2 w + e
@@ -606,18 +606,20 @@ constexpr int mfma_block_threads(int nodes, int tpw) { return tpw == 0 ? PSPLIT_
 // spilled, depth 3 4 % faster at 128^3 and 8 % on a 16^3 lattice) - but for
 // depth 2 with one tile per wavefront, where the lattice has no third wave to
 // offer a SIMD and the constraint only costs (24^3 30.2 against 32.7 us, 32^3
-// 53.5 against 57.8) -, 4 for the bf16 depth-3 steps (ReLU 132 VGPRs
-// unconstrained, 128 without spills at 4 waves, 2 % faster), no constraint
-// otherwise.
-constexpr int mfma_min_waves(int prec, int depth, int tpw, bool sums) {
+// 53.5 against 57.8) -, 4 for float32 networks of at most 20 units (0-4 spilled;
+// depth 3, ReLU: 24^3 28.6 -> 25.9 us, 96^3 1.035 -> 1.022 ms) and for the bf16
+// depth-3 steps (ReLU 132 VGPRs unconstrained, 128 without spills at 4 waves,
+// 2 % faster), no constraint otherwise.
+constexpr int mfma_min_waves(int act, int prec, int depth, int tpw, bool sums) {
     return prec == MLP_PREC_BF16 && depth == 3 ? 4
+           : prec == MLP_PREC_F32 && sums && act_tail(act) < 4 && tpw != 0 ? 4
            : prec == MLP_PREC_F32S || (prec == MLP_PREC_F32 && sums && (depth == 3 || tpw != 1)) ? 3
                                                                                                    : 1;
 }
 
 template <int S, int ACT, bool RATES, int PREC, int NODES, int DEPTH, int TPW, bool SUMS = false>
 __global__ __launch_bounds__(mfma_block_threads(NODES, TPW))
-__attribute__((amdgpu_waves_per_eu(mfma_min_waves(PREC, DEPTH, TPW, SUMS)))) void k_nco_mfma(
+__attribute__((amdgpu_waves_per_eu(mfma_min_waves(ACT, PREC, DEPTH, TPW, SUMS)))) void k_nco_mfma(
     const typename Codec<S>::store_t* __restrict__ fin, typename Codec<S>::store_t* __restrict__ fout,
     StepArgs a, const float* __restrict__ lane_tab, const int* __restrict__ gtab, double* __restrict__ omega_out) {
     NCO_BLOCK_LDS(NODES)
