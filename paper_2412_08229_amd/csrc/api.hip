@@ -716,7 +716,7 @@ int nco_set_net_weights_depth(nco_lattice* lat, int depth, int width, int act, i
             // Reverse mode on the matrix cores, float32 (also for a bf16 or
             // split network), whose table holds the float32 forward weights.
             std::vector<char> at(mfma_adjoint_table_bytes(depth));
-            mfma_prepare_adjoint_table(params, act, depth, G.src, at.data());
+            mfma_prepare_adjoint_table(params, act, depth, width, G.src, at.data());
             if (!lat->adj_tab) HIP_TRY(hipMalloc(&lat->adj_tab, mfma_adjoint_table_bytes(3)));
             HIP_TRY(hipMemcpyAsync(lat->adj_tab, at.data(), at.size(), hipMemcpyHostToDevice, lat->stream));
             HIP_TRY(hipStreamSynchronize(lat->stream));

@@ -205,7 +205,8 @@ hipError_t launch_force_phase_adjoint(int storage, const void* x, const float* l
 // adjoint_param_count_depth(depth).  With a.net_sums the network values the
 // forward step kept are read instead of computed again.
 size_t mfma_adjoint_table_bytes(int depth);
-void mfma_prepare_adjoint_table(const float* params, int act, int depth, const int (*gsrc)[27], void* table);
+void mfma_prepare_adjoint_table(const float* params, int act, int depth, int units, const int (*gsrc)[27],
+                                void* table);
 int adjoint_mfma_blocks(int n);
 hipError_t launch_adjoint_mfma(int storage, int act, const void* xin, const float* lam_in, float* lam_out,
                                const StepArgs& a, const void* table, double* partial, hipStream_t st);

@@ -48,6 +48,11 @@
 // 105 -> 47 us, 32^3 203 -> 154, 64^3 1390 -> 1078, 96^3 4870 -> 3640 (about
 // 60 TFLOP/s of products, 40 % of what a large float32 product reaches);
 // depth 3 tanh 16^3 348 -> 64, 32^3 1537 -> 233, 64^3 11960 -> 1714.
+//
+// Networks of at most 20 hidden units (depth 3) lie in the tiles as in the
+// forward step (act_tail): five K-steps and activations instead of eight; the
+// products over nodes and per class stay (rows without a unit are zero or not
+// read).  Width 20, ReLU: 16^3 61 -> 52 us, 32^3 219 -> 175, 64^3 1606 -> 1264.
 #include <algorithm>
 #include <cmath>
 #include <vector>
@@ -103,29 +108,32 @@ __device__ __forceinline__ void wave_sync() {
 // act' (without the folded 4) and h from the activation r.
 template <int ACT>
 __device__ __forceinline__ float act_slope(float r) {
-    return ACT == ACT_RELU ? (r > 0.0f ? 1.0f : 0.0f) : fmaf(-r, r, r);
+    return act_base(ACT) == ACT_RELU ? (r > 0.0f ? 1.0f : 0.0f) : fmaf(-r, r, r);
 }
 template <int ACT>
 __device__ __forceinline__ float act_value(float r) {
-    return ACT == ACT_RELU ? r : fmaf(-2.0f, r, 1.0f);
+    return act_base(ACT) == ACT_RELU ? r : fmaf(-2.0f, r, 1.0f);
 }
 
 __device__ __forceinline__ f32x4 ld4(const float* p) { return *reinterpret_cast<const f32x4*>(p); }
 
-// v (hidden 16 t + 4 q + r of node c) to buf [hidden][node].
+// v (hidden 16 t + 4 q + r of node c) to buf [hidden][node]; of the second
+// tile the first TAIL rows of each lane.
+template <int TAIL = 4>
 __device__ __forceinline__ void to_buf(float* __restrict__ buf, int q, int c, const f32x4 (&v)[2]) {
 #pragma unroll
     for (int t = 0; t < 2; ++t)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) buf[(16 * t + 4 * q + r) * TSTRIDE + c] = v[t][r];
+        for (int r = 0; r < (t == 0 ? 4 : TAIL); ++r) buf[(16 * t + 4 * q + r) * TSTRIDE + c] = v[t][r];
 }
 
 // g[x][y] += sum over the tile's nodes of h[16 x + .] dz[16 y + .]^T, through
-// the two buffers.
+// the two buffers (rows that hold no unit give entries that are not read).
+template <int TAIL>
 __device__ __forceinline__ void outer_product(float* __restrict__ buf, int q, int c, const f32x4 (&h)[2],
                                               const f32x4 (&dz)[2], f32x4 (&g)[2][2]) {
-    to_buf(buf, q, c, h);
-    to_buf(buf + TBUF, q, c, dz);
+    to_buf<TAIL>(buf, q, c, h);
+    to_buf<TAIL>(buf + TBUF, q, c, dz);
     wave_sync();
     f32x4 a[2], b[2];
 #pragma unroll
@@ -178,6 +186,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(2)))
 #pragma unroll
         for (int y = 0; y < 2; ++y) gW2[x][y] = gW2b[x][y] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
+    constexpr int TAIL = act_tail(ACT);
     double gW3 = 0.0;                                   // entry tid of W3, then of b3 (tid < 132)
 
     // wl: the lane's place in the weight tables, hidden from the compiler anew
@@ -252,7 +261,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(2)))
                 for (int p = 0; p < 6; ++p) {
                     const int* __restrict__ ge = ti + TI_GE + (p * 4 + q) * GT_STRIDE;
                     f32x4 Y[8][2], b2[2], b2b[2];
-                    layer1_f32(A1, [&](int st) { return sm[ge[st] * NS + node]; }, Y);
+                    layer1_f32<TAIL>(A1, [&](int st) { return sm[ge[st] * NS + node]; }, Y);
                     reflections(Y);
                     rows(TA_B2, b2);
                     if constexpr (DEPTH == 3)
@@ -263,6 +272,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(2)))
                         A2, b2, A2b, b2b, Y, [&]() { fresh_lane(wl); },
                         [&](int, const f32x4(&z)[2]) { add_act<ACT>(z, acc); });
                 }
+                units_in_order<ACT>(acc, q, c);
 #pragma unroll
                 for (int u = 0; u < 2; ++u)
 #pragma unroll
@@ -313,7 +323,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(2)))
                 const float d = sw[n * NS + nd];
                 if (o < 32) {
                     const float acc = sdm[o * NS + nd];
-                    v = fmaf((ACT == ACT_RELU ? acc : (float)NGROUP - 2.0f * acc) * (1.0f / NGROUP), d, v);
+                    v = fmaf((act_base(ACT) == ACT_RELU ? acc : (float)NGROUP - 2.0f * acc) * (1.0f / NGROUP), d, v);
                 } else {
                     v += d;
                 }
@@ -350,7 +360,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(2)))
                 // Pre-activations of the eight reflections; dz1 of reflection
                 // s takes the place of Z[s] once they are used.
                 f32x4 Z[8][2];
-                layer1_f32(A1, [&](int st) { return sm[ge[st] * NS + node]; }, Z);
+                layer1_f32<TAIL>(A1, [&](int st) { return sm[ge[st] * NS + node]; }, Z);
                 reflections(Z);
 #pragma unroll
                 for (int s = 0; s < 8; ++s) {
@@ -358,24 +368,24 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(2)))
                     fresh_lane(wl);
                     act_f32<ACT>(Z[s], r1);
                     rows(TA_B2, h);
-                    hidden_f32(A2, r1, h);
+                    hidden_f32<TAIL>(A2, r1, h);
                     act_f32<ACT>(h, r2);
                     if constexpr (DEPTH == 3) {
                         f32x4 r3[2], v[2];
                         rows(TA_B2B, h);
-                        hidden_f32(A2b, r2, h);
+                        hidden_f32<TAIL>(A2b, r2, h);
                         act_f32<ACT>(h, r3);
 #pragma unroll
                         for (int u = 0; u < 2; ++u)
 #pragma unroll
-                            for (int r = 0; r < 4; ++r) {
+                            for (int r = 0; r < act_values(ACT, u); ++r) {
                                 dz[u][r] = dhl[u][r] * act_slope<ACT>(r3[u][r]);
                                 gb2b[u][r] += dz[u][r];
                                 v[u][r] = act_value<ACT>(r2[u][r]);
                             }
-                        outer_product(buf, q, c, v, dz, gW2b);
+                        outer_product<TAIL>(buf, q, c, v, dz, gW2b);
                         h[0] = h[1] = f32x4{0.f, 0.f, 0.f, 0.f};
-                        hidden_f32(W2bT, dz, h);
+                        hidden_f32<TAIL>(W2bT, dz, h);
                     } else {
                         h[0] = dhl[0];
                         h[1] = dhl[1];
@@ -385,19 +395,20 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(2)))
 #pragma unroll
                         for (int u = 0; u < 2; ++u)
 #pragma unroll
-                            for (int r = 0; r < 4; ++r) {
+                            for (int r = 0; r < act_values(ACT, u); ++r) {
                                 dz[u][r] = h[u][r] * act_slope<ACT>(r2[u][r]);
                                 gb2[u][r] += dz[u][r];
                                 v[u][r] = act_value<ACT>(r1[u][r]);
                             }
-                        outer_product(buf, q, c, v, dz, gW2);
+                        outer_product<TAIL>(buf, q, c, v, dz, gW2);
                     }
                     h[0] = h[1] = f32x4{0.f, 0.f, 0.f, 0.f};
-                    hidden_f32(W2T, dz, h);
+                    hidden_f32<TAIL>(W2T, dz, h);
 #pragma unroll
                     for (int t = 0; t < 2; ++t)
 #pragma unroll
-                        for (int r = 0; r < 4; ++r) Z[s][t][r] = h[t][r] * act_slope<ACT>(r1[t][r]);
+                        for (int r = 0; r < 4; ++r)
+                            Z[s][t][r] = r < act_values(ACT, t) ? h[t][r] * act_slope<ACT>(r1[t][r]) : 0.0f;
                 }
                 reflections(Z);
                 // The row groups of the classes, two at a time.
@@ -495,6 +506,8 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(2)))
         add(OFF_W3 + tid, gW3);
     else if (tid < 132)
         add(OFF_B3 + tid - 128, gW3);
+    // The unit in row j of the 32 rows of a layer, -1 for none.
+    auto unit = [](int j) { return tile_unit(TAIL == 1, j >> 4, (j >> 2) & 3, j & 3); };
     // A hidden-to-hidden layer: lane (q, c) holds [j = 16 x + 4 q + r][o = 16 y + c].
     auto add_layer = [&](const f32x4(&g)[2][2], const f32x4(&gb)[2], int offw, int offb) {
 #pragma unroll
@@ -505,10 +518,12 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(2)))
                 for (int r = 0; r < 4; ++r) red[wave * 1024 + (16 * x + 4 * q + r) * 32 + 16 * y + c] = g[x][y][r];
         __syncthreads();
         for (int e = tid; e < 1024; e += THREADS) {
+            const int j = unit(e >> 5), o = unit(e & 31);
+            if (j < 0 || o < 0) continue;
             float v = red[e];
 #pragma unroll
             for (int w = 1; w < WAVES; ++w) v += red[w * 1024 + e];
-            add(offw + e, (double)v);
+            add(offw + j * 32 + o, (double)v);
         }
         __syncthreads();
 #pragma unroll
@@ -516,10 +531,10 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(2)))
 #pragma unroll
             for (int r = 0; r < 4; ++r) red[(wave * 16 + c) * 32 + 16 * u + 4 * q + r] = gb[u][r];
         __syncthreads();
-        if (tid < 32) {
+        if (tid < 32 && unit(tid) >= 0) {
             float v = 0.0f;
             for (int w = 0; w < 16 * WAVES; ++w) v += red[w * 32 + tid];
-            add(offb + tid, (double)v);
+            add(offb + unit(tid), (double)v);
         }
         __syncthreads();
     };
@@ -533,8 +548,8 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(2)))
             red[wave * (PAIRS * 256) + (k * 8 + (lane >> 5) * 4 + r) * 32 + (lane & 31)] = gW1[k][r];
     __syncthreads();
     for (int e = tid; e < PAIRS * 256; e += THREADS) {
-        const int row = ti[TI_ROW + (e >> 5)], j = e & 31;
-        if (row > 27) continue;
+        const int row = ti[TI_ROW + (e >> 5)], j = unit(e & 31);
+        if (row > 27 || j < 0) continue;
         float v = red[e];
 #pragma unroll
         for (int w = 1; w < WAVES; ++w) v += red[w * (PAIRS * 256) + e];
@@ -557,8 +572,11 @@ int adjoint_groups(int n) { return std::max(1, std::min(4, n / 65536)); }
 
 size_t mfma_adjoint_table_bytes(int depth) { return sizeof(float) * ta_floats(depth) + sizeof(int) * TI_INTS; }
 
-void mfma_prepare_adjoint_table(const float* params, int act, int depth, const int (*gsrc)[27], void* out) {
+void mfma_prepare_adjoint_table(const float* params, int act, int depth, int units, const int (*gsrc)[27],
+                                void* out) {
     const int W = MW;
+    const bool u20 = units <= 20;
+    auto weight = [&](const float* Wl, int j, int o) { return j < 0 || o < 0 ? 0.0f : Wl[j * W + o]; };
     const float* W1 = params;
     const float* b1 = W1 + 27 * W;
     const float* W2 = b1 + W;
@@ -572,7 +590,7 @@ void mfma_prepare_adjoint_table(const float* params, int act, int depth, const i
     // forward step's own table (the same roundings).
     std::vector<float> fwd(mfma_lane_table_floats());
     std::vector<int> gather(mfma_group_table_ints());
-    mfma_prepare_tables(params, act, MLP_PREC_F32, gsrc, fwd.data(), gather.data(), depth, MW);
+    mfma_prepare_tables(params, act, MLP_PREC_F32, gsrc, fwd.data(), gather.data(), depth, units);
     const float slope = act == ACT_TANH ? 4.0f : 1.0f;
     for (int lane = 0; lane < 64; ++lane) {
         const LaneTabT<float> lt(fwd.data(), lane);
@@ -584,11 +602,12 @@ void mfma_prepare_adjoint_table(const float* params, int act, int depth, const i
                 for (int r = 0; r < 4; ++r) {
                     const int e = ((u * 2 + t) * 64 + lane) * 4 + r;
                     tab[TA_A2 + e] = lt[LT_A2 + u * 8 + t * 4 + r];
-                    // Output rows 16 u + c of the transposed layer, inputs 16 t + 4 q + r.
-                    tab[TA_W2T + e] = slope * W2[(16 * u + c) * W + 16 * t + 4 * q + r];
+                    // Row c of tile u of the transposed layer's output, rows 4 q + r of tile t of its input.
+                    const int j = tile_unit(u20, u, c / 4, c % 4), o = tile_unit(u20, t, q, r);
+                    tab[TA_W2T + e] = slope * weight(W2, j, o);
                     if (depth == 3) {
                         tab[TA_A2B + e] = lt[LT_A2B + u * 8 + t * 4 + r];
-                        tab[TA_W2BT + e] = slope * W2b[(16 * u + c) * W + 16 * t + 4 * q + r];
+                        tab[TA_W2BT + e] = slope * weight(W2b, j, o);
                     }
                 }
         if (c == 0)
@@ -602,8 +621,11 @@ void mfma_prepare_adjoint_table(const float* params, int act, int depth, const i
         if (lane == 0)
             for (int n = 0; n < 4; ++n) tab[TA_B3F + n] = lt[LT_B3 + n];
     }
-    for (int o = 0; o < W; ++o)
-        for (int n = 0; n < 4; ++n) tab[TA_W3 + o * 4 + n] = slope * (W3[o * 4 + n] / (float)NGROUP);
+    for (int j = 0; j < W; ++j)
+        for (int n = 0; n < 4; ++n) {
+            const int o = tile_unit(u20, j / 16, j / 4 % 4, j % 4);
+            tab[TA_W3 + j * 4 + n] = o < 0 ? 0.0f : slope * (W3[o * 4 + n] / (float)NGROUP);
+        }
     // Row groups: the rows of each class (the bias row 27 with class 0) in
     // groups of four, 28 where there is none.
     int taken[8] = {0};
@@ -618,7 +640,7 @@ void mfma_prepare_adjoint_table(const float* params, int act, int depth, const i
                 for (int half = 0; half < 2; ++half)
                     for (int j = 0; j < 16; ++j)
                         tab[TA_W1 + (((k * 2 + half) * 2 + g) * 4 + i) * 16 + j] =
-                            row < 27 ? W1[row * W + 16 * half + j] : 0.0f;
+                            row < 27 ? weight(W1, row, tile_unit(u20, half, j / 4, j % 4)) : 0.0f;
                 for (int p = 0; p < 6; ++p)
                     ti[TI_SRC + (p * PAIRS + k) * 8 + g * 4 + i] = row < 27 ? gsrc[8 * p][row] : row;
             }
@@ -648,7 +670,10 @@ hipError_t launch_adjoint_mfma(int storage, int act, const void* xin, const floa
     else ADJN(SS, AA, DD, 4);
 #define ADJN_CASE(SS)                                               \
     case SS:                                                        \
-        if (a.depth == 3) {                                         \
+        if (a.depth == 3 && a.units <= 20) {                        \
+            if (act == ACT_TANH) { ADJN_SHAPE(SS, ACT_TANH + UNITS_20, 3) } \
+            else { ADJN_SHAPE(SS, ACT_RELU + UNITS_20, 3) }         \
+        } else if (a.depth == 3) {                                  \
             if (act == ACT_TANH) { ADJN_SHAPE(SS, ACT_TANH, 3) }    \
             else { ADJN_SHAPE(SS, ACT_RELU, 3) }                    \
         } else {                                                    \

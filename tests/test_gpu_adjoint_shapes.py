@@ -26,7 +26,8 @@ def _gradient(shape, width, depth, act, mlp, T, K, cache=None):
     return params, fs, w, g, df0
 
 
-@pytest.mark.parametrize("width,depth,act", [(32, 2, "tanh"), (32, 2, "relu"), (20, 3, "relu"), (32, 3, "tanh")])
+@pytest.mark.parametrize("width,depth,act", [(32, 2, "tanh"), (32, 2, "relu"), (20, 3, "relu"), (20, 3, "tanh"),
+                                             (32, 3, "tanh")])
 @pytest.mark.parametrize("shape", [(1, 1, 1), (3, 1, 5), (1, 17, 1), (7, 3, 3), (5, 13, 1)])
 def test_gradient_matches_oracle_at_tile_edges(shape, width, depth, act):
     """1, 15, 17, 63 and 65 nodes, 3 steps in segments of 2: float32 sums of
