@@ -1205,8 +1205,7 @@ int backward(nco_lattice* lat, const double* dL_dk, int every, const double* dL_
     }
     for (int b = 0; b < 2; ++b)
         if (!lat->lam[b]) HIP_TRY(hipMalloc(&lat->lam[b], sizeof(float) * nf));
-    // Matrix-core adjoint for matrix-core networks, vector-unit adjoint for
-    // the vector-unit network.
+    // Vector-unit adjoint for NCO_MLP_F32, matrix-core adjoint for the others.
     const bool mfma = lat->mlp_prec != NCO_MLP_F32 && lat->adj_tab;
     const int npar = adjoint_param_count_depth(lat->depth);
     const int nblk = mfma ? adjoint_mfma_blocks(lat->n) : adjoint_blocks(lat->n, lat->depth);
