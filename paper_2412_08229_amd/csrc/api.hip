@@ -197,11 +197,13 @@ struct nco_lattice {
     // largest |k_x| of the modes.
     void* d_force = nullptr;
     int force_kx = 0;
-    int force_ky = 0;             // and the largest |k_y|
     // Velocity-dependent phase (Alvelius' rule): per-mode basis and |A|
-    // [8 per mode], per-step draws phi, psi [steps][modes][2], mode-sum work
-    // space and the coefficients of the current step.
+    // [8 per mode], per-step draws phi, psi [steps][modes][2], the modes as
+    // their sums take them (ModeLayout), mode-sum work space and the
+    // coefficients of the current step.
     bool phase_rule = false;
+    int* d_flist = nullptr;
+    int flist_groups = 0, flist_chunks = 0;
     double* d_fbasis = nullptr;
     double* d_fdraw = nullptr;
     double* d_fpart = nullptr;
@@ -445,8 +447,9 @@ int launch_one(nco_lattice* lat, const void* fin, void* fout, long t, int slot =
         double* fh = slot >= 0 ? phase_slot(lat, slot) : lat->d_fhat_cur;
         // This step's coefficients from the velocity of the state it starts from.
         if (!replay)
-            HIP_TRY(launch_force_phase(lat->storage, fin, lat->n, lat->nx, lat->ny, lat->nz, lat->d_fk,
-                                       lat->n_modes, lat->force_kx, lat->force_ky, lat->d_fpart, lat->d_fbasis,
+            HIP_TRY(launch_force_phase(lat->storage, fin, lat->n, lat->nx, lat->ny, lat->nz, lat->n_modes,
+                                       mode_list(lat->flist_groups, lat->flist_chunks, lat->d_flist),
+                                       lat->d_fpart, lat->d_fbasis,
                                        lat->d_fdraw + (size_t)(t % lat->force_steps) * lat->n_modes * 2, fh,
                                        slot >= 0 ? fh + 6 * lat->n_modes : nullptr, lat->stream));
         a.fhat = fh;
@@ -551,6 +554,7 @@ int nco_lattice_destroy(nco_lattice* lat) {
     if (lat->d_fk) hipFree(lat->d_fk);
     if (lat->d_fhat) hipFree(lat->d_fhat);
     if (lat->d_force) hipFree(lat->d_force);
+    if (lat->d_flist) hipFree(lat->d_flist);
     if (lat->d_fbasis) hipFree(lat->d_fbasis);
     if (lat->d_fdraw) hipFree(lat->d_fdraw);
     if (lat->d_fpart) hipFree(lat->d_fpart);
@@ -946,11 +950,8 @@ int nco_set_forcing_ex(nco_lattice* lat, int n_modes, const int* k, const double
     if (phase_rule && n_modes > 1024) return fail(NCO_E_INVALID, "at most 1024 modes with the phase rule");
     if (n_modes > 0 && lat->domain != NCO_DOMAIN_PERIODIC)
         return fail(NCO_E_UNSUPPORTED, "spectral forcing needs the periodic domain");
-    int kx_max = 0, ky_max = 0;
-    for (int m = 0; m < n_modes; ++m) {
-        kx_max = std::max(kx_max, std::abs(k[3 * m]));
-        ky_max = std::max(ky_max, std::abs(k[3 * m + 1]));
-    }
+    int kx_max = 0;
+    for (int m = 0; m < n_modes; ++m) kx_max = std::max(kx_max, std::abs(k[3 * m]));
     if (kx_max > FORCE_KX_MAX)
         return fail(NCO_E_UNSUPPORTED, "forced wavevectors need |k_x| <= %d (got %d)", FORCE_KX_MAX, kx_max);
     if (int rc = set_device(lat)) return rc;
@@ -967,6 +968,8 @@ int nco_set_forcing_ex(nco_lattice* lat, int n_modes, const int* k, const double
         if (*b) HIP_TRY(hipFree(*b));
         *b = nullptr;
     }
+    if (lat->d_flist) HIP_TRY(hipFree(lat->d_flist));
+    lat->d_flist = nullptr;
     lat->phist_cap = 0;
     lat->phase_rule = false;
     lat->rec_steps = -1;
@@ -1014,11 +1017,11 @@ int nco_set_forcing_ex(nco_lattice* lat, int n_modes, const int* k, const double
     }
     HIP_TRY(hipMalloc(&lat->d_force, 3 * (size_t)lat->n * (lat->storage == NCO_F64 ? sizeof(double) : sizeof(float))));
     lat->force_kx = kx_max;
-    lat->force_ky = ky_max;
     HIP_TRY(hipMalloc(&lat->d_fk, sizeof(int) * 3 * n_modes));
     HIP_TRY(hipMalloc(&lat->d_fhat, sizeof(double) * fh.size()));
     HIP_TRY(hipMemcpyAsync(lat->d_fk, k, sizeof(int) * 3 * n_modes, hipMemcpyHostToDevice, lat->stream));
     HIP_TRY(hipMemcpyAsync(lat->d_fhat, fh.data(), sizeof(double) * fh.size(), hipMemcpyHostToDevice, lat->stream));
+    const ModeLayout layout(k, phase_rule ? n_modes : 0, lat->ny);
     if (phase_rule) {
         // phi, psi of every step and mode (the theta1 draws are not used).
         std::vector<double> dr((size_t)n_steps * n_modes * 2);
@@ -1032,6 +1035,11 @@ int nco_set_forcing_ex(nco_lattice* lat, int n_modes, const int* k, const double
                                               mode_partial_blocks(lat->nx, lat->ny, lat->nz)));
         HIP_TRY(hipMalloc(&lat->d_fhat_cur, sizeof(double) * 6 * (size_t)n_modes));
         HIP_TRY(hipMalloc(&lat->d_fduhat, sizeof(double) * 6 * (size_t)n_modes));
+        HIP_TRY(hipMalloc(&lat->d_flist, sizeof(int) * layout.ints.size()));
+        lat->flist_groups = layout.groups;
+        lat->flist_chunks = layout.chunks;
+        HIP_TRY(hipMemcpyAsync(lat->d_flist, layout.ints.data(), sizeof(int) * layout.ints.size(),
+                               hipMemcpyHostToDevice, lat->stream));
         HIP_TRY(hipMemcpyAsync(lat->d_fbasis, basis.data(), sizeof(double) * basis.size(), hipMemcpyHostToDevice,
                                lat->stream));
         HIP_TRY(hipMemcpyAsync(lat->d_fdraw, dr.data(), sizeof(double) * dr.size(), hipMemcpyHostToDevice,
@@ -1314,7 +1322,9 @@ int backward(nco_lattice* lat, const double* dL_dk, int every, const double* dL_
                 // The force of step t also depends on x_t through its velocity modes.
                 const long ft = (lat->rec_force_t0 + t) % lat->force_steps;
                 HIP_TRY(launch_force_phase_adjoint(lat->storage, state(t - t0), lin, lout, a, lat->force_kx,
-                                                   lat->force_ky, lat->d_fpart, lat->d_fbasis, lat->d_fdraw + (size_t)ft * lat->n_modes * 2,
+                                                   mode_list(lat->flist_groups, lat->flist_chunks, lat->d_flist),
+                                                   lat->d_fpart, lat->d_fbasis,
+                                                   lat->d_fdraw + (size_t)ft * lat->n_modes * 2,
                                                    phase_slot(lat, t) + 6 * lat->n_modes, lat->d_fduhat,
                                                    lat->stream));
             }

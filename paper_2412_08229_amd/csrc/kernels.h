@@ -3,6 +3,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include <vector>
+
 #include "collide.h"
 
 namespace nco {
@@ -120,18 +122,45 @@ hipError_t launch_step(int storage, const void* fin, void* fout, const StepArgs&
 // One step of an in-place pair on a single buffer (BGK or fixed-rate,
 // periodic): phase 0 from the standard layout, phase 1 back to it.
 hipError_t launch_step_inplace(int storage, void* f, const StepArgs& a, int phase, hipStream_t st);
-// Velocity-dependent Alvelius phase: F_hat of this step's forced modes from
-// the state f (partial: mode_partial_blocks x n_modes x 6 doubles of work
-// space; ky_max: the largest |k_y| of the modes), and u_hat into uhat (6
-// doubles per mode) unless it is null.
+// The wavenumbers of a set of forced modes as the mode sums take them
+// (modes.h), in device memory: groups of up to three distinct |k_y| (modulo
+// ny), each with its contractions (chunks of up to three distinct |k_x|), each
+// with its modes (entries).
+struct ModeGroup {
+    int ky[3], end;             // contractions up to end, from the previous group's end
+};
+struct ModeChunk {
+    int kx[3], begin, end;      // entries [begin, end)
+};
+struct ModeEntry {
+    int place, kz;
+};
+struct ModeList {
+    int groups, chunks;
+    const ModeGroup* group;
+    const ModeChunk* chunk;
+    const ModeEntry* entries;
+};
+// Host layout of the list of the modes k [n_modes][3] on a lattice of ny rows:
+// the groups, the chunks and the entries in one run of ints; and the list in
+// a copy of it at `ints`.
+struct ModeLayout {
+    int groups = 0, chunks = 0;
+    std::vector<int> ints;
+    ModeLayout(const int* k, int n_modes, int ny);
+};
+ModeList mode_list(int groups, int chunks, const int* ints);
 // Force field of one step, F(x) = sum_m 2 Re(Fhat_m e^{i k_m . x}), on every
 // node in float64 arithmetic, written to out32 or out64 ([3][n]); kx_max
 // is the largest |k_x| of the modes (at most FORCE_KX_MAX).
 constexpr int FORCE_KX_MAX = 16;
 hipError_t launch_force_field(const StepArgs& a, int kx_max, float* out32, double* out64, hipStream_t st);
-hipError_t launch_force_phase(int storage, const void* f, int n, int nx, int ny, int nz, const int* fk,
-                              int n_modes, int kx_max, int ky_max, double* partial, const double* basis,
-                              const double* draw, double* fhat, double* uhat, hipStream_t st);
+// Velocity-dependent Alvelius phase: F_hat of this step's forced modes from
+// the state f (partial: mode_partial_blocks x n_modes x 6 doubles of work
+// space), and u_hat into uhat (6 doubles per mode) unless it is null.
+hipError_t launch_force_phase(int storage, const void* f, int n, int nx, int ny, int nz, int n_modes,
+                              const ModeList& list, double* partial, const double* basis, const double* draw,
+                              double* fhat, double* uhat, hipStream_t st);
 // Blocks of the mode sums on an nx x ny x nz lattice.
 int mode_partial_blocks(int nx, int ny, int nz);
 // Fine-to-coarse restriction (coarse extent x r = fine extent on every axis).
@@ -192,10 +221,10 @@ hipError_t launch_grad_reduce_f64(const double* partial, int nblocks, int npar, 
 // step's coefficients, uhat its u_hat, draw its (phi, psi) per mode;
 // lam_out (already holding the rest of dL/dx) gets the path x -> u_hat ->
 // theta1 -> F_hat -> source added.  partial: mode_partial_blocks x n_modes x 6
-// doubles of work space, duhat: 6 doubles per mode; kx_max, ky_max: the
-// largest |k_x| and |k_y| of the modes.  Float storages only.
+// doubles of work space, duhat: 6 doubles per mode; kx_max: the largest |k_x|
+// of the modes.  Float storages only.
 hipError_t launch_force_phase_adjoint(int storage, const void* x, const float* lam_next, float* lam_out,
-                                      const StepArgs& a, int kx_max, int ky_max, double* partial,
+                                      const StepArgs& a, int kx_max, const ModeList& list, double* partial,
                                       const double* basis, const double* draw, const double* uhat, double* duhat,
                                       hipStream_t st);
 

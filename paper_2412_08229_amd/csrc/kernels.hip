@@ -329,17 +329,17 @@ __global__ __launch_bounds__(256) void k_sums_partial(const typename Codec<S>::s
 // Velocity-dependent forcing phase (Alvelius' rule, Sec. "Training Data -
 // Forced Isotropic Turbulence").  Stage 1: per block and forced mode, the
 // partial sums of u(x) exp(-i k_m.x) over the block's nodes.
-template <int S>
+template <int S, int GROUPS>
 __global__ __launch_bounds__(256) void k_mode_partials(const typename Codec<S>::store_t* __restrict__ f, int nx,
-                                                       int ny, int nz, ModeGrid g, const int* __restrict__ fk,
-                                                       int n_modes, int kx_max, int ky_max, double* __restrict__ partial) {
+                                                       int ny, int nz, ModeGrid g, ModeList l,
+                                                       double* __restrict__ partial) {
     const int n = nx * ny * nz;
-    mode_partials(
+    mode_partials<GROUPS>(
         [&](int idx, NodeIdx, double(&u)[3]) {
             double r;
             macro_double<S>(f, n, idx, r, u[0], u[1], u[2]);
         },
-        nx, ny, nz, g, fk, n_modes, kx_max, ky_max, partial);
+        nx, ny, nz, g, l, partial);
 }
 
 // Stage 2, one block per mode: u_hat = sum of the partials (fixed order) / N,
@@ -607,14 +607,81 @@ hipError_t launch_force_field(const StepArgs& a, int kx_max, float* out32, doubl
 
 int mode_partial_blocks(int nx, int ny, int nz) { return mode_grid(nx, ny, nz).blocks; }
 
-hipError_t launch_force_phase(int storage, const void* f, int n, int nx, int ny, int nz, const int* fk,
-                              int n_modes, int kx_max, int ky_max, double* partial, const double* basis, const double* draw,
+ModeLayout::ModeLayout(const int* k, int n_modes, int ny) {
+    struct Mode {
+        int m, ax, ay;
+        bool xneg, yneg;
+    };
+    std::vector<Mode> modes(n_modes);
+    for (int m = 0; m < n_modes; ++m) {
+        long y = k[3 * m + 1] % ny;             // e^{i 2 pi k_y y / ny} depends on k_y modulo ny
+        if (2 * y > ny) y -= ny;
+        if (2 * y < -ny) y += ny;
+        modes[m] = Mode{m, std::abs(k[3 * m]), (int)std::abs(y), k[3 * m] < 0, y < 0};
+    }
+    std::sort(modes.begin(), modes.end(), [](const Mode& a, const Mode& b) {
+        return a.ay != b.ay ? a.ay < b.ay : a.m < b.m;
+    });
+    std::vector<ModeGroup> group;
+    std::vector<ModeChunk> chunk;
+    std::vector<ModeEntry> entries;
+    for (size_t i = 0; i < modes.size();) {
+        ModeGroup g{{0, 0, 0}, 0};
+        std::vector<std::pair<int, Mode>> in;   // place of |k_y|, mode
+        int ky = -1;
+        for (; i < modes.size(); ++i) {
+            if (in.empty() || modes[i].ay != g.ky[ky]) {
+                if (ky + 1 == MODES_M) break;
+                g.ky[++ky] = modes[i].ay;
+            }
+            in.push_back({ky, modes[i]});
+        }
+        std::stable_sort(in.begin(), in.end(), [](const auto& a, const auto& b) { return a.second.ax < b.second.ax; });
+        for (size_t j = 0; j < in.size();) {
+            ModeChunk c{{0, 0, 0}, (int)entries.size(), 0};
+            int kx = -1;
+            for (; j < in.size(); ++j) {
+                const Mode& m = in[j].second;
+                if (kx < 0 || m.ax != c.kx[kx]) {
+                    if (kx + 1 == MODES_K) break;
+                    c.kx[++kx] = m.ax;
+                }
+                entries.push_back(ModeEntry{mode_place(m.m, kx, in[j].first, m.xneg, m.yneg), k[3 * m.m + 2]});
+            }
+            c.end = (int)entries.size();
+            chunk.push_back(c);
+        }
+        g.end = (int)chunk.size();
+        group.push_back(g);
+    }
+    groups = (int)group.size();
+    chunks = (int)chunk.size();
+    for (const ModeGroup& g : group) ints.insert(ints.end(), {g.ky[0], g.ky[1], g.ky[2], g.end});
+    for (const ModeChunk& c : chunk) ints.insert(ints.end(), {c.kx[0], c.kx[1], c.kx[2], c.begin, c.end});
+    for (const ModeEntry& e : entries) ints.insert(ints.end(), {e.place, e.kz});
+}
+
+ModeList mode_list(int groups, int chunks, const int* ints) {
+    static_assert(sizeof(ModeGroup) == 4 * sizeof(int) && sizeof(ModeChunk) == 5 * sizeof(int) &&
+                      sizeof(ModeEntry) == 2 * sizeof(int) && alignof(ModeEntry) == alignof(int),
+                  "the layout's runs");
+    return ModeList{groups, chunks, reinterpret_cast<const ModeGroup*>(ints),
+                    reinterpret_cast<const ModeChunk*>(ints + 4 * (size_t)groups),
+                    reinterpret_cast<const ModeEntry*>(ints + 4 * (size_t)groups + 5 * (size_t)chunks)};
+}
+
+hipError_t launch_force_phase(int storage, const void* f, int n, int nx, int ny, int nz, int n_modes,
+                              const ModeList& list, double* partial, const double* basis, const double* draw,
                               double* fhat, double* uhat, hipStream_t st) {
     const ModeGrid g = mode_grid(nx, ny, nz);
     DISPATCH_STORAGE(storage, {
-        hipLaunchKernelGGL(k_mode_partials<SS>, dim3(g.blocks), dim3(256), 0, st,
-                           static_cast<const typename Codec<SS>::store_t*>(f), nx, ny, nz, g, fk, n_modes, kx_max, ky_max,
-                           partial);
+        const auto* fs = static_cast<const typename Codec<SS>::store_t*>(f);
+        if (list.groups == 1)
+            hipLaunchKernelGGL((k_mode_partials<SS, 1>), dim3(g.blocks), dim3(256), 0, st, fs, nx, ny, nz, g, list,
+                               partial);
+        else
+            hipLaunchKernelGGL((k_mode_partials<SS, MODES_GROUPS>), dim3(g.blocks), dim3(256), 0, st, fs, nx, ny, nz, g,
+                               list, partial);
         if (hipError_t e = hipGetLastError()) return e;
         hipLaunchKernelGGL(k_force_phase, dim3(n_modes), dim3(256), 0, st, partial, g.blocks, 1.0 / n, basis, draw,
                            fhat, uhat);

@@ -18,21 +18,29 @@ namespace nco {
 // A block takes up to 256 consecutive x and `rows` consecutive y of one z
 // plane.  Thread t keeps to one x (and to the rows sub, sub + rp, ...: below
 // 256 nodes per row, rp rows run side by side) and accumulates its column's
-// sums of v cos(m y'), v sin(m y') for MODES_M wavenumbers m = |k_y| at a
-// time (y' = 2 pi y / ny, from a table per block).  The columns' sums then
-// meet the x phases of MODES_K wavenumbers |k_x| in LDS, all products shared
-// by the modes that need them, and each mode combines four of the block's
-// totals with its signs and its z phase.
+// sums of v cos(m y'), v sin(m y') (y' = 2 pi y / ny, from a table per block)
+// for the wavenumbers m = |k_y| of the modes, MODES_M of them to a group and
+// GROUPS groups to a pass over the nodes.  The columns' sums of a group then
+// meet the x phases of MODES_K of its modes' wavenumbers |k_x| in LDS, all
+// products shared by the modes that need them, and each mode combines four of
+// the block's totals with its signs and its z phase.  Which wavenumbers make a
+// group, and which |k_x| meet it, is laid out once per set of modes
+// (mode_list): only those that occur, k_y modulo ny.
 //
 // What bounds it: reading the state (the velocity of a 256^3 float32 lattice:
-// 1.8 GB).  A phase per mode and node (about 60 float64 operations each) took
-// 2.07 ms at 256^3 with 16 modes and 0.149 ms at 64^3 with 40; contracting
-// the columns once per mode 0.90 and 0.083 ms; this form 0.35
-// and 0.013 ms.
-constexpr int MODES_M = 3;          // wavenumbers |k_y| per pass
+// 1.8 GB), once for up to MODES_M GROUPS distinct |k_y|.  A phase per mode and
+// node (about 60 float64 operations each) took 2.07 ms at 256^3 with 16 modes
+// and 0.149 ms at 64^3 with 40; contracting the columns once per mode 0.90
+// and 0.083 ms; this form 0.35 and 0.013 ms.  A 256^3 step forced in four
+// modes of |k_y| 3 to 16: 1.25 ms (2.38 with a phase per mode and node, 2.74
+// with every |k_x| and |k_y| up to the largest, three |k_y| to a pass).
+constexpr int MODES_M = 3;          // wavenumbers |k_y| per group
 constexpr int MODES_K = 3;          // wavenumbers |k_x| per contraction
 constexpr int MODES_ROWS = 64;      // rows of a block at most
 constexpr int MODES_COLS = 257;     // LDS row of 256 columns
+// Groups per pass where there are more than MODES_M distinct |k_y|: what the
+// sums' registers allow (18 doubles per group and thread).
+constexpr int MODES_GROUPS = 3;
 
 struct ModeGrid {
     int width, rp, rows, xchunks, ychunks, blocks;
@@ -57,14 +65,19 @@ inline ModeGrid mode_grid(int nx, int ny, int nz) {
     return g;
 }
 
+// A mode's place in its contraction: among the contraction's |k_x| and the
+// group's |k_y|, and the signs of k_x and of k_y modulo ny.
+constexpr int mode_place(int mode, int ix, int iy, bool nx, bool ny) { return mode << 6 | ny << 5 | nx << 4 | iy << 2 | ix; }
+
 // value(idx, p, v): the field's three components v at node idx = (x, y, z) p.
-template <typename F>
-__device__ __forceinline__ void mode_partials(F&& value, int nx, int ny, int nz, ModeGrid g, const int* __restrict__ fk,
-                                              int n_modes, int kx_max, int ky_max, double* __restrict__ partial) {
+template <int GROUPS, typename F>
+__device__ __forceinline__ void mode_partials(F&& value, int nx, int ny, int nz, ModeGrid g, ModeList l,
+                                              double* __restrict__ partial) {
     constexpr int GROWS = 6 * MODES_M;          // [component 3][m][cos, sin] sums of a column
     constexpr int COMBOS = 3 * MODES_K, PARTS = 256 / COMBOS, VALS = 4 * MODES_M;
+    constexpr int YTAB = MODES_M * GROUPS;
     __shared__ double G[GROWS][MODES_COLS], X[2 * MODES_K][MODES_COLS], H[COMBOS * VALS];
-    __shared__ Phasor ytab[MODES_ROWS][MODES_M];
+    __shared__ Phasor ytab[MODES_ROWS][YTAB];
     static_assert(COMBOS * PARTS * VALS <= GROWS * MODES_COLS, "the partial totals reuse G");
     double* const red = &G[0][0];
     const int tid = threadIdx.x;
@@ -77,91 +90,107 @@ __device__ __forceinline__ void mode_partials(F&& value, int nx, int ny, int nz,
     const bool active = sub < g.rp && x < nx;
     const int nt = g.rp * g.width;              // threads with a column
     const Phasor bx = axis_phasor(active ? x : 0, nx), bz = axis_phasor(z, nz);
-    for (int m0 = 0; m0 <= ky_max; m0 += MODES_M) {
-        for (int e = tid; e < rows * MODES_M; e += 256) {
-            const int m = m0 + e % MODES_M;
-            ytab[e / MODES_M][e % MODES_M] = axis_phasor((int)(((long)m * (y0 + e / MODES_M)) % ny), ny);
-        }
+    // One contraction of a group, whose column sums are acc.
+    auto contract = [&](const ModeChunk& ch, const double(&acc)[3][2 * MODES_M]) __attribute__((always_inline)) {
+        ModeEntry next = ch.begin + tid < ch.end ? l.entries[ch.begin + tid] : ModeEntry{0, 0};
         __syncthreads();
-        double acc[3][2 * MODES_M];
 #pragma unroll
         for (int d = 0; d < 3; ++d)
 #pragma unroll
-            for (int j = 0; j < 2 * MODES_M; ++j) acc[d][j] = 0.0;
+            for (int j = 0; j < 2 * MODES_M; ++j) G[2 * MODES_M * d + j][tid] = acc[d][j];
+#pragma unroll
+        for (int k = 0; k < MODES_K; ++k) {
+            const Phasor e = phasor_pow(bx, ch.kx[k]);
+            X[2 * k][tid] = e.c;
+            X[2 * k + 1][tid] = e.s;
+        }
+        __syncthreads();
+        // Thread (k, component, part): its run of columns, the sums
+        // [m][cos, sin of y'] x [cos, sin of x'].
+        const int combo = tid % COMBOS, part = tid / COMBOS, k = combo % MODES_K, d = combo / MODES_K;
+        double t[VALS];
+#pragma unroll
+        for (int j = 0; j < VALS; ++j) t[j] = 0.0;
+        if (part < PARTS) {
+            const int c1 = (part + 1) * nt / PARTS;
+            for (int c = part * nt / PARTS; c < c1; ++c) {
+                const double xcs = X[2 * k][c], xsn = X[2 * k + 1][c];
+#pragma unroll
+                for (int j = 0; j < 2 * MODES_M; ++j) {
+                    const double v = G[2 * MODES_M * d + j][c];
+                    t[2 * j] = fma(v, xcs, t[2 * j]);
+                    t[2 * j + 1] = fma(v, xsn, t[2 * j + 1]);
+                }
+            }
+        }
+        __syncthreads();
+        if (part < PARTS)
+#pragma unroll
+            for (int j = 0; j < VALS; ++j) red[(combo * VALS + j) * PARTS + part] = t[j];
+        __syncthreads();
+        if (tid < COMBOS * VALS) {
+            double s = 0.0;
+            for (int q = 0; q < PARTS; ++q) s += red[tid * PARTS + q];
+            H[tid] = s;
+        }
+        __syncthreads();
+        for (int i = ch.begin + tid; i < ch.end; i += 256) {
+            const int e = next.place, m = e >> 6, ix = e & 3, iy = (e >> 2) & 3;
+            const bool xneg = e & 16, yneg = e & 32;
+            const Phasor ez = phasor_pow(bz, -next.kz);
+            if (i + 256 < ch.end) next = l.entries[i + 256];
+            for (int c = 0; c < 3; ++c) {
+                // sum of v cos y' cos x', v cos y' sin x', v sin y' cos x', v sin y' sin x'
+                const double* h = H + ((c * MODES_K + ix) * VALS + 4 * iy);
+                const double sxy = xneg != yneg ? -h[3] : h[3];
+                const Phasor o = phasor_mul(Phasor{h[0] - sxy, -((xneg ? -h[1] : h[1]) + (yneg ? -h[2] : h[2]))}, ez);
+                partial[(size_t)(6 * m + 2 * c) * gridDim.x + blockIdx.x] = o.c;
+                partial[(size_t)(6 * m + 2 * c + 1) * gridDim.x + blockIdx.x] = o.s;
+            }
+        }
+    };
+    // The next contraction (they follow one another in the order of the groups),
+    // read ahead.
+    ModeChunk ch = l.chunk[0];
+    int at = 0;
+    for (int pass = 0; pass < l.groups; pass += GROUPS) {
+        for (int e = tid; e < rows * YTAB; e += 256) {
+            const int j = e % YTAB, gr = pass + j / MODES_M;
+            const int m = gr < l.groups ? l.group[gr].ky[j % MODES_M] : 0;
+            ytab[e / YTAB][j] = axis_phasor((int)(((long)m * (y0 + e / YTAB)) % ny), ny);
+        }
+        __syncthreads();
+        double acc[GROUPS][3][2 * MODES_M];
+#pragma unroll
+        for (int u = 0; u < GROUPS; ++u)
+#pragma unroll
+            for (int d = 0; d < 3; ++d)
+#pragma unroll
+                for (int j = 0; j < 2 * MODES_M; ++j) acc[u][d][j] = 0.0;
         if (active)
             for (int r = sub; r < rows; r += g.rp) {
                 const NodeIdx p{x, y0 + r, z};
                 double v[3];
                 value((p.z * ny + p.y) * nx + p.x, p, v);
 #pragma unroll
-                for (int j = 0; j < MODES_M; ++j) {
+                for (int j = 0; j < YTAB; ++j) {
                     const Phasor e = ytab[r][j];
+                    auto& s = acc[j / MODES_M];
 #pragma unroll
                     for (int d = 0; d < 3; ++d) {
-                        acc[d][2 * j] = fma(v[d], e.c, acc[d][2 * j]);
-                        acc[d][2 * j + 1] = fma(v[d], e.s, acc[d][2 * j + 1]);
+                        s[d][2 * (j % MODES_M)] = fma(v[d], e.c, s[d][2 * (j % MODES_M)]);
+                        s[d][2 * (j % MODES_M) + 1] = fma(v[d], e.s, s[d][2 * (j % MODES_M) + 1]);
                     }
                 }
             }
-        for (int k0 = 0; k0 <= kx_max; k0 += MODES_K) {
-            __syncthreads();
 #pragma unroll
-            for (int d = 0; d < 3; ++d)
-#pragma unroll
-                for (int j = 0; j < 2 * MODES_M; ++j) G[2 * MODES_M * d + j][tid] = acc[d][j];
-            Phasor e = phasor_pow(bx, k0);
-#pragma unroll
-            for (int k = 0; k < MODES_K; ++k) {
-                X[2 * k][tid] = e.c;
-                X[2 * k + 1][tid] = e.s;
-                e = phasor_mul(e, bx);
-            }
-            __syncthreads();
-            // Thread (k, component, part): its run of columns, the sums
-            // [m][cos, sin of y'] x [cos, sin of x'].
-            const int combo = tid % COMBOS, part = tid / COMBOS, k = combo % MODES_K, d = combo / MODES_K;
-            double t[VALS];
-#pragma unroll
-            for (int j = 0; j < VALS; ++j) t[j] = 0.0;
-            if (part < PARTS) {
-                const int c1 = (part + 1) * nt / PARTS;
-                for (int c = part * nt / PARTS; c < c1; ++c) {
-                    const double xcs = X[2 * k][c], xsn = X[2 * k + 1][c];
-#pragma unroll
-                    for (int j = 0; j < 2 * MODES_M; ++j) {
-                        const double v = G[2 * MODES_M * d + j][c];
-                        t[2 * j] = fma(v, xcs, t[2 * j]);
-                        t[2 * j + 1] = fma(v, xsn, t[2 * j + 1]);
-                    }
+        for (int u = 0; u < GROUPS; ++u)
+            if (pass + u < l.groups)
+                for (const int g1 = l.group[pass + u].end;;) {
+                    contract(ch, acc[u]);
+                    if (++at < l.chunks) ch = l.chunk[at];
+                    if (at == g1) break;
                 }
-            }
-            __syncthreads();
-            if (part < PARTS)
-#pragma unroll
-                for (int j = 0; j < VALS; ++j) red[(combo * VALS + j) * PARTS + part] = t[j];
-            __syncthreads();
-            if (tid < COMBOS * VALS) {
-                double s = 0.0;
-                for (int q = 0; q < PARTS; ++q) s += red[tid * PARTS + q];
-                H[tid] = s;
-            }
-            __syncthreads();
-            for (int m = tid; m < n_modes; m += 256) {
-                const int kx = fk[3 * m], ky = fk[3 * m + 1];
-                const int ix = (kx < 0 ? -kx : kx) - k0, iy = (ky < 0 ? -ky : ky) - m0;
-                if (ix < 0 || ix >= MODES_K || iy < 0 || iy >= MODES_M) continue;
-                const Phasor ez = phasor_pow(bz, -fk[3 * m + 2]);
-                for (int c = 0; c < 3; ++c) {
-                    // sum of v cos y' cos x', v cos y' sin x', v sin y' cos x', v sin y' sin x'
-                    const double* h = H + ((c * MODES_K + ix) * VALS + 4 * iy);
-                    const double sxy = (kx < 0) != (ky < 0) ? -h[3] : h[3];
-                    const Phasor o = phasor_mul(
-                        Phasor{h[0] - sxy, -((kx < 0 ? -h[1] : h[1]) + (ky < 0 ? -h[2] : h[2]))}, ez);
-                    partial[(size_t)(6 * m + 2 * c) * gridDim.x + blockIdx.x] = o.c;
-                    partial[(size_t)(6 * m + 2 * c + 1) * gridDim.x + blockIdx.x] = o.s;
-                }
-            }
-        }
         __syncthreads();
     }
 }
