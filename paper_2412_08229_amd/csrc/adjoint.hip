@@ -578,11 +578,11 @@ __global__ __launch_bounds__(256) void k_add_energy_grad(const typename Codec<S>
 // v = j + F; then per block and forced mode the partial sums of
 // (g cos(k.x), -g sin(k.x)) as in the forward's mode sums (64^3, 40 modes:
 // 0.106 ms with a phase per mode and node, 0.018 ms now).
-template <int S, int GROUPS>
+template <int S, int GROUPS, int ROWS>
 __global__ __launch_bounds__(256) void k_force_adj_partials(const typename Codec<S>::store_t* __restrict__ xin,
                                                             const float* __restrict__ lam, StepArgs a, ModeGrid grid,
                                                             ModeList list, double* __restrict__ partial) {
-    mode_partials<GROUPS>(
+    mode_partials<GROUPS, ROWS>(
         [&](int idx, NodeIdx p, double(&g)[3]) {
             typename Codec<S>::real f[Q];
             pull<S>(xin, a, p, f);
@@ -614,7 +614,7 @@ __global__ __launch_bounds__(256) void k_force_adj_partials(const typename Codec
 #pragma unroll
             for (int c = 0; c < 3; ++c) g[c] -= 3.0 * v[c] * inv_rho * s0;
         },
-        a.nx, a.ny, a.nz, grid, list, partial);
+        grid, list, partial);
 }
 
 // Stage 2, one block per mode: dL/dF_hat = 2 x (sum of the partials, fixed
@@ -879,12 +879,10 @@ hipError_t launch_force_phase_adjoint(int storage, const void* x, const float* l
 #define FPA_CASE(SS)                                                                                           \
     case SS: {                                                                                                 \
         const auto* xs = static_cast<const typename Codec<SS>::store_t*>(x);                                   \
-        if (list.groups == 1)                                                                                  \
-            hipLaunchKernelGGL((k_force_adj_partials<SS, 1>), pgrid, block, 0, st, xs, lam_next, a, g, list,   \
-                               partial);                                                                       \
-        else                                                                                                   \
-            hipLaunchKernelGGL((k_force_adj_partials<SS, MODES_GROUPS>), pgrid, block, 0, st, xs, lam_next, a, \
-                               g, list, partial);                                                              \
+        mode_launch(g, list, [&](auto groups, auto rows) {                                             \
+            hipLaunchKernelGGL((k_force_adj_partials<SS, groups(), rows()>), pgrid, block, 0, st, xs,  \
+                               lam_next, a, g, list, partial);                                         \
+        });                                                                                            \
         if (hipError_t e = hipGetLastError()) return e;                                                        \
         hipLaunchKernelGGL(k_force_phase_adj, dim3(a.n_modes), block, 0, st, partial, g.blocks, 1.0 / a.n,     \
                            basis, draw, a.fhat, uhat, duhat);                                                  \

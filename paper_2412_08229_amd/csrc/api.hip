@@ -1021,7 +1021,7 @@ int nco_set_forcing_ex(nco_lattice* lat, int n_modes, const int* k, const double
     HIP_TRY(hipMalloc(&lat->d_fhat, sizeof(double) * fh.size()));
     HIP_TRY(hipMemcpyAsync(lat->d_fk, k, sizeof(int) * 3 * n_modes, hipMemcpyHostToDevice, lat->stream));
     HIP_TRY(hipMemcpyAsync(lat->d_fhat, fh.data(), sizeof(double) * fh.size(), hipMemcpyHostToDevice, lat->stream));
-    const ModeLayout layout(k, phase_rule ? n_modes : 0, lat->ny);
+    const ModeLayout layout(k, phase_rule ? n_modes : 0, lat->nx, lat->ny, lat->nz);
     if (phase_rule) {
         // phi, psi of every step and mode (the theta1 draws are not used).
         std::vector<double> dr((size_t)n_steps * n_modes * 2);

@@ -133,7 +133,7 @@ struct ModeChunk {
     int kx[3], begin, end;      // entries [begin, end)
 };
 struct ModeEntry {
-    int place, kz;
+    int place, kz;              // kz: the component across the planes of the sums
 };
 struct ModeList {
     int groups, chunks;
@@ -141,13 +141,13 @@ struct ModeList {
     const ModeChunk* chunk;
     const ModeEntry* entries;
 };
-// Host layout of the list of the modes k [n_modes][3] on a lattice of ny rows:
+// Host layout of the list of the modes k [n_modes][3] on an nx x ny x nz lattice:
 // the groups, the chunks and the entries in one run of ints; and the list in
 // a copy of it at `ints`.
 struct ModeLayout {
     int groups = 0, chunks = 0;
     std::vector<int> ints;
-    ModeLayout(const int* k, int n_modes, int ny);
+    ModeLayout(const int* k, int n_modes, int nx, int ny, int nz);
 };
 ModeList mode_list(int groups, int chunks, const int* ints);
 // Force field of one step, F(x) = sum_m 2 Re(Fhat_m e^{i k_m . x}), on every

@@ -329,17 +329,15 @@ __global__ __launch_bounds__(256) void k_sums_partial(const typename Codec<S>::s
 // Velocity-dependent forcing phase (Alvelius' rule, Sec. "Training Data -
 // Forced Isotropic Turbulence").  Stage 1: per block and forced mode, the
 // partial sums of u(x) exp(-i k_m.x) over the block's nodes.
-template <int S, int GROUPS>
-__global__ __launch_bounds__(256) void k_mode_partials(const typename Codec<S>::store_t* __restrict__ f, int nx,
-                                                       int ny, int nz, ModeGrid g, ModeList l,
-                                                       double* __restrict__ partial) {
-    const int n = nx * ny * nz;
-    mode_partials<GROUPS>(
+template <int S, int GROUPS, int ROWS>
+__global__ __launch_bounds__(256) void k_mode_partials(const typename Codec<S>::store_t* __restrict__ f, int n,
+                                                       ModeGrid g, ModeList l, double* __restrict__ partial) {
+    mode_partials<GROUPS, ROWS>(
         [&](int idx, NodeIdx, double(&u)[3]) {
             double r;
             macro_double<S>(f, n, idx, r, u[0], u[1], u[2]);
         },
-        nx, ny, nz, g, l, partial);
+        g, l, partial);
 }
 
 // Stage 2, one block per mode: u_hat = sum of the partials (fixed order) / N,
@@ -607,16 +605,18 @@ hipError_t launch_force_field(const StepArgs& a, int kx_max, float* out32, doubl
 
 int mode_partial_blocks(int nx, int ny, int nz) { return mode_grid(nx, ny, nz).blocks; }
 
-ModeLayout::ModeLayout(const int* k, int n_modes, int ny) {
+ModeLayout::ModeLayout(const int* k, int n_modes, int nx, int ny, int nz) {
+    const ModeGrid grid = mode_grid(nx, ny, nz);
+    const int iy = grid.swap ? 2 : 1, iz = 3 - iy;      // components along the rows' axis and across the planes
     struct Mode {
         int m, ax, ay;
         bool xneg, yneg;
     };
     std::vector<Mode> modes(n_modes);
     for (int m = 0; m < n_modes; ++m) {
-        long y = k[3 * m + 1] % ny;             // e^{i 2 pi k_y y / ny} depends on k_y modulo ny
-        if (2 * y > ny) y -= ny;
-        if (2 * y < -ny) y += ny;
+        long y = k[3 * m + iy] % grid.n1;       // e^{i 2 pi k_y y / ny} depends on k_y modulo ny
+        if (2 * y > grid.n1) y -= grid.n1;
+        if (2 * y < -grid.n1) y += grid.n1;
         modes[m] = Mode{m, std::abs(k[3 * m]), (int)std::abs(y), k[3 * m] < 0, y < 0};
     }
     std::sort(modes.begin(), modes.end(), [](const Mode& a, const Mode& b) {
@@ -646,7 +646,7 @@ ModeLayout::ModeLayout(const int* k, int n_modes, int ny) {
                     if (kx + 1 == MODES_K) break;
                     c.kx[++kx] = m.ax;
                 }
-                entries.push_back(ModeEntry{mode_place(m.m, kx, in[j].first, m.xneg, m.yneg), k[3 * m.m + 2]});
+                entries.push_back(ModeEntry{mode_place(m.m, kx, in[j].first, m.xneg, m.yneg), k[3 * m.m + iz]});
             }
             c.end = (int)entries.size();
             chunk.push_back(c);
@@ -676,12 +676,10 @@ hipError_t launch_force_phase(int storage, const void* f, int n, int nx, int ny,
     const ModeGrid g = mode_grid(nx, ny, nz);
     DISPATCH_STORAGE(storage, {
         const auto* fs = static_cast<const typename Codec<SS>::store_t*>(f);
-        if (list.groups == 1)
-            hipLaunchKernelGGL((k_mode_partials<SS, 1>), dim3(g.blocks), dim3(256), 0, st, fs, nx, ny, nz, g, list,
+        mode_launch(g, list, [&](auto groups, auto rows) {
+            hipLaunchKernelGGL((k_mode_partials<SS, groups(), rows()>), dim3(g.blocks), dim3(256), 0, st, fs, n, g, list,
                                partial);
-        else
-            hipLaunchKernelGGL((k_mode_partials<SS, MODES_GROUPS>), dim3(g.blocks), dim3(256), 0, st, fs, nx, ny, nz, g,
-                               list, partial);
+        });
         if (hipError_t e = hipGetLastError()) return e;
         hipLaunchKernelGGL(k_force_phase, dim3(n_modes), dim3(256), 0, st, partial, g.blocks, 1.0 / n, basis, draw,
                            fhat, uhat);

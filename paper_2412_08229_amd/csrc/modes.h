@@ -5,6 +5,8 @@
 // phase per mode.
 #pragma once
 
+#include <type_traits>
+
 #include "kernels.h"
 #include "stream.h"
 
@@ -16,7 +18,7 @@ namespace nco {
 // six doubles (Re, Im of x, y, z) at partial[(6 m + q) nblocks + block].
 //
 // A block takes up to 256 consecutive x and `rows` consecutive y of one z
-// plane.  Thread t keeps to one x (and to the rows sub, sub + rp, ...: below
+// plane (or z of one y plane: ModeGrid).  Thread t keeps to one x (and to the rows sub, sub + rp, ...: below
 // 256 nodes per row, rp rows run side by side) and accumulates its column's
 // sums of v cos(m y'), v sin(m y') (y' = 2 pi y / ny, from a table per block)
 // for the wavenumbers m = |k_y| of the modes, MODES_M of them to a group and
@@ -36,32 +38,45 @@ namespace nco {
 // with every |k_x| and |k_y| up to the largest, three |k_y| to a pass).
 constexpr int MODES_M = 3;          // wavenumbers |k_y| per group
 constexpr int MODES_K = 3;          // wavenumbers |k_x| per contraction
-constexpr int MODES_ROWS = 64;      // rows of a block at most
+constexpr int MODES_ROWS = 64;      // rows of the phase table,
+constexpr int MODES_ROWS_SHORT = 256;   // and where a block has more (filled anew for every 256)
 constexpr int MODES_COLS = 257;     // LDS row of 256 columns
 // Groups per pass where there are more than MODES_M distinct |k_y|: what the
 // sums' registers allow (18 doubles per group and thread).
 constexpr int MODES_GROUPS = 3;
 
+// Blocks of the sums: `width` consecutive x and `rows` consecutive places of
+// the other axis of their plane, y, or with `swap` z (the planes are then those
+// of one y, and k_y and k_z exchange their parts in all of the above).
 struct ModeGrid {
+    int nx, n1, n2;             // extents of x, of the rows' axis and of the planes
+    bool swap;
     int width, rp, rows, xchunks, ychunks, blocks;
 };
 
 // Rows per block: about 16 nodes per thread on large lattices, fewer where
-// that would leave fewer than ~500 blocks (64^3: two).
+// that would leave fewer than ~500 blocks (64^3: two).  A block costs its
+// contractions whatever it holds, and the work space a column per block, so
+// the rows go along z where a plane of y holds less than half as many.  BGK
+// step forced in the 40 modes of |k| <= 2.5, one block or more per z plane
+// against this: 8 x 8 x 16384 431 -> 290 us, 1 x 1 x 262144 3198 -> 402 (a phase
+// per mode and node 547 and 524).
 inline ModeGrid mode_grid(int nx, int ny, int nz) {
     ModeGrid g;
+    g.nx = nx;
     g.width = nx < 256 ? nx : 256;
     g.rp = 256 / g.width;
     const long n = (long)nx * ny * nz;
     long s = n / (256L * 512);
     s = s < 1 ? 1 : s > 16 ? 16 : s;
-    long rows = g.rp * s;
-    if (rows > MODES_ROWS) rows = MODES_ROWS;
-    if (rows > ny) rows = ny;
-    g.rows = (int)rows;
+    const long most = g.rp * s, ry = most < ny ? most : ny, rz = most < nz ? most : nz;
+    g.swap = rz >= 2 * ry;
+    g.rows = (int)(g.swap ? rz : ry);
+    g.n1 = g.swap ? nz : ny;
+    g.n2 = g.swap ? ny : nz;
     g.xchunks = (nx + g.width - 1) / g.width;
-    g.ychunks = (ny + g.rows - 1) / g.rows;
-    g.blocks = g.xchunks * g.ychunks * nz;
+    g.ychunks = (g.n1 + g.rows - 1) / g.rows;
+    g.blocks = g.xchunks * g.ychunks * g.n2;
     return g;
 }
 
@@ -70,17 +85,16 @@ inline ModeGrid mode_grid(int nx, int ny, int nz) {
 constexpr int mode_place(int mode, int ix, int iy, bool nx, bool ny) { return mode << 6 | ny << 5 | nx << 4 | iy << 2 | ix; }
 
 // value(idx, p, v): the field's three components v at node idx = (x, y, z) p.
-template <int GROUPS, typename F>
-__device__ __forceinline__ void mode_partials(F&& value, int nx, int ny, int nz, ModeGrid g, ModeList l,
-                                              double* __restrict__ partial) {
+template <int GROUPS, int ROWS, typename F>
+__device__ __forceinline__ void mode_partials(F&& value, ModeGrid g, ModeList l, double* __restrict__ partial) {
     constexpr int GROWS = 6 * MODES_M;          // [component 3][m][cos, sin] sums of a column
     constexpr int COMBOS = 3 * MODES_K, PARTS = 256 / COMBOS, VALS = 4 * MODES_M;
     constexpr int YTAB = MODES_M * GROUPS;
     __shared__ double G[GROWS][MODES_COLS], X[2 * MODES_K][MODES_COLS], H[COMBOS * VALS];
-    __shared__ Phasor ytab[MODES_ROWS][YTAB];
+    __shared__ Phasor ytab[ROWS][YTAB];
     static_assert(COMBOS * PARTS * VALS <= GROWS * MODES_COLS, "the partial totals reuse G");
     double* const red = &G[0][0];
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, nx = g.nx, ny = g.n1, nz = g.n2;       // y, z: the rows' and the planes' axis
     int b = blockIdx.x;
     const int xc = b % g.xchunks;
     b /= g.xchunks;
@@ -154,12 +168,6 @@ __device__ __forceinline__ void mode_partials(F&& value, int nx, int ny, int nz,
     ModeChunk ch = l.chunk[0];
     int at = 0;
     for (int pass = 0; pass < l.groups; pass += GROUPS) {
-        for (int e = tid; e < rows * YTAB; e += 256) {
-            const int j = e % YTAB, gr = pass + j / MODES_M;
-            const int m = gr < l.groups ? l.group[gr].ky[j % MODES_M] : 0;
-            ytab[e / YTAB][j] = axis_phasor((int)(((long)m * (y0 + e / YTAB)) % ny), ny);
-        }
-        __syncthreads();
         double acc[GROUPS][3][2 * MODES_M];
 #pragma unroll
         for (int u = 0; u < GROUPS; ++u)
@@ -167,11 +175,21 @@ __device__ __forceinline__ void mode_partials(F&& value, int nx, int ny, int nz,
             for (int d = 0; d < 3; ++d)
 #pragma unroll
                 for (int j = 0; j < 2 * MODES_M; ++j) acc[u][d][j] = 0.0;
-        if (active)
-            for (int r = sub; r < rows; r += g.rp) {
-                const NodeIdx p{x, y0 + r, z};
+        for (int r0 = 0; r0 < rows; r0 += ROWS) {
+            const int nr = min(ROWS, rows - r0);
+            if (r0 > 0) __syncthreads();
+            for (int e = tid; e < nr * YTAB; e += 256) {
+                const int j = e % YTAB, gr = pass + j / MODES_M;
+                const int m = gr < l.groups ? l.group[gr].ky[j % MODES_M] : 0;
+                ytab[e / YTAB][j] = axis_phasor((int)(((long)m * (y0 + r0 + e / YTAB)) % ny), ny);
+            }
+            __syncthreads();
+            if (!active) continue;
+            for (int r = sub; r < nr; r += g.rp) {
+                const int y = y0 + r0 + r;
+                const NodeIdx p = g.swap ? NodeIdx{x, z, y} : NodeIdx{x, y, z};
                 double v[3];
-                value((p.z * ny + p.y) * nx + p.x, p, v);
+                value((g.swap ? p.z * nz + p.y : p.z * ny + p.y) * nx + x, p, v);
 #pragma unroll
                 for (int j = 0; j < YTAB; ++j) {
                     const Phasor e = ytab[r][j];
@@ -183,6 +201,7 @@ __device__ __forceinline__ void mode_partials(F&& value, int nx, int ny, int nz,
                     }
                 }
             }
+        }
 #pragma unroll
         for (int u = 0; u < GROUPS; ++u)
             if (pass + u < l.groups)
@@ -193,6 +212,20 @@ __device__ __forceinline__ void mode_partials(F&& value, int nx, int ny, int nz,
                 }
         __syncthreads();
     }
+}
+
+// Launches launch(groups per pass, rows of the table), both as types, for the
+// grid and the list.
+template <typename L>
+void mode_launch(const ModeGrid& g, const ModeList& l, L&& launch) {
+    using One = std::integral_constant<int, 1>;
+    using All = std::integral_constant<int, MODES_GROUPS>;
+    using Few = std::integral_constant<int, MODES_ROWS>;
+    using Many = std::integral_constant<int, MODES_ROWS_SHORT>;
+    if (l.groups == 1)
+        g.rows <= MODES_ROWS ? launch(One{}, Few{}) : launch(One{}, Many{});
+    else
+        g.rows <= MODES_ROWS ? launch(All{}, Few{}) : launch(All{}, Many{});
 }
 
 // ------------------------------------------------------------ synthesis --

@@ -90,3 +90,66 @@ def test_gradient_of_many_wavenumbers(shape, kmax, count):
     go = adjoint.flatten(go)
     assert np.linalg.norm(g - go) < 1e-4 * np.linalg.norm(go)
     assert np.linalg.norm(df0 - gfo) < 1e-4 * np.linalg.norm(gfo)
+
+
+@pytest.mark.parametrize("shape,kmax,count", [((300, 2, 3), (2, 2, 20), 40), ((600, 1, 1), (1, 1, 30), 30),
+                                              ((70, 3, 5), (2, 1, 9), 40), ((3, 300, 2), (1, 12, 2), 40),
+                                              ((512, 1, 600), (3, 0, 5), 12), ((1, 1 << 18, 1), (0, 9, 0), 9), ((900, 1, 300), (2, 0, 5), 6), ((520, 3, 1), (0, 1, 25), 30)])
+def test_rows_along_either_axis(shape, kmax, count):
+    """Short and thin planes: rows along z (300, 600, 70, 512, 520 long) or y,
+    up to 256 to a block, with a remainder, in one group of wavenumbers and
+    several; as _check, one step."""
+    rng = np.random.Generator(np.random.PCG64(3))
+    ks = rng.integers(-np.array(kmax), np.array(kmax) + 1, size=(count, 3))
+    ks = ks[np.abs(ks).sum(axis=1) > 0]
+    draws = inputs.uniform_draws(1, len(ks), 6)
+    rho, u = inputs.random_velocity(shape, seed=7, amp=0.05)
+    with Lattice(shape, "f64", "bgk", 0.6) as lat:
+        lat.set_forcing(ks, draws, 1e-6, 1.5, 400.0, phase_rule=True)
+        lat.init_equilibrium(rho, u)
+        f = lat.populations()
+        lat.step(1)
+        got = lat.populations()
+    _, ut = collision.macroscopic(f)
+    want = step.step(f, step.Operator("bgk", 0.6), force=_oracle_force(ks, draws[0], 1e-6, 1.5, 400.0, ut))
+    assert np.abs(got - want).max() < 1e-13
+
+
+@pytest.mark.parametrize("shape", [(70, 3, 5), (5, 130, 2)])
+def test_gradient_with_rows_along_either_axis(shape):
+    """As test_gradient_of_many_wavenumbers."""
+    rng = np.random.Generator(np.random.PCG64(5))
+    ks = rng.integers([-2, -1, -2], [3, 2, 3], size=(30, 3))
+    ks = ks[np.abs(ks).sum(axis=1) > 0]
+    draws = inputs.uniform_draws(2, len(ks), 8)
+    rho, u = inputs.random_velocity(shape, seed=9, amp=0.05)
+    params = inputs.mlp_params(32, 10)
+    w = np.random.Generator(np.random.PCG64(11)).standard_normal((27,) + shape)
+    with Lattice(shape, "f32", "nco", 0.58) as lat:
+        lat.set_net_weights(params, 32, "tanh", "f32_mfma")
+        lat.set_forcing(ks, draws, 1e-5, 1.5, 40.0, phase_rule=True)
+        lat.init_equilibrium(rho, u)
+        fs = lat.populations()
+        lat.forward_record(3, 2)
+        g, df0 = lat.backward(dL_df=w, want_df0=True)
+    _, go, gfo = adjoint.run_and_grad(fs, 0.58, collision.unpack_params(params, 32), "tanh", 3,
+                                      lambda x: (float((w * x).sum()), w), state_forcing=(ks, draws, 1e-5, 1.5, 40.0))
+    go = adjoint.flatten(go)
+    assert np.linalg.norm(g - go) < 1e-4 * np.linalg.norm(go)
+    assert np.linalg.norm(df0 - gfo) < 1e-4 * np.linalg.norm(gfo)
+
+
+@pytest.mark.parametrize("shape", [(1 << 20, 1, 1), (1 << 18, 2, 2), (1, 1 << 20, 1), (1 << 14, 8, 8)])
+def test_work_space_of_thin_lattices(shape):
+    """The sums' work space: six doubles per mode and block of at least 256
+    nodes, whatever the lattice's shape, beside the force field (3 floats per
+    node); 64 MB for the coefficients and the allocator's granules."""
+    torch = pytest.importorskip("torch")
+    n, modes = int(np.prod(shape)), 60
+    ks = np.array([[m % 5 - 2, m % 3 - 1, 1 + m] for m in range(modes)])
+    with Lattice(shape, "f32", "bgk", 0.6) as lat:
+        lat.sync()
+        before = torch.cuda.mem_get_info()[0]
+        lat.set_forcing(ks, inputs.uniform_draws(1, modes, 6), 1e-6, 1.5, 400.0, phase_rule=True)
+        used = before - torch.cuda.mem_get_info()[0]
+    assert used <= 12 * n + 48 * modes * n // 256 + (64 << 20)
