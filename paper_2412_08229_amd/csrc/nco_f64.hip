@@ -5,8 +5,7 @@
 // The same scheme as the float32 matrix-core network (nco_mfma.hip): tiles
 // of 16 nodes as transposed GEMMs (hidden x nodes), the eight reflections of
 // an axis permutation as a Walsh-Hadamard transform of eight parity-class
-// products, each layer's accumulator the next layer's B operand, tanh as
-// 1 - 2 r with the affine map folded into the next layer.  The float64
+// products, each layer's accumulator the next layer's B operand.  The float64
 // product's accumulator holds, in lane (q, c) = (lane / 16, lane % 16),
 // element i = row 4 i + q of column c, so K-step ks of the next product takes
 // hidden units 4 ks + q straight from element ks % 4 of tile ks / 4, and a
@@ -57,36 +56,35 @@ __device__ __forceinline__ f64x4 mfma64(double a, double b, f64x4 c) {
     return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
 
-// tanh: r = 1 / (1 + 2^y) for the pre-activation scaled by 2 log2(e), so that
-// tanh(z) = 1 - 2 r.  2^y = 2^n 2^f with n the nearest integer and f in
-// [-1/2, 1/2]; 2^f by the interpolant of degree 11 at the Chebyshev nodes
-// (relative error 2.0e-17 with these rounded coefficients); n is capped so
-// that 1 + 2^y stays finite (r underflows the sum 1 - 2 r long before).  The
-// reciprocal takes two Newton steps from the hardware's estimate.  A NaN
-// pre-activation stays NaN.
+// tanh(z) = (2^y - 1) / (2^y + 1), y = 2 log2(e) z the pre-activation as the
+// tables scale it; with n the nearest integer to y, f = y - n in [-1/2, 1/2] and
+// c = 2^-n, numerator and denominator times c are (2^f - 1) + (1 - c) and that
+// plus 2 c.  2^f - 1 = f P(f), P the interpolant of degree 10 of (2^f - 1) / f at
+// the Chebyshev nodes (relative error 5.1e-17 with these rounded coefficients):
+// no digits are lost near z = 0.  -n is capped so that c stays finite.  The
+// reciprocal takes one step of third order from the hardware's estimate (24
+// bits).  Within 5 units of the last place.  A NaN pre-activation stays NaN.
 template <int ACT>
 __device__ __forceinline__ double act64(double y) {
     if constexpr (ACT == ACT_RELU) {
         return y > 0.0 ? y : 0.0;
     } else {
-        const double n = __builtin_rint(y), f = y - n;
-        double p = 4.45581790833606449e-10;
-        p = fma(p, f, 7.07419429728852106e-09);
-        p = fma(p, f, 1.01780570877339407e-07);
-        p = fma(p, f, 1.32154325359123753e-06);
-        p = fma(p, f, 1.52527338415567733e-05);
-        p = fma(p, f, 1.54035304637243530e-04);
-        p = fma(p, f, 1.33335581464064708e-03);
-        p = fma(p, f, 9.61812910758725638e-03);
-        p = fma(p, f, 5.55041086648216248e-02);
-        p = fma(p, f, 2.40226506959101582e-01);
-        p = fma(p, f, 6.93147180559945286e-01);
-        p = fma(p, f, 1.0);
-        const int e = min((int)n, 1000);
-        const double d = 1.0 + __builtin_amdgcn_ldexp(p, e);
-        double r = __builtin_amdgcn_rcp(d);
-        r = fma(r, fma(-d, r, 1.0), r);
-        return fma(r, fma(-d, r, 1.0), r);
+        const double m = __builtin_rint(-y), f = y + m;
+        double p = 4.4549605981865186e-10;
+        p = fma(p, f, 7.072585949269223e-09);
+        p = fma(p, f, 1.0178062445845774e-07);
+        p = fma(p, f, 1.321544258792169e-06);
+        p = fma(p, f, 1.525273382983612e-05);
+        p = fma(p, f, 1.540353044173605e-04);
+        p = fma(p, f, 1.3333558146416936e-03);
+        p = fma(p, f, 9.618129107606888e-03);
+        p = fma(p, f, 5.55041086648216e-02);
+        p = fma(p, f, 2.4022650695910097e-01);
+        p = fma(p, f, 6.931471805599453e-01);
+        const double c = __builtin_amdgcn_ldexp(1.0, min((int)m, 1000));
+        const double num = fma(p, f, 1.0 - c), d = fma(2.0, c, num);
+        const double r = __builtin_amdgcn_rcp(d), e = fma(-d, r, 1.0);
+        return num * fma(r, fma(e, e, e), r);
     }
 }
 
@@ -268,27 +266,20 @@ void nco_f64_prepare_table(const float* params, int W, int act, int depth, const
     const float* b2b = W2b + W * W;
     const float* W3 = depth == 3 ? b2b + W : b2 + W;
     const float* b3 = W3 + 4 * W;
-    const bool th = act == ACT_TANH;
-    const double kappa = th ? 2.0 / 0.69314718055994530942 : 1.0, fold = th ? -2.0 : 1.0;
+    const double kappa = act == ACT_TANH ? 2.0 / 0.69314718055994530942 : 1.0;
     const int MT = mt_of(W), KS = W / 4;
     double* tab = static_cast<double*>(out);
     int slot_row[KSTEPS][4];
     class_slots(slot_row);
     auto w1 = [&](int k, int h) { return k < 0 || h >= W ? 0.0 : (double)(k < 27 ? W1[k * W + h] : b1[h]); };
-    // Layer fed by activations 1 - 2 r: weights -2 w, bias plus the column sum.
     auto hidden = [&](const float* w, const float* b, double* A, double* bias) {
         for (int u = 0; u < MT; ++u)
             for (int ks = 0; ks < KS; ++ks)
                 for (int lane = 0; lane < 64; ++lane) {
                     const int in = 4 * ks + (lane >> 4), o = 16 * u + (lane & 15);
-                    A[(u * KS + ks) * 64 + lane] = o < W ? kappa * fold * w[in * W + o] : 0.0;
+                    A[(u * KS + ks) * 64 + lane] = o < W ? kappa * w[in * W + o] : 0.0;
                 }
-        for (int o = 0; o < W; ++o) {
-            double s = b[o];
-            if (th)
-                for (int h = 0; h < W; ++h) s += w[h * W + o];
-            bias[o] = kappa * s;
-        }
+        for (int o = 0; o < W; ++o) bias[o] = kappa * b[o];
     };
     for (int t = 0; t < MT; ++t)
         for (int st = 0; st < KSTEPS; ++st)
@@ -298,13 +289,8 @@ void nco_f64_prepare_table(const float* params, int W, int act, int depth, const
     hidden(W2, b2, tab + t64_a2(W), tab + t64_b2(W, depth));
     if (depth == 3) hidden(W2b, b2b, tab + t64_a2b(W), tab + t64_b2b(W, depth));
     for (int o = 0; o < W; ++o)
-        for (int n = 0; n < 4; ++n) tab[t64_w3(W, depth) + o * 4 + n] = fold * (double)W3[o * 4 + n] / NGROUP;
-    for (int n = 0; n < 4; ++n) {
-        double s = b3[n];
-        if (th)
-            for (int h = 0; h < W; ++h) s += W3[h * 4 + n];
-        tab[t64_b3(W, depth) + n] = s;
-    }
+        for (int n = 0; n < 4; ++n) tab[t64_w3(W, depth) + o * 4 + n] = (double)W3[o * 4 + n] / NGROUP;
+    for (int n = 0; n < 4; ++n) tab[t64_b3(W, depth) + n] = b3[n];
     int* gtab = reinterpret_cast<int*>(tab + t64_doubles(W, depth));
     for (int p = 0; p < 6; ++p)
         for (int q = 0; q < 4; ++q)
