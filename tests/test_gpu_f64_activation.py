@@ -39,3 +39,26 @@ def test_small_activations_keep_their_digits(scale, width, depth):
     p[-2] /= np.float32(scale)
     got, want = _rates(params, width, depth)
     assert np.abs(got - want).max() < 1e-13
+
+
+@pytest.mark.parametrize("width,depth", [(8, 2), (20, 2), (32, 2), (32, 3)])
+def test_infinite_and_huge_parameters_saturate(width, depth):
+    """Infinite biases of either sign in every hidden layer, an infinite weight
+    of the density row and weights whose pre-activations pass 2^31 and 2^1000
+    of the exponent's unit: tanh is +-1, the rates those of the oracle."""
+    params = inputs.mlp_params(width, 8, depth=depth).astype(np.float32)
+    p = _parts(params, width, depth)
+    for b in p[1:-1:2]:
+        b[1], b[4] = np.inf, -np.inf
+    p[0][2], p[0][5] = np.inf, -np.inf      # row 0 of W1: the density moment
+    p[1][3], p[1][6], p[1][7] = 1e12, -3e38, 600.0
+    got, want = _rates(params, width, depth)
+    assert np.all(np.isfinite(want)) and np.abs(got - want).max() < 1e-13
+
+
+@pytest.mark.parametrize("width,depth", [(8, 2), (32, 3)])
+def test_nan_parameter_gives_nan(width, depth):
+    params = inputs.mlp_params(width, 8, depth=depth).astype(np.float32)
+    _parts(params, width, depth)[1][3] = np.nan
+    got, want = _rates(params, width, depth)
+    assert np.all(np.isnan(want)) and np.all(np.isnan(got))
