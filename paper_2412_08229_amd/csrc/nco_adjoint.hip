@@ -8,7 +8,7 @@
 // Per node tile of 16 and group element g = (pi, s), in the layout of the
 // forward network (hidden x nodes, lane (q, c) = (lane / 16, lane % 16)
 // holding rows 4 q .. 4 q + 3 of node c):
-//   forward recompute   r_l = act(Z_l)                      (forward weights)
+//   forward recompute   r_l = act(Z_l)
 //   dz_L = dh_L (.) act'(z_L),   dh_L = W3 dtt / 48 (the same for every g)
 //   dh_l-1 = W_l dz_l,   dz_l-1 = dh_l-1 (.) act'(z_l-1)   (products whose
 //         B operands are the previous accumulators, as in the forward)
@@ -19,8 +19,13 @@
 // rows:
 //   dL/dm[src_pi(k)] += (W1 Z_class(k))[k],   dW1[k] += x_pi[k] Z_class(k)^T
 // (the bias row of x_pi gives db1).
-// For tanh, with r = 1 / (1 + 2^(kappa z)): h = 1 - 2 r, act' = 4 r (1 - r);
-// the 4 is folded into the transposed weights and W3 (exactly, a power of 2).
+// For tanh at depth 2, with r = 1 / (1 + 2^(kappa z)): h = 1 - 2 r, act' =
+// 4 r (1 - r); the 4 is folded into the transposed weights and W3 (exactly, a
+// power of 2).  At depth 3 tanh itself on the unfolded weights, act' = 1 - h^2:
+// h = 1 - 2 r is right to 6e-8 of one, and the gradient of a layer fed by small
+// activations would be no better than that over their size.  The
+// group sum H of the output layer's gradient is added up here as well, not
+// unfolded from the forward step's.  It costs 17-25 % of a reverse step: 16^3 63 -> 74 us, 64^3 1707 -> 2139.
 //
 // Products over nodes.  h and dz go through a per-wavefront LDS buffer
 // [hidden][node] of row stride 20: a lane reads the nodes 4 q .. 4 q + 3 of
@@ -47,7 +52,7 @@
 // registers at depth 2, vector units at depth 3) and here: depth 2 tanh 16^3
 // 105 -> 47 us, 32^3 203 -> 154, 64^3 1390 -> 1078, 96^3 4870 -> 3640 (about
 // 60 TFLOP/s of products, 40 % of what a large float32 product reaches);
-// depth 3 tanh 16^3 348 -> 64, 32^3 1537 -> 233, 64^3 11960 -> 1714.
+// depth 3 tanh 16^3 348 -> 74, 32^3 1537 -> 288, 64^3 11960 -> 2139.
 //
 // Networks of at most 20 hidden units (depth 3) lie in the tiles as in the
 // forward step (act_tail): five K-steps and activations instead of eight; the
@@ -105,14 +110,15 @@ __device__ __forceinline__ void wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// act' (without the folded 4) and h from the activation r.
+// act' (for the folded tanh without its 4) and h from the activation r.
 template <int ACT>
 __device__ __forceinline__ float act_slope(float r) {
-    return act_base(ACT) == ACT_RELU ? (r > 0.0f ? 1.0f : 0.0f) : fmaf(-r, r, r);
+    return act_base(ACT) == ACT_RELU ? (r > 0.0f ? 1.0f : 0.0f)
+                                     : fmaf(-r, r, act_base(ACT) == ACT_TANH_FULL ? 1.0f : r);
 }
 template <int ACT>
 __device__ __forceinline__ float act_value(float r) {
-    return act_base(ACT) == ACT_RELU ? r : fmaf(-2.0f, r, 1.0f);
+    return act_base(ACT) == ACT_TANH ? fmaf(-2.0f, r, 1.0f) : r;
 }
 
 __device__ __forceinline__ f32x4 ld4(const float* p) { return *reinterpret_cast<const f32x4*>(p); }
@@ -163,6 +169,8 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(2)))
     constexpr int COPIES = WAVES == 4 ? 1 : WAVES;      // dL/dm sums in LDS
     constexpr int TAF = ta_floats(DEPTH);
     constexpr int ROW = DEPTH == 3 ? NPAR3 : NPAR;
+    constexpr bool FULL = act_base(ACT) == ACT_TANH_FULL;
+    constexpr int FWD = FULL ? ACT - ACT_TANH_FULL + ACT_TANH : ACT;    // the forward step's activation
     __shared__ __align__(16) float tab[TAF + TI_INTS];
     __shared__ __align__(16) float sm[29 * NS];         // [moment row][node]; row 27 = 1, 28 = 0
     __shared__ float sdm[COPIES == 1 ? 32 * NS : COPIES * 29 * NS];   // group sums [32][node], then dL/dm
@@ -239,17 +247,17 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(2)))
             sm[27 * NS + tid] = 1.0f;
             sm[28 * NS + tid] = 0.0f;
         }
-        // Phase B1: group sums and tilde tau, kept by the forward step of this
-        // state (places past the last node read as zero) or computed again,
-        // the same arithmetic in the same order.
+        // Phase B1: group sums (unless they come from phase B3) and tilde tau,
+        // kept by the forward step of this state (places past the last node
+        // read as zero) or computed again, the same arithmetic in the same order.
         if (a.net_sums) {
             for (int e = tid; e < NB * NET_SUMS_PER_NODE; e += THREADS) {
                 const int nd = e / NET_SUMS_PER_NODE, k = e % NET_SUMS_PER_NODE;
                 const float v = first + nd < a.n ? a.net_sums[(size_t)first * NET_SUMS_PER_NODE + e] : 0.0f;
-                if (k < 32)
-                    sdm[k * NS + nd] = v;
-                else
+                if (k >= 32)
                     sw[(k - 32) * NS + nd] = v;
+                else if constexpr (!FULL)
+                    sdm[k * NS + nd] = v;
             }
             __syncthreads();
         } else {
@@ -257,36 +265,53 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(2)))
             if (wave < TILES) {
                 const int node = wave * 16 + c;
                 f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+                // The forward step's weights: the table's, or its own where the
+                // table holds the unfolded ones.
+                const LaneTab lt(table + TAF + TI_INTS, lane);
+                auto fA1 = [&](int t, int st) { return FULL ? lt[LT_A1 + t * KSTEPS + st] : A1(t, st); };
+                auto fA2 = [&](int u, int t, int r) { return FULL ? lt[LT_A2 + u * 8 + t * 4 + r] : A2(u, t, r); };
+                auto fA2b = [&](int v, int t, int r) { return FULL ? lt[LT_A2B + v * 8 + t * 4 + r] : A2b(v, t, r); };
+                auto fB = [&](int off, int word, f32x4(&v)[2]) {
+                    rows(off, v);
+                    if constexpr (FULL)
+#pragma unroll
+                        for (int u = 0; u < 2; ++u)
+#pragma unroll
+                            for (int r = 0; r < 4; ++r) v[u][r] = lt[word + u * 4 + r];
+                };
 #pragma unroll 1
                 for (int p = 0; p < 6; ++p) {
                     const int* __restrict__ ge = ti + TI_GE + (p * 4 + q) * GT_STRIDE;
                     f32x4 Y[8][2], b2[2], b2b[2];
-                    layer1_f32<TAIL>(A1, [&](int st) { return sm[ge[st] * NS + node]; }, Y);
+                    layer1_f32<TAIL>(fA1, [&](int st) { return sm[ge[st] * NS + node]; }, Y);
                     reflections(Y);
-                    rows(TA_B2, b2);
+                    fB(TA_B2, LT_B2, b2);
                     if constexpr (DEPTH == 3)
-                        rows(TA_B2B, b2b);
+                        fB(TA_B2B, LT_B2B, b2b);
                     else
-                        rows(TA_B2, b2b);
-                    hidden_reflections<ACT, DEPTH, 8>(
-                        A2, b2, A2b, b2b, Y, [&]() { fresh_lane(wl); },
-                        [&](int, const f32x4(&z)[2]) { add_act<ACT>(z, acc); });
+                        fB(TA_B2, LT_B2, b2b);
+                    hidden_reflections<FWD, DEPTH, 8>(
+                        fA2, b2, fA2b, b2b, Y, [&]() { fresh_lane(wl); },
+                        [&](int, const f32x4(&z)[2]) { add_act<FWD>(z, acc); });
                 }
                 units_in_order<ACT>(acc, q, c);
+                if constexpr (!FULL)
 #pragma unroll
-                for (int u = 0; u < 2; ++u)
+                    for (int u = 0; u < 2; ++u)
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) sdm[(16 * u + 4 * q + r) * NS + node] = acc[u][r];
+                        for (int r = 0; r < 4; ++r) sdm[(16 * u + 4 * q + r) * NS + node] = acc[u][r];
                 for (int n = 0; n < 4; ++n) {
                     float v = 0.0f;
 #pragma unroll
                     for (int u = 0; u < 2; ++u)
 #pragma unroll
                         for (int r = 0; r < 4; ++r)
-                            v = fmaf(tab[TA_W3F + (16 * u + 4 * q + r) * 4 + n], acc[u][r], v);
+                            v = fmaf(FULL ? lt[LT_W3 + (u * 4 + r) * 4 + n]
+                                          : tab[TA_W3F + (16 * u + 4 * q + r) * 4 + n],
+                                     acc[u][r], v);
                     v += __shfl_xor(v, 16, 64);
                     v += __shfl_xor(v, 32, 64);
-                    if (q == 0) sw[n * NS + node] = v + tab[TA_B3F + n];
+                    if (q == 0) sw[n * NS + node] = v + (FULL ? lt[LT_B3 + n] : tab[TA_B3F + n]);
                 }
             }
             __syncthreads();
@@ -316,20 +341,25 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(2)))
         __syncthreads();
         // Output layer: dW3 = sum (H / 48) dtt^T with H the group sum of the
         // (unfolded) last-layer activations, db3 = sum dtt.
-        if (tid < 132) {
-            const int o = tid >> 2, n = tid & 3;        // o = 32: b3
-            float v = 0.0f;
-            for (int nd = 0; nd < NB; ++nd) {
-                const float d = sw[n * NS + nd];
-                if (o < 32) {
-                    const float acc = sdm[o * NS + nd];
-                    v = fmaf((act_base(ACT) == ACT_RELU ? acc : (float)NGROUP - 2.0f * acc) * (1.0f / NGROUP), d, v);
-                } else {
-                    v += d;
+        auto output_gradient = [&](auto&& H) {
+            if (tid < 132) {
+                const int o = tid >> 2, n = tid & 3;        // o = 32: b3
+                float v = 0.0f;
+                for (int nd = 0; nd < NB; ++nd) {
+                    const float d = sw[n * NS + nd];
+                    if (o < 32)
+                        v = fmaf(H(o, nd) * (1.0f / NGROUP), d, v);
+                    else
+                        v += d;
                 }
+                gW3 += (double)v;
             }
-            gW3 += (double)v;
-        }
+        };
+        if constexpr (!FULL)
+            output_gradient([&](int o, int nd) {
+                const float acc = sdm[o * NS + nd];
+                return act_base(ACT) == ACT_RELU ? acc : (float)NGROUP - 2.0f * acc;
+            });
         __syncthreads();
         for (int e = tid; e < COPIES * 29 * NS; e += THREADS) sdm[e] = 0.0f;
         __syncthreads();
@@ -338,7 +368,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(2)))
         {
             const int base = WAVES == 4 ? wave * 16 : 0, node = base + c;
             float* __restrict__ dmc = sdm + (COPIES == 1 ? 0 : wave * 29 * NS);
-            f32x4 dhl[2];
+            f32x4 dhl[2], hsum[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
             for (int u = 0; u < 2; ++u)
 #pragma unroll
@@ -381,6 +411,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(2)))
                             for (int r = 0; r < act_values(ACT, u); ++r) {
                                 dz[u][r] = dhl[u][r] * act_slope<ACT>(r3[u][r]);
                                 gb2b[u][r] += dz[u][r];
+                                if constexpr (FULL) hsum[u][r] += r3[u][r];
                                 v[u][r] = act_value<ACT>(r2[u][r]);
                             }
                         outer_product<TAIL>(buf, q, c, v, dz, gW2b);
@@ -456,8 +487,21 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(2)))
                     wave_sync();
                 }
             }
+            if constexpr (FULL) {
+                units_in_order<ACT>(hsum, q, c);
+                to_buf(buf, q, c, hsum);
+            }
         }
         __syncthreads();
+        // The group sum, from the wavefront of the node's tile or from the six
+        // that share it.
+        if constexpr (FULL)
+            output_gradient([&](int o, int nd) {
+                float v = bufs[nd >> 4][o * TSTRIDE + (nd & 15)];
+                if constexpr (WAVES != 4)
+                    for (int w = 1; w < WAVES; ++w) v += bufs[w][o * TSTRIDE + nd];
+                return v;
+            });
         if constexpr (COPIES > 1) {
             for (int e = tid; e < Q * NS; e += THREADS) {
                 float t = sdm[e];
@@ -570,7 +614,9 @@ int adjoint_groups(int n) { return std::max(1, std::min(4, n / 65536)); }
 
 }  // namespace
 
-size_t mfma_adjoint_table_bytes(int depth) { return sizeof(float) * ta_floats(depth) + sizeof(int) * TI_INTS; }
+size_t mfma_adjoint_table_bytes(int depth) {
+    return sizeof(float) * (ta_floats(depth) + (depth == 3 ? mfma_lane_table_floats() : 0)) + sizeof(int) * TI_INTS;
+}
 
 void mfma_prepare_adjoint_table(const float* params, int act, int depth, int units, const int (*gsrc)[27],
                                 void* out) {
@@ -586,12 +632,18 @@ void mfma_prepare_adjoint_table(const float* params, int act, int depth, int uni
     const float* W3 = depth == 3 ? b2b + W : b2 + W;
     float* tab = static_cast<float*>(out);
     int* ti = reinterpret_cast<int*>(tab + ta_floats(depth));
-    // The forward weights, folded for the activations as evaluated, from the
-    // forward step's own table (the same roundings).
+    // The forward weights in the order of the forward step's own table: its
+    // very values, or with tanh at depth 3 the unfolded ones, behind which the
+    // forward step's table follows.
+    const bool full = act == ACT_TANH && depth == 3;
     std::vector<float> fwd(mfma_lane_table_floats());
     std::vector<int> gather(mfma_group_table_ints());
-    mfma_prepare_tables(params, act, MLP_PREC_F32, gsrc, fwd.data(), gather.data(), depth, units);
-    const float slope = act == ACT_TANH ? 4.0f : 1.0f;
+    if (depth == 3)
+        mfma_prepare_tables(params, act, MLP_PREC_F32, gsrc, reinterpret_cast<float*>(ti + TI_INTS), gather.data(), depth,
+                            units);
+    mfma_prepare_tables(params, act, full ? MLP_PREC_F32_FULL : MLP_PREC_F32, gsrc, fwd.data(), gather.data(), depth,
+                        units);
+    const float slope = act == ACT_TANH && !full ? 4.0f : 1.0f;
     for (int lane = 0; lane < 64; ++lane) {
         const LaneTabT<float> lt(fwd.data(), lane);
         const int q = lane >> 4, c = lane & 15;
@@ -671,10 +723,10 @@ hipError_t launch_adjoint_mfma(int storage, int act, const void* xin, const floa
 #define ADJN_CASE(SS)                                               \
     case SS:                                                        \
         if (a.depth == 3 && a.units <= 20) {                        \
-            if (act == ACT_TANH) { ADJN_SHAPE(SS, ACT_TANH + UNITS_20, 3) } \
+            if (act == ACT_TANH) { ADJN_SHAPE(SS, ACT_TANH_FULL + UNITS_20, 3) } \
             else { ADJN_SHAPE(SS, ACT_RELU + UNITS_20, 3) }         \
         } else if (a.depth == 3) {                                  \
-            if (act == ACT_TANH) { ADJN_SHAPE(SS, ACT_TANH, 3) }    \
+            if (act == ACT_TANH) { ADJN_SHAPE(SS, ACT_TANH_FULL, 3) } \
             else { ADJN_SHAPE(SS, ACT_RELU, 3) }                    \
         } else {                                                    \
             if (act == ACT_TANH) { ADJN_SHAPE(SS, ACT_TANH, 2) }    \
