@@ -151,7 +151,9 @@ int nco_set_stochastic_rounding(nco_lattice* lat, int enable, unsigned seed);
  * when both fit.  Where they are kept (default budget 4 GiB), the adjoint
  * reads the group sums of the last hidden layer and the pre-squash outputs
  * instead of running the network forward again; the gradient is the same
- * bit for bit.  With K = 1 every state is a checkpoint, nothing is
+ * bit for bit, also where device memory is too short to keep them (values
+ * already kept are given up when another buffer of the lattice needs the
+ * room).  With K = 1 every state is a checkpoint, nothing is
  * recomputed, and every adjoint reads kept values (T x 144 bytes per node
  * beside the T checkpoints).  0 switches it off.  The recompute's share
  * takes effect at the next nco_backward, the segment ends' at the next

@@ -296,6 +296,52 @@ int maybe_check(nco_lattice* lat, hipStream_t st) {
 
 // Host-transfer staging of at least `per_node` doubles per node, grown on
 // demand (4 for velocity and density fields, 27 for populations).
+// Frees the kept network values, without which the reverse mode runs the
+// network again.
+hipError_t drop_kept_values(nco_lattice* lat) {
+    if (hipError_t e = hipStreamSynchronize(lat->stream)) return e;
+    for (float** b : {&lat->net_sums, &lat->net_ends}) {
+        if (*b)
+            if (hipError_t e = hipFree(*b)) return e;
+        *b = nullptr;
+    }
+    lat->net_sums_floats = lat->net_ends_floats = 0;
+    lat->rec_ends = false;
+    return hipSuccess;
+}
+
+// Device memory that a call needs: where it is short, the kept network values
+// make room.
+template <typename T>
+hipError_t lat_malloc(nco_lattice* lat, T** p, size_t bytes) {
+    const hipError_t e = hipMalloc(p, bytes);
+    if (e != hipErrorOutOfMemory || !(lat->net_sums || lat->net_ends)) return e;
+    (void)hipGetLastError();
+    if (hipError_t d = drop_kept_values(lat)) return d;
+    return hipMalloc(p, bytes);
+}
+
+// Memory for kept network values in *buf, at least `need` floats; ok = false
+// where there is none.
+int kept_buffer(nco_lattice* lat, float** buf, size_t* floats, size_t need, bool* ok) {
+    *ok = true;
+    if (*floats >= need) return NCO_OK;
+    HIP_TRY(hipStreamSynchronize(lat->stream));
+    if (*buf) HIP_TRY(hipFree(*buf));
+    *buf = nullptr;
+    *floats = 0;
+    const hipError_t e = hipMalloc(buf, sizeof(float) * need);
+    if (e == hipErrorOutOfMemory) {
+        (void)hipGetLastError();
+        *buf = nullptr;
+        *ok = false;
+        return NCO_OK;
+    }
+    HIP_TRY(e);
+    *floats = need;
+    return NCO_OK;
+}
+
 int ensure_staging(nco_lattice* lat, int per_node) {
     if (lat->staging_per_node >= per_node) return NCO_OK;
     if (lat->staging) {
@@ -304,7 +350,7 @@ int ensure_staging(nco_lattice* lat, int per_node) {
         lat->staging = nullptr;
         lat->staging_per_node = 0;
     }
-    HIP_TRY(hipMalloc(&lat->staging, sizeof(double) * per_node * (size_t)lat->n));
+    HIP_TRY(lat_malloc(lat, &lat->staging, sizeof(double) * per_node * (size_t)lat->n));
     lat->staging_per_node = per_node;
     return NCO_OK;
 }
@@ -1015,10 +1061,11 @@ int nco_set_forcing_ex(nco_lattice* lat, int n_modes, const int* k, const double
             }
         }
     }
-    HIP_TRY(hipMalloc(&lat->d_force, 3 * (size_t)lat->n * (lat->storage == NCO_F64 ? sizeof(double) : sizeof(float))));
+    HIP_TRY(lat_malloc(lat, &lat->d_force,
+                       3 * (size_t)lat->n * (lat->storage == NCO_F64 ? sizeof(double) : sizeof(float))));
     lat->force_kx = kx_max;
-    HIP_TRY(hipMalloc(&lat->d_fk, sizeof(int) * 3 * n_modes));
-    HIP_TRY(hipMalloc(&lat->d_fhat, sizeof(double) * fh.size()));
+    HIP_TRY(lat_malloc(lat, &lat->d_fk, sizeof(int) * 3 * n_modes));
+    HIP_TRY(lat_malloc(lat, &lat->d_fhat, sizeof(double) * fh.size()));
     HIP_TRY(hipMemcpyAsync(lat->d_fk, k, sizeof(int) * 3 * n_modes, hipMemcpyHostToDevice, lat->stream));
     HIP_TRY(hipMemcpyAsync(lat->d_fhat, fh.data(), sizeof(double) * fh.size(), hipMemcpyHostToDevice, lat->stream));
     const ModeLayout layout(k, phase_rule ? n_modes : 0, lat->nx, lat->ny, lat->nz);
@@ -1029,13 +1076,13 @@ int nco_set_forcing_ex(nco_lattice* lat, int n_modes, const int* k, const double
             dr[2 * e] = M_PI * draws[3 * e];
             dr[2 * e + 1] = 2.0 * M_PI * draws[3 * e + 1];
         }
-        HIP_TRY(hipMalloc(&lat->d_fbasis, sizeof(double) * basis.size()));
-        HIP_TRY(hipMalloc(&lat->d_fdraw, sizeof(double) * dr.size()));
-        HIP_TRY(hipMalloc(&lat->d_fpart, sizeof(double) * 6 * (size_t)n_modes *
-                                              mode_partial_blocks(lat->nx, lat->ny, lat->nz)));
-        HIP_TRY(hipMalloc(&lat->d_fhat_cur, sizeof(double) * 6 * (size_t)n_modes));
-        HIP_TRY(hipMalloc(&lat->d_fduhat, sizeof(double) * 6 * (size_t)n_modes));
-        HIP_TRY(hipMalloc(&lat->d_flist, sizeof(int) * layout.ints.size()));
+        HIP_TRY(lat_malloc(lat, &lat->d_fbasis, sizeof(double) * basis.size()));
+        HIP_TRY(lat_malloc(lat, &lat->d_fdraw, sizeof(double) * dr.size()));
+        HIP_TRY(lat_malloc(lat, &lat->d_fpart, sizeof(double) * 6 * (size_t)n_modes *
+                                                    mode_partial_blocks(lat->nx, lat->ny, lat->nz)));
+        HIP_TRY(lat_malloc(lat, &lat->d_fhat_cur, sizeof(double) * 6 * (size_t)n_modes));
+        HIP_TRY(lat_malloc(lat, &lat->d_fduhat, sizeof(double) * 6 * (size_t)n_modes));
+        HIP_TRY(lat_malloc(lat, &lat->d_flist, sizeof(int) * layout.ints.size()));
         lat->flist_groups = layout.groups;
         lat->flist_chunks = layout.chunks;
         HIP_TRY(hipMemcpyAsync(lat->d_flist, layout.ints.data(), sizeof(int) * layout.ints.size(),
@@ -1099,30 +1146,15 @@ int forward_record(nco_lattice* lat, int nsteps, int ckpt_every, int every, doub
             if (lat->d_phist) HIP_TRY(hipFree(lat->d_phist));
             lat->d_phist = nullptr;
             lat->phist_cap = 0;
-            HIP_TRY(hipMalloc(&lat->d_phist, sizeof(double) * need));
+            HIP_TRY(lat_malloc(lat, &lat->d_phist, sizeof(double) * need));
             lat->phist_cap = need;
         }
     }
     const int ncp = (nsteps + ckpt_every - 1) / ckpt_every;
     while ((int)lat->ckpt.size() < ncp) {
         void* p = nullptr;
-        HIP_TRY(hipMalloc(&p, lat->pop_bytes));
+        HIP_TRY(lat_malloc(lat, &p, lat->pop_bytes));
         lat->ckpt.push_back(p);
-    }
-    // The last step of each segment keeps its network values for the adjoint
-    // of its state (no recomputed step precedes that adjoint) when they fit
-    // the budget beside the recompute's K - 1 states.
-    const size_t stride = net_values_stride(lat);
-    const size_t ends_floats = (size_t)ncp * stride;
-    lat->rec_ends = net_values_apply(lat) &&
-                    ((size_t)(ckpt_every - 1) * stride + ends_floats) * sizeof(float) <= lat->net_cache_bytes;
-    if (lat->rec_ends && lat->net_ends_floats < ends_floats) {
-        HIP_TRY(hipStreamSynchronize(lat->stream));
-        if (lat->net_ends) HIP_TRY(hipFree(lat->net_ends));
-        lat->net_ends = nullptr;
-        lat->net_ends_floats = 0;
-        HIP_TRY(hipMalloc(&lat->net_ends, sizeof(float) * ends_floats));
-        lat->net_ends_floats = ends_floats;
     }
     const int nk = every > 0 ? nsteps / every + 1 : 0;
     if (nk > lat->d_k_cap) {
@@ -1131,9 +1163,18 @@ int forward_record(nco_lattice* lat, int nsteps, int ckpt_every, int every, doub
         if (lat->d_k) HIP_TRY(hipFree(lat->d_k));
         lat->d_k = nullptr;
         lat->d_k_cap = 0;
-        HIP_TRY(hipMalloc(&lat->d_k, sizeof(double) * 5 * nk));
+        HIP_TRY(lat_malloc(lat, &lat->d_k, sizeof(double) * 5 * nk));
         lat->d_k_cap = nk;
     }
+    // The last step of each segment keeps its network values for the adjoint
+    // of its state (no recomputed step precedes that adjoint) when they fit
+    // the budget beside the recompute's K - 1 states, and the memory.
+    const size_t stride = net_values_stride(lat);
+    const size_t ends_floats = (size_t)ncp * stride;
+    lat->rec_ends = net_values_apply(lat) &&
+                    ((size_t)(ckpt_every - 1) * stride + ends_floats) * sizeof(float) <= lat->net_cache_bytes;
+    if (lat->rec_ends)
+        if (int rc = kept_buffer(lat, &lat->net_ends, &lat->net_ends_floats, ends_floats, &lat->rec_ends)) return rc;
     double* d_k = lat->d_k;
     auto sample = [&](int m) -> int {
         HIP_TRY(launch_global_sums(lat->storage, lat->f[lat->cur], lat->partial, d_k + 5 * m, lat->n, lat->stream));
@@ -1212,7 +1253,7 @@ int backward(nco_lattice* lat, const double* dL_dk, int every, const double* dL_
         if (nbins != spectrum_bins(lat->nx)) return fail(NCO_E_INVALID, "nbins must be %d", spectrum_bins(lat->nx));
     }
     for (int b = 0; b < 2; ++b)
-        if (!lat->lam[b]) HIP_TRY(hipMalloc(&lat->lam[b], sizeof(float) * nf));
+        if (!lat->lam[b]) HIP_TRY(lat_malloc(lat, &lat->lam[b], sizeof(float) * nf));
     // Vector-unit adjoint for NCO_MLP_F32, matrix-core adjoint for the others.
     const bool mfma = lat->mlp_prec != NCO_MLP_F32 && lat->adj_tab;
     const int npar = adjoint_param_count_depth(lat->depth);
@@ -1225,7 +1266,7 @@ int backward(nco_lattice* lat, const double* dL_dk, int every, const double* dL_
             if (lat->adj_partial64) HIP_TRY(hipFree(lat->adj_partial64));
             lat->adj_partial64 = nullptr;
             lat->adj_partial64_doubles = 0;
-            HIP_TRY(hipMalloc(&lat->adj_partial64, sizeof(double) * rows));
+            HIP_TRY(lat_malloc(lat, &lat->adj_partial64, sizeof(double) * rows));
             lat->adj_partial64_doubles = rows;
         }
         HIP_TRY(launch_fill_f64(lat->adj_partial64, (size_t)nblk * npar, 0.0, lat->stream));
@@ -1234,7 +1275,7 @@ int backward(nco_lattice* lat, const double* dL_dk, int every, const double* dL_
         if (lat->adj_partial) HIP_TRY(hipFree(lat->adj_partial));
         lat->adj_partial = nullptr;
         lat->adj_partial_floats = 0;
-        HIP_TRY(hipMalloc(&lat->adj_partial, sizeof(float) * (size_t)nblk * npar));
+        HIP_TRY(lat_malloc(lat, &lat->adj_partial, sizeof(float) * (size_t)nblk * npar));
         lat->adj_partial_floats = (size_t)nblk * npar;
     }
     if (!mfma && adjoint_xwork_floats(lat->n, lat->depth) > lat->adj_xwork_floats) {
@@ -1243,10 +1284,16 @@ int backward(nco_lattice* lat, const double* dL_dk, int every, const double* dL_
         lat->adj_xwork = nullptr;
         lat->adj_xwork_floats = 0;
         const size_t nx = adjoint_xwork_floats(lat->n, lat->depth);
-        HIP_TRY(hipMalloc(&lat->adj_xwork, sizeof(float) * nx));
+        HIP_TRY(lat_malloc(lat, &lat->adj_xwork, sizeof(float) * nx));
         lat->adj_xwork_floats = nx;
     }
-    if (!lat->d_grad) HIP_TRY(hipMalloc(&lat->d_grad, sizeof(double) * adjoint_param_count_depth(3)));
+    if (!lat->d_grad) HIP_TRY(lat_malloc(lat, &lat->d_grad, sizeof(double) * adjoint_param_count_depth(3)));
+    // States 1..K-1 of a segment (its state 0 is the checkpoint).
+    while ((int)lat->seg.size() < lat->rec_every) {
+        void* p = nullptr;
+        if (!lat->seg.empty()) HIP_TRY(lat_malloc(lat, &p, lat->pop_bytes));
+        lat->seg.push_back(p);
+    }
     // Float32 matrix-core networks: each recomputed forward step keeps its
     // network values (group sums and tilde tau), and the adjoint of that
     // step reads them instead of running the network forward again (the
@@ -1254,33 +1301,24 @@ int backward(nco_lattice* lat, const double* dL_dk, int every, const double* dL_
     // bit).  The last state of a segment has no recomputed step and runs it.
     // The last state of a segment reads what the recorded run kept for it
     // (rec_ends), if it did.
-    const size_t sums_stride = net_values_stride(lat);
-    const bool keep_sums = mfma && net_values_apply(lat) && lat->rec_every > 1 &&
-                           (size_t)(lat->rec_every - 1) * sums_stride * sizeof(float) <= lat->net_cache_bytes;
-    if (keep_sums && lat->net_sums_floats < (size_t)(lat->rec_every - 1) * sums_stride) {
-        HIP_TRY(hipStreamSynchronize(lat->stream));
-        if (lat->net_sums) HIP_TRY(hipFree(lat->net_sums));
-        lat->net_sums = nullptr;
-        lat->net_sums_floats = 0;
-        HIP_TRY(hipMalloc(&lat->net_sums, sizeof(float) * (size_t)(lat->rec_every - 1) * sums_stride));
-        lat->net_sums_floats = (size_t)(lat->rec_every - 1) * sums_stride;
-    }
-    auto sums_of = [&](int i) { return keep_sums ? lat->net_sums + (size_t)i * sums_stride : nullptr; };
+    const size_t sums_stride = net_values_stride(lat), sums_floats = (size_t)(lat->rec_every - 1) * sums_stride;
+    bool keep_sums = mfma && net_values_apply(lat) && lat->rec_every > 1 &&
+                     sums_floats * sizeof(float) <= lat->net_cache_bytes;
+    if (keep_sums)
+        if (int rc = kept_buffer(lat, &lat->net_sums, &lat->net_sums_floats, sums_floats, &keep_sums)) return rc;
+    auto sums_of = [&](int i) {
+        return keep_sums && lat->net_sums ? lat->net_sums + (size_t)i * sums_stride : nullptr;
+    };
     auto end_of = [&](int sgi) { return lat->rec_ends ? lat->net_ends + (size_t)sgi * sums_stride : nullptr; };
-    // States 1..K-1 of a segment (its state 0 is the checkpoint).
-    while ((int)lat->seg.size() < lat->rec_every) {
-        void* p = nullptr;
-        if (!lat->seg.empty()) HIP_TRY(hipMalloc(&p, lat->pop_bytes));
-        lat->seg.push_back(p);
-    }
     // Adjoint of the final state.
     float* lin = lat->lam[0];
     float* lout = lat->lam[1];
     HIP_TRY(launch_fill_f32(lin, nf, 0.0f, lat->stream));
     if (dL_dE) {
         const int nn = lat->nx;
-        if (!lat->spec_work) HIP_TRY(hipMalloc(&lat->spec_work, spectrum_workspace_bytes(nn) + 256 * sizeof(double) * 8));
-        if (!lat->d_dE) HIP_TRY(hipMalloc(&lat->d_dE, sizeof(double) * 2048));
+        if (!lat->spec_work)
+            HIP_TRY(lat_malloc(lat, &lat->spec_work, spectrum_workspace_bytes(nn) + 256 * sizeof(double) * 8));
+        if (!lat->d_dE) HIP_TRY(lat_malloc(lat, &lat->d_dE, sizeof(double) * 2048));
         if (nbins > 2048) return fail(NCO_E_UNSUPPORTED, "too many shells");
         HIP_TRY(hipMemcpyAsync(lat->d_dE, dL_dE, sizeof(double) * nbins, hipMemcpyHostToDevice, lat->stream));
         HIP_TRY(launch_spectrum_adjoint(lat->storage, lat->f[lat->cur], nn, lat->spec_work, lat->d_dE, nbins, lin,
@@ -1440,7 +1478,8 @@ int nco_energy_spectrum(nco_lattice* lat, double* E, int nbins) {
     const int n = lat->nx;
     if (nbins != spectrum_bins(n)) return fail(NCO_E_INVALID, "nbins must be %d for n = %d", spectrum_bins(n), n);
     if (int rc = set_device(lat)) return rc;
-    if (!lat->spec_work) HIP_TRY(hipMalloc(&lat->spec_work, spectrum_workspace_bytes(n) + 256 * sizeof(double) * 8));
+    if (!lat->spec_work)
+        HIP_TRY(lat_malloc(lat, &lat->spec_work, spectrum_workspace_bytes(n) + 256 * sizeof(double) * 8));
     double* E_dev = reinterpret_cast<double*>(static_cast<char*>(lat->spec_work) + spectrum_workspace_bytes(n));
     if (nbins > 256 * 8) return fail(NCO_E_UNSUPPORTED, "too many shells");
     HIP_TRY(launch_energy_spectrum(lat->storage, lat->f[lat->cur], n, lat->spec_work, E_dev, nbins, lat->stream));
