@@ -12,6 +12,21 @@ STATE = 54 * N ** 3             # bytes of a BF16-deviation state
 KEPT = 144 * N ** 3             # bytes of network values of one
 
 
+def _fill(torch, spare, chunk=32 << 20):
+    """Tensors that leave ``spare`` bytes of the device's memory: chunks up to
+    the first refusal, then as many given back."""
+    big = torch.cuda.mem_get_info()[0] - spare - (1 << 30)
+    hold = [torch.empty(big, dtype=torch.uint8, device="cuda")]
+    for _ in range(2000):
+        try:
+            hold.append(torch.empty(chunk, dtype=torch.uint8, device="cuda"))
+        except torch.cuda.OutOfMemoryError:
+            break
+    del hold[len(hold) - -(-spare // chunk):]
+    torch.cuda.empty_cache()
+    return hold
+
+
 def _run(T, K, cache, spare=None):
     """Gradient of a recorded run; with ``spare`` bytes of the device's memory
     left once the lattice stands."""
@@ -28,7 +43,7 @@ def _run(T, K, cache, spare=None):
         lat.sync()
         try:
             if spare is not None:
-                hold = torch.empty(torch.cuda.mem_get_info()[0] - spare, dtype=torch.uint8, device="cuda")
+                hold = _fill(torch, spare)
             lat.forward_record(T, K)
             return lat.backward(dL_df=w)[0]
         finally:
