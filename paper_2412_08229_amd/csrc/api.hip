@@ -177,6 +177,8 @@ struct nco_lattice {
     // arithmetic (mfma_tab; not for NCO_MLP_F32) and in full float32.
     void* mfma_tab = nullptr;
     void* full_tab = nullptr;
+    bool full_ready = false;      // full_tab holds the present weights (built when first needed)
+    std::vector<float> net_host;  // their parameters at width 32
     void* f64_tab = nullptr;      // network table of float64 storage
     int width = 0, act = 0, mlp_prec = 0;
     int depth = 2;                // hidden layers
@@ -389,6 +391,18 @@ bool use_mfma(const nco_lattice* lat) {
     return lat->op == NCO_OP_NCO && lat->mlp_prec != NCO_MLP_F32 && lat->mfma_tab;
 }
 bool use_f64_net(const nco_lattice* lat) { return lat->op == NCO_OP_NCO && lat->storage == NCO_F64; }
+const GroupAction& group_action() {
+    static const GroupAction G = build_group_action();
+    return G;
+}
+// Lane and group table of the lattice's network in arithmetic `prec`.
+std::vector<char> net_table(const nco_lattice* lat, int prec) {
+    const size_t lane = sizeof(float) * mfma_lane_table_floats();
+    std::vector<char> tab(lane + sizeof(int) * mfma_group_table_ints());
+    mfma_prepare_tables(lat->net_host.data(), lat->act, prec, group_action().src, reinterpret_cast<float*>(tab.data()),
+                        reinterpret_cast<int*>(tab.data() + lane), lat->depth, lat->user_width);
+    return tab;
+}
 // Matrix-core network of a step or of rates, in the lattice's arithmetic or in
 // full float32.
 hipError_t launch_net(const nco_lattice* lat, int prec, const void* fin, void* fout, const StepArgs& a,
@@ -684,7 +698,7 @@ int nco_set_net_weights_depth(nco_lattice* lat, int depth, int width, int act, i
         params = padded3.data();
     }
     const int W = depth == 3 ? 32 : width;
-    static const GroupAction G = build_group_action();
+    const GroupAction& G = group_action();
     std::vector<float> buf(net_floats_depth(W, depth), 0.0f);
     const float* W1 = params;
     const float* b1 = W1 + 27 * W;
@@ -712,66 +726,75 @@ int nco_set_net_weights_depth(nco_lattice* lat, int depth, int width, int act, i
         if (lat->f64_tab) HIP_TRY(hipFree(lat->f64_tab));
         lat->f64_tab = nullptr;
     }
+    // Uploads in stream order and one wait for all of them at the end, which
+    // their host copies outlive (also where a call in between fails).
+    std::vector<std::vector<char>> held;
+    struct Wait {
+        hipStream_t st;
+        bool pending = true;
+        ~Wait() {
+            if (pending) (void)hipStreamSynchronize(st);
+        }
+    } wait{lat->stream};
+    auto upload = [&](void** dst, size_t capacity, std::vector<char>&& data) -> int {
+        if (!*dst) HIP_TRY(lat_malloc(lat, dst, capacity));
+        held.push_back(std::move(data));
+        HIP_TRY(hipMemcpyAsync(*dst, held.back().data(), held.back().size(), hipMemcpyHostToDevice, lat->stream));
+        return NCO_OK;
+    };
     if (lat->storage == NCO_F64) {
         std::vector<char> tab(nco_f64_table_bytes(W, depth));
         nco_f64_prepare_table(params, W, act, depth, G.src, tab.data());
-        if (!lat->f64_tab) HIP_TRY(hipMalloc(&lat->f64_tab, tab.size()));
-        HIP_TRY(hipMemcpyAsync(lat->f64_tab, tab.data(), tab.size(), hipMemcpyHostToDevice, lat->stream));
-        HIP_TRY(hipStreamSynchronize(lat->stream));
+        const size_t bytes = tab.size();
+        if (int rc = upload(&lat->f64_tab, bytes, std::move(tab))) return rc;
     }
-    if (!lat->net) HIP_TRY(hipMalloc(&lat->net, sizeof(float) * buf.size()));
-    HIP_TRY(hipMemcpyAsync(lat->net, buf.data(), sizeof(float) * buf.size(), hipMemcpyHostToDevice,
-                           lat->stream));
-    HIP_TRY(hipStreamSynchronize(lat->stream));
+    const char* bytes = reinterpret_cast<const char*>(buf.data());
+    if (int rc = upload(reinterpret_cast<void**>(&lat->net), sizeof(float) * buf.size(),
+                        std::vector<char>(bytes, bytes + sizeof(float) * buf.size())))
+        return rc;
     lat->width = W;
     lat->user_width = width;
     lat->depth = depth;
     lat->act = act;
     lat->mlp_prec = mlp_prec;
     lat->rec_steps = -1;  // a recorded run used the previous network
-    {
+    lat->full_ready = false;
+    if (!lat->d_gsrc) {
         // Group table of the adjoint: source row | sign bit per element and row.
-        int gs[48 * 27];
+        std::vector<char> gs(sizeof(int) * NGROUP * 27);
         for (int g = 0; g < NGROUP; ++g)
             for (int k = 0; k < 27; ++k)
-                gs[g * 27 + k] = G.src[g][k] | (G.sign[g][k] < 0.0f ? (int)0x80000000 : 0);
-        if (!lat->d_gsrc) HIP_TRY(hipMalloc(&lat->d_gsrc, sizeof(gs)));
-        HIP_TRY(hipMemcpyAsync(lat->d_gsrc, gs, sizeof(gs), hipMemcpyHostToDevice, lat->stream));
-        HIP_TRY(hipStreamSynchronize(lat->stream));
+                reinterpret_cast<int*>(gs.data())[g * 27 + k] =
+                    G.src[g][k] | (G.sign[g][k] < 0.0f ? (int)0x80000000 : 0);
+        const size_t gb = gs.size();
+        if (int rc = upload(reinterpret_cast<void**>(&lat->d_gsrc), gb, std::move(gs))) return rc;
     }
     if (lat->storage != NCO_F64) {
-        const size_t nf = mfma_lane_table_floats(), ni = mfma_group_table_ints();
-        std::vector<char> tab(sizeof(float) * nf + sizeof(int) * ni);
         // Narrower networks run zero-padded to width 32: a padded hidden unit
         // has zero weights and bias and zero outgoing weights, so it adds
         // nothing to the next layer for either activation.
-        std::vector<float> padded;
-        const float* p32 = params;
-        if (W < 32) {
-            padded = pad_params(params, W, 2, 32);
-            p32 = padded.data();
+        lat->net_host = W < 32 ? pad_params(params, W, 2, 32) : std::vector<float>(params, params + n_params_depth(W, depth));
+        std::vector<char> tab = net_table(lat, mlp_prec);
+        const char* folded = nullptr;               // the float32 network's table, if that is it
+        const size_t tb = tab.size();
+        if (mlp_prec == NCO_MLP_F32) {
+            if (int rc = upload(&lat->full_tab, tb, std::move(tab))) return rc;
+            lat->full_ready = true;
+        } else {
+            if (int rc = upload(&lat->mfma_tab, tb, std::move(tab))) return rc;
+            if (mlp_prec == NCO_MLP_F32_MFMA) folded = held.back().data();
         }
-        auto upload = [&](int prec, void** dst) -> int {
-            mfma_prepare_tables(p32, act, prec, G.src, reinterpret_cast<float*>(tab.data()),
-                                reinterpret_cast<int*>(tab.data() + sizeof(float) * nf), depth, width);
-            if (!*dst) HIP_TRY(hipMalloc(dst, tab.size()));
-            HIP_TRY(hipMemcpyAsync(*dst, tab.data(), tab.size(), hipMemcpyHostToDevice, lat->stream));
-            HIP_TRY(hipStreamSynchronize(lat->stream));
-            return NCO_OK;
-        };
-        if (int rc = upload(NCO_MLP_F32, &lat->full_tab)) return rc;
-        if (mlp_prec != NCO_MLP_F32)
-            if (int rc = upload(mlp_prec, &lat->mfma_tab)) return rc;
         if (W == 32 && mlp_prec != NCO_MLP_F32) {
             // Reverse mode on the matrix cores, float32 (also for a bf16 or
             // split network), whose table holds the float32 forward weights.
             std::vector<char> at(mfma_adjoint_table_bytes(depth));
-            mfma_prepare_adjoint_table(params, act, depth, width, G.src, at.data());
-            if (!lat->adj_tab) HIP_TRY(hipMalloc(&lat->adj_tab, mfma_adjoint_table_bytes(3)));
-            HIP_TRY(hipMemcpyAsync(lat->adj_tab, at.data(), at.size(), hipMemcpyHostToDevice, lat->stream));
-            HIP_TRY(hipStreamSynchronize(lat->stream));
+            mfma_prepare_adjoint_table(params, act, depth, width, G.src, reinterpret_cast<const float*>(folded),
+                                       at.data());
+            if (int rc = upload(&lat->adj_tab, mfma_adjoint_table_bytes(3), std::move(at))) return rc;
         }
     }
+    HIP_TRY(hipStreamSynchronize(lat->stream));
+    wait.pending = false;
     return NCO_OK;
 }
 
@@ -1447,6 +1470,16 @@ int nco_read_rates(nco_lattice* lat, double* omega) {
     if (int rc = set_device(lat)) return rc;
     if (int rc = ensure_staging(lat, 4)) return rc;
     const StepArgs a = step_args(lat);
+    // Under another operator the network runs in full float32, whose table
+    // only these readouts and the NCO_MLP_F32 network need.
+    std::vector<char> tab;
+    if (lat->storage != NCO_F64 && !use_mfma(lat) && !lat->full_ready) {
+        tab = net_table(lat, NCO_MLP_F32);
+        if (!lat->full_tab) HIP_TRY(lat_malloc(lat, &lat->full_tab, tab.size()));
+        HIP_TRY(hipMemcpyAsync(lat->full_tab, tab.data(), tab.size(), hipMemcpyHostToDevice, lat->stream));
+        HIP_TRY(hipStreamSynchronize(lat->stream));
+        lat->full_ready = true;
+    }
     if (lat->storage == NCO_F64)
         HIP_TRY(launch_nco_f64(lat->f[lat->cur], nullptr, a, lat->f64_tab, lat->staging, lat->stream));
     else

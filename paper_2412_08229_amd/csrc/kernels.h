@@ -229,13 +229,14 @@ hipError_t launch_force_phase_adjoint(int storage, const void* x, const float* l
                                       hipStream_t st);
 
 // The same adjoint on the matrix cores (nco_adjoint.hip), depth 2 or 3:
-// table as mfma_prepare_adjoint_table leaves it (params: a width-32 network);
+// table as mfma_prepare_adjoint_table leaves it (params: a width-32 network;
+// folded: the float32 network's lane and group table, built here if null);
 // the step's parameter gradient is added to partial[block][row], rows of
 // adjoint_param_count_depth(depth).  With a.net_sums the network values the
 // forward step kept are read instead of computed again.
 size_t mfma_adjoint_table_bytes(int depth);
 void mfma_prepare_adjoint_table(const float* params, int act, int depth, int units, const int (*gsrc)[27],
-                                void* table);
+                                const float* folded, void* table);
 int adjoint_mfma_blocks(int n);
 hipError_t launch_adjoint_mfma(int storage, int act, const void* xin, const float* lam_in, float* lam_out,
                                const StepArgs& a, const void* table, double* partial, hipStream_t st);

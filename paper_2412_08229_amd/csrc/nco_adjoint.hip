@@ -60,6 +60,7 @@
 // read).  Width 20, ReLU: 16^3 61 -> 52 us, 32^3 219 -> 175, 64^3 1606 -> 1264.
 #include <algorithm>
 #include <cmath>
+#include <cstring>
 #include <vector>
 
 #include "adjoint.h"
@@ -619,7 +620,7 @@ size_t mfma_adjoint_table_bytes(int depth) {
 }
 
 void mfma_prepare_adjoint_table(const float* params, int act, int depth, int units, const int (*gsrc)[27],
-                                void* out) {
+                                const float* folded, void* out) {
     const int W = MW;
     const bool u20 = units <= 20;
     auto weight = [&](const float* Wl, int j, int o) { return j < 0 || o < 0 ? 0.0f : Wl[j * W + o]; };
@@ -636,16 +637,22 @@ void mfma_prepare_adjoint_table(const float* params, int act, int depth, int uni
     // very values, or with tanh at depth 3 the unfolded ones, behind which the
     // forward step's table follows.
     const bool full = act == ACT_TANH && depth == 3;
-    std::vector<float> fwd(mfma_lane_table_floats());
-    std::vector<int> gather(mfma_group_table_ints());
-    if (depth == 3)
-        mfma_prepare_tables(params, act, MLP_PREC_F32, gsrc, reinterpret_cast<float*>(ti + TI_INTS), gather.data(), depth,
-                            units);
-    mfma_prepare_tables(params, act, full ? MLP_PREC_F32_FULL : MLP_PREC_F32, gsrc, fwd.data(), gather.data(), depth,
-                        units);
+    const size_t nf = mfma_lane_table_floats(), ni = mfma_group_table_ints();
+    std::vector<float> own(folded ? 0 : nf + ni), unfolded(full ? nf + ni : 0);     // floats, then ints
+    auto build = [&](int prec, std::vector<float>& t) {
+        mfma_prepare_tables(params, act, prec, gsrc, t.data(), reinterpret_cast<int*>(t.data() + nf), depth, units);
+    };
+    if (!folded) {
+        build(MLP_PREC_F32, own);
+        folded = own.data();
+    }
+    if (full) build(MLP_PREC_F32_FULL, unfolded);
+    const float* fwd = full ? unfolded.data() : folded;
+    const int* gather = reinterpret_cast<const int*>(folded + nf);
+    if (depth == 3) std::memcpy(ti + TI_INTS, folded, sizeof(float) * nf);
     const float slope = act == ACT_TANH && !full ? 4.0f : 1.0f;
     for (int lane = 0; lane < 64; ++lane) {
-        const LaneTabT<float> lt(fwd.data(), lane);
+        const LaneTab lt(fwd, lane);
         const int q = lane >> 4, c = lane & 15;
         for (int t = 0; t < 2; ++t)
             for (int st = 0; st < KSTEPS; ++st) tab[TA_A1 + (t * KSTEPS + st) * 64 + lane] = lt[LT_A1 + t * KSTEPS + st];
