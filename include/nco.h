@@ -185,9 +185,10 @@ int nco_set_rates(nco_lattice* lat, const double omega_high[4]);
  * m^(g) = M Pi_g f in the row order of M; the output is tilde tau_n for the
  * orders 3..6.  width must be 8, 16, 20 or 32 (the paper's network is
  * width 20 with ReLU).  NCO_MLP_F32_MFMA, NCO_MLP_BF16 and
- * NCO_MLP_F32_SPLIT need float32 or 16-bit storage and run narrower networks
- * zero-padded to width 32, at the cost of width 32 (NCO_MLP_F32: to 16 or
- * 32). */
+ * NCO_MLP_F32_SPLIT need float32 or 16-bit storage.  In those storages narrower
+ * networks are stored zero-padded to width 32 and run in the form of 20 units,
+ * five activations per layer where width 32 has eight (NCO_MLP_F32 up to width 16
+ * in the form of 16, four). */
 int nco_set_net_weights(nco_lattice* lat, int width, int act, int mlp_prec,
                         const float* params, size_t n_params);
 
@@ -196,8 +197,9 @@ int nco_set_net_weights(nco_lattice* lat, int width, int act, int mlp_prec,
  * 27 -> width -> width -> width -> 4, params in the order W1[27][width],
  * b1, W2[width][width], b2, W2b[width][width], b2b, W3[width][4], b3
  * (n_params = width*(27 + 2 width + 4) + 3 width + 4).  Depth 3 runs in
- * every network arithmetic (narrower networks zero-padded to width 32) and has the reverse mode: nco_backward returns
- * the gradient in this parameter order.  nco_batch_step refuses
+ * every network arithmetic (narrower networks zero-padded as above; to width
+ * 32 throughout in float64 storage) and has the reverse mode: nco_backward
+ * returns the gradient in this parameter order.  nco_batch_step refuses
  * depth-3 lattices.  Setting the weights drops a recorded run. */
 int nco_set_net_weights_depth(nco_lattice* lat, int depth, int width, int act, int mlp_prec,
                               const float* params, size_t n_params);
@@ -389,8 +391,9 @@ int nco_forward_record_energy(nco_lattice* lat, int nsteps, int ckpt_every, int 
  * recomputed steps run the lattice's own network arithmetic; the adjoint
  * differentiates the network in float32: on the matrix cores for the
  * matrix-core networks (NCO_MLP_F32_MFMA, and NCO_MLP_F32_SPLIT and
- * NCO_MLP_BF16, whose product rounding it does not differentiate), on the
- * vector units for NCO_MLP_F32. */
+ * NCO_MLP_BF16, whose product rounding it does not differentiate; tanh folded
+ * into the weights at depth 2, tanh itself at depth 3), on the vector units for
+ * NCO_MLP_F32. */
 int nco_backward(nco_lattice* lat, const double* dL_dE, int nbins, const double* dL_df, double* grad,
                  size_t n_params, double* dL_df0);
 

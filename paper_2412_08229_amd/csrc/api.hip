@@ -773,7 +773,8 @@ int nco_set_net_weights_depth(nco_lattice* lat, int depth, int width, int act, i
         // Narrower networks run zero-padded to width 32: a padded hidden unit
         // has zero weights and bias and zero outgoing weights, so it adds
         // nothing to the next layer for either activation.
-        lat->net_host = W < 32 ? pad_params(params, W, 2, 32) : std::vector<float>(params, params + n_params_depth(W, depth));
+        lat->net_host = W < 32 ? pad_params(params, W, 2, 32)
+                               : std::vector<float>(params, params + n_params_depth(W, depth));
         std::vector<char> tab = net_table(lat, mlp_prec);
         const char* folded = nullptr;               // the float32 network's table, if that is it
         const size_t tb = tab.size();
@@ -925,7 +926,7 @@ int nco_batch_step(nco_lattice** lats, int n, const int* nsteps) {
         for (int j = 0; j < i; ++j)
             if (lats[j] == lat) return fail(NCO_E_INVALID, "lattice %d appears twice", i);
         if (lat->op == NCO_OP_NCO && !use_mfma(lat))
-            return fail(NCO_E_UNSUPPORTED, "batched NCO lattices need the matrix-core network (width 32)");
+            return fail(NCO_E_UNSUPPORTED, "batched NCO lattices need the folded, split or bf16 network arithmetic");
         if (lat->op == NCO_OP_STREAM) return fail(NCO_E_UNSUPPORTED, "batched streaming-only lattices");
         if (lat->phase_rule) return fail(NCO_E_UNSUPPORTED, "batched lattices with the velocity-dependent forcing phase");
         if (lat->depth != 2) return fail(NCO_E_UNSUPPORTED, "batched lattices with a third hidden layer");
@@ -935,7 +936,8 @@ int nco_batch_step(nco_lattice** lats, int n, const int* nsteps) {
     // Kernel kind of each lattice; chunks of up to GROUP_MAX lattices of one
     // kind share a dispatch per step.
     auto kind = [](const nco_lattice* l) {
-        return l->op == NCO_OP_NCO ? 1000 + 100 * l->storage + 10 * l->mlp_prec + 2 * (l->user_width <= 20) + l->act : 10 * l->storage + l->op;
+        if (l->op != NCO_OP_NCO) return 10 * l->storage + l->op;
+        return 1000 + 100 * l->storage + 10 * l->mlp_prec + 2 * (l->user_width <= 20) + l->act;
     };
     std::vector<int> order(n);
     for (int i = 0; i < n; ++i) order[i] = i;

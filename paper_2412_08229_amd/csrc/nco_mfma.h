@@ -7,10 +7,14 @@
 //     Z2_g = W2^T H1 + b2        (32 x 32) (32 x 16)
 //     acc += act(Z2_g)           summed over the 48 elements g of O_h
 //     tilde tau = W3^T acc / 48 + b3
-// in one of two arithmetics:
-//   PREC_F32  v_mfma_f32_16x16x4f32 (float32 operands and accumulation);
-//   PREC_BF16 v_mfma_f32_16x16x32_bf16 (bf16 operands, float32 accumulation,
-//             activations and group sum in float32).
+// in one of these arithmetics:
+//   F32_FULL  v_mfma_f32_16x16x4f32 (float32 operands and accumulation), tanh
+//             itself;
+//   F32       the same products, tanh folded into the weights (net_f32.h);
+//   BF16      v_mfma_f32_16x16x32_bf16 (bf16 operands, float32 accumulation,
+//             activations and group sum in float32);
+//   F32S      float32 operands split into 16-bit parts, whose products run on
+//             the f16 or bf16 matrix cores (split_layer).
 //
 // Group structure.  An element g of O_h is an axis permutation pi followed by
 // axis reflections s in {+-1}^3.  Every row of M is a product of
@@ -38,7 +42,8 @@
 // to LDS.  Phase B: each wavefront runs the network for its 64 nodes, 16 at a
 // time, and writes the four rates per node to LDS.  Phase C: each thread pulls
 // its populations again (the kernel is compute bound; the second read is
-// cheap), relaxes with the rates and stores.
+// cheap), relaxes with the rates and stores.  Smaller lattices take other block
+// shapes (launch_kind).
 //
 // One source per arithmetic instantiates the kernels (nco_mfma.hip float32,
 // nco_mfma_full.hip float32 without the folding of tanh, nco_mfma_split.hip,
