@@ -13,14 +13,14 @@
 // rows, without padding.
 //
 // What bounds it: the float64 tanh (1,536 wavefront evaluations per 16-node
-// tile at width 32, 22 float64 instructions each) and then the products (148
+// tile at width 32, 24 instructions each) and then the products (148
 // per axis permutation, 64 cycles each).  One tile per wavefront and four
 // per block, so that a 40^3 lattice gives each SIMD four wavefronts; the
 // weights of the products come from LDS (read by every wavefront of the
 // block, 10 B/cycle), which leaves the registers to the 64 pre-activations
 // of a permutation.  A 40^3 step of the 27-32-32-4 tanh network: 19.4 ms on
 // the vector units (one lane per node, all weights unrolled: 8 KB of scratch
-// per lane), 0.259 ms here.
+// per lane), 0.262 ms here.
 #include <algorithm>
 #include <cmath>
 #include <cstring>

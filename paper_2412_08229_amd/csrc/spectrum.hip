@@ -354,12 +354,13 @@ __global__ __launch_bounds__(256) void k_lambda_from_u(const double2* __restrict
 // Passes of the spectrum: the x pass forms the velocity of its rows from the
 // populations itself (three lines per row) and writes the half spectrum
 // k_x <= n / 2 in rows of n / 2 + 1; the z pass bins |u_hat|^2 into shells in
-// LDS and writes one sum per block and shell.  What bounds them: the state is
-// read once (1.8 GB at 256^3 in float32) and the half spectrum moves four
-// times (0.4 GB each).  256^3, float32 state: x 0.64 ms, y 0.31, z with the
-// shells 0.47, together with the host side of a readout 1.29 ms where the
-// velocity, direct transforms and shells took 4.29 (128^3 0.22 against 0.47,
-// 64^3 0.059 against 0.186).
+// LDS and writes one sum per block and shell.  The state is read once
+// (1.8 GB at 256^3 in float32) and the half spectrum moves four times (0.4 GB
+// each), but what bounds them is their vector instructions: 85-91 % of the issue
+// cycles in every pass.  256^3, float32 state: x 0.58-0.67 ms, y 0.28-0.32, z with
+// the shells 0.42-0.49, a readout 1.29-1.52 ms where the velocity, direct
+// transforms and shells took 4.29 (128^3 0.22 against 0.47, 64^3 0.059 against
+// 0.186).
 constexpr int FT_THREADS = 512;
 constexpr int FT_CAP = 2304;                    // LDS elements of the lines: n (C + 1), 256 x 9
 constexpr int FT_SMALL = 256, FT_LARGE = 576;   // twiddles held (two blocks per CU up to 256; 576 (3 + 1) fills FT_CAP)
