@@ -1022,9 +1022,11 @@ int nco_set_forcing_ex(nco_lattice* lat, int n_modes, const int* k, const double
     if (n_modes > 0 && lat->domain != NCO_DOMAIN_PERIODIC)
         return fail(NCO_E_UNSUPPORTED, "spectral forcing needs the periodic domain");
     int kx_max = 0;
-    for (int m = 0; m < n_modes; ++m) kx_max = std::max(kx_max, std::abs(k[3 * m]));
-    if (kx_max > FORCE_KX_MAX)
-        return fail(NCO_E_UNSUPPORTED, "forced wavevectors need |k_x| <= %d (got %d)", FORCE_KX_MAX, kx_max);
+    for (int m = 0; m < n_modes; ++m) {
+        if (k[3 * m] > FORCE_KX_MAX || k[3 * m] < -FORCE_KX_MAX)
+            return fail(NCO_E_UNSUPPORTED, "forced wavevectors need |k_x| <= %d (got %d)", FORCE_KX_MAX, k[3 * m]);
+        kx_max = std::max(kx_max, std::abs(k[3 * m]));
+    }
     if (int rc = set_device(lat)) return rc;
     HIP_TRY(hipStreamSynchronize(lat->stream));
     if (lat->d_fk) HIP_TRY(hipFree(lat->d_fk));

@@ -133,7 +133,7 @@ struct ModeChunk {
     int kx[3], begin, end;      // entries [begin, end)
 };
 struct ModeEntry {
-    int place, kz;              // kz: the component across the planes of the sums
+    int place, kz;              // kz: the component across the planes, modulo their number
 };
 struct ModeList {
     int groups, chunks;

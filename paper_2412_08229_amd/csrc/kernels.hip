@@ -613,11 +613,14 @@ ModeLayout::ModeLayout(const int* k, int n_modes, int nx, int ny, int nz) {
         bool xneg, yneg;
     };
     std::vector<Mode> modes(n_modes);
+    // e^{i 2 pi k y / n} depends on k modulo n: the remainder of least magnitude.
+    auto remainder = [](int k, int n) {
+        const long r = k % n;
+        return (int)(2 * r > n ? r - n : 2 * r < -n ? r + n : r);
+    };
     for (int m = 0; m < n_modes; ++m) {
-        long y = k[3 * m + iy] % grid.n1;       // e^{i 2 pi k_y y / ny} depends on k_y modulo ny
-        if (2 * y > grid.n1) y -= grid.n1;
-        if (2 * y < -grid.n1) y += grid.n1;
-        modes[m] = Mode{m, std::abs(k[3 * m]), (int)std::abs(y), k[3 * m] < 0, y < 0};
+        const int y = remainder(k[3 * m + iy], grid.n1);
+        modes[m] = Mode{m, std::abs(k[3 * m]), std::abs(y), k[3 * m] < 0, y < 0};
     }
     std::sort(modes.begin(), modes.end(), [](const Mode& a, const Mode& b) {
         return a.ay != b.ay ? a.ay < b.ay : a.m < b.m;
@@ -646,7 +649,8 @@ ModeLayout::ModeLayout(const int* k, int n_modes, int nx, int ny, int nz) {
                     if (kx + 1 == MODES_K) break;
                     c.kx[++kx] = m.ax;
                 }
-                entries.push_back(ModeEntry{mode_place(m.m, kx, in[j].first, m.xneg, m.yneg), k[3 * m.m + iz]});
+                entries.push_back(ModeEntry{mode_place(m.m, kx, in[j].first, m.xneg, m.yneg),
+                                            remainder(k[3 * m.m + iz], grid.n2)});
             }
             c.end = (int)entries.size();
             chunk.push_back(c);

@@ -27,7 +27,7 @@ namespace nco {
 // products shared by the modes that need them, and each mode combines four of
 // the block's totals with its signs and its z phase.  Which wavenumbers make a
 // group, and which |k_x| meet it, is laid out once per set of modes
-// (mode_list): only those that occur, k_y modulo ny.
+// (ModeLayout): only those that occur, k_y and k_z modulo ny and nz.
 //
 // What bounds it: reading the state (the velocity of a 256^3 float32 lattice:
 // 1.8 GB), once for up to MODES_M GROUPS distinct |k_y|.  A phase per mode and

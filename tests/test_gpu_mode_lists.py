@@ -6,6 +6,7 @@ import pytest
 
 from oracle import adjoint, collision, forcing, step
 from paper_2412_08229_amd import Lattice, inputs
+from paper_2412_08229_amd import _lib as L
 
 pytestmark = pytest.mark.gpu
 
@@ -153,3 +154,21 @@ def test_work_space_of_thin_lattices(shape):
         lat.set_forcing(ks, inputs.uniform_draws(1, modes, 6), 1e-6, 1.5, 400.0, phase_rule=True)
         used = before - torch.cuda.mem_get_info()[0]
     assert used <= 12 * n + 48 * modes * n // 256 + (64 << 20)
+
+
+@pytest.mark.parametrize("turns", [1, -1, 142857143, None])
+def test_wavenumbers_beyond_the_planes(turns):
+    """k_z = turns nz + r acts like r, down to the most negative integer, whose
+    magnitude an int does not hold."""
+    base = -2 ** 31 if turns is None else turns * SHAPE[0]
+    ks = [[kx, ky, base + r] for r in (0, 1, 2) for kx, ky in ((0, 1), (-2, 3), (5, -2))]
+    kk = float(abs(base))
+    _check(ks, 1e-6 * kk ** 2, kk, kk ** 2)
+
+
+@pytest.mark.parametrize("kx", [17, -17, -2 ** 31, 2 ** 31 - 1])
+def test_large_kx_is_refused(kx):
+    with Lattice((4, 4, 4), "f32", "bgk", 0.6) as lat:
+        with pytest.raises(L.NCOError) as e:
+            lat.set_forcing(np.array([[kx, 1, 0]]), inputs.uniform_draws(1, 1, 6), 1e-6, 1.5, 4.0, phase_rule=True)
+        assert e.value.status == L.NCO_E_UNSUPPORTED
