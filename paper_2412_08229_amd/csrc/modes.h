@@ -18,11 +18,12 @@ namespace nco {
 // six doubles (Re, Im of x, y, z) at partial[(6 m + q) nblocks + block].
 //
 // A block takes up to 256 consecutive x and `rows` consecutive y of one z
-// plane (or z of one y plane: ModeGrid).  Thread t keeps to one x (and to the rows sub, sub + rp, ...: below
-// 256 nodes per row, rp rows run side by side) and accumulates its column's
-// sums of v cos(m y'), v sin(m y') (y' = 2 pi y / ny, from a table per block)
-// for the wavenumbers m = |k_y| of the modes, MODES_M of them to a group and
-// GROUPS groups to a pass over the nodes.  The columns' sums of a group then
+// plane (or z of one y plane: ModeGrid).  Thread t keeps to one x (and to the
+// rows sub, sub + rp, ...: below 256 nodes per row, rp rows run side by side)
+// and accumulates its column's sums of v cos(m y'), v sin(m y') (y' =
+// 2 pi y / ny, from a table per block) for the wavenumbers m = |k_y| of the
+// modes, MODES_M of them to a group and GROUPS groups to a pass over the
+// nodes.  The columns' sums of a group then
 // meet the x phases of MODES_K of its modes' wavenumbers |k_x| in LDS, all
 // products shared by the modes that need them, and each mode combines four of
 // the block's totals with its signs and its z phase.  Which wavenumbers make a
@@ -82,7 +83,9 @@ inline ModeGrid mode_grid(int nx, int ny, int nz) {
 
 // A mode's place in its contraction: among the contraction's |k_x| and the
 // group's |k_y|, and the signs of k_x and of k_y modulo ny.
-constexpr int mode_place(int mode, int ix, int iy, bool nx, bool ny) { return mode << 6 | ny << 5 | nx << 4 | iy << 2 | ix; }
+constexpr int mode_place(int mode, int ix, int iy, bool xneg, bool yneg) {
+    return mode << 6 | yneg << 5 | xneg << 4 | iy << 2 | ix;
+}
 
 // value(idx, p, v): the field's three components v at node idx = (x, y, z) p.
 template <int GROUPS, int ROWS, typename F>

@@ -23,9 +23,10 @@
 // 4 r (1 - r); the 4 is folded into the transposed weights and W3 (exactly, a
 // power of 2).  At depth 3 tanh itself on the unfolded weights, act' = 1 - h^2:
 // h = 1 - 2 r is right to 6e-8 of one, and the gradient of a layer fed by small
-// activations would be no better than that over their size.  The
-// group sum H of the output layer's gradient is added up here as well, not
-// unfolded from the forward step's.  It costs 17-25 % of a reverse step: 16^3 63 -> 74 us, 64^3 1707 -> 2139.
+// activations would be no better than that over their size.  The group sum H
+// of the output layer's gradient is added up here as well, not unfolded from
+// the forward step's.  It costs 17-25 % of a reverse step: 16^3 63 -> 74 us,
+// 64^3 1707 -> 2139.
 //
 // Products over nodes.  h and dz go through a per-wavefront LDS buffer
 // [hidden][node] of row stride 20: a lane reads the nodes 4 q .. 4 q + 3 of
